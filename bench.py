@@ -175,8 +175,9 @@ def traffic_for(phase: str, workload: str):
 
 # the sources that define the kernels (host-only API code does not change
 # what a kernel moves)
-KERNEL_SOURCES = ["kc_batched.hip", "kc_batched.hpp", "kc_bin_hash.hpp", "kc_binned.hip", "kc_device.hpp",
-                  "kc_kernels.hip", "kc_kernels.hpp", "kc_scan.hip"]
+KERNEL_SOURCES = ["kc_batched.hip", "kc_batched.hpp", "kc_bin_hash.hpp", "kc_binned.hip", "kc_blocks.hip",
+                  "kc_blocks.hpp", "kc_device.hpp", "kc_kernels.hip", "kc_kernels.hpp", "kc_region.hpp",
+                  "kc_scan.hip"]
 
 
 def code_text(src: str) -> str:

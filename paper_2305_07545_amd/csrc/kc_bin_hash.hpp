@@ -87,6 +87,45 @@ __device__ __forceinline__ void window_counters(const FilterArgs &F,
     }
 }
 
+// The code words that hold the window at position q of codes (q % 16 bases
+// into the first).
+template <bool kWide>
+struct WindowWords {
+    uint32_t w[kWide ? 5 : 3];
+    __device__ __forceinline__ WindowWords(const uint32_t *__restrict__ codes, uint32_t q) {
+#pragma unroll
+        for (int i = 0; i < (kWide ? 5 : 3); i++)
+            w[i] = codes[(q >> 4) + i];
+    }
+};
+
+// The counters of the window at position q, from its code words, for the
+// first kKh hash functions at most, unrolled: emit(a, r, local) for a = 0 ..
+// min(kKh, k_h) - 1.
+template <bool kFast, bool kWide, int kKh, typename Emit>
+__device__ __forceinline__ void window_entries(const FilterArgs &F, const WindowWords<kWide> &W,
+                                               uint32_t q, uint32_t K, uint32_t shift,
+                                               Emit emit) {
+    uint32_t r, local;
+    if constexpr (kWide) {
+        const CanonWide c = canonical_wide(window_key_wide(W.w, q & 15u, K), K);
+#pragma unroll
+        for (int a = 0; a < kKh; a++)
+            if (a == 0 || (uint32_t)a < F.k_h) {
+                counter_of<kFast>(F, a == 0 ? c.h1 : hash_a_wide(c.b, a + 1), shift, r, local);
+                emit(a, r, local);
+            }
+    } else {
+        const Canon c = canonical_fast(window_key32(W.w, q & 15u, K), K);
+#pragma unroll
+        for (int a = 0; a < kKh; a++)
+            if (a == 0 || (uint32_t)a < F.k_h) {
+                counter_of<kFast>(F, a == 0 ? c.h1 : hash_a(c.b0, c.b1, a + 1), shift, r, local);
+                emit(a, r, local);
+            }
+    }
+}
+
 // The windows of positions [g0, g1) (g0 a multiple of 64), 64 positions
 // per wavefront at a time (wave w takes g0 + 64 w, then every kBinWG
 // positions).  Validity comes from the valid-window bitmap (R.valid, one

@@ -27,8 +27,10 @@
 #include <cstdlib>
 
 #include "kc_bin_hash.hpp"
+#include "kc_blocks.hpp"
 #include "kc_device.hpp"
 #include "kc_kernels.hpp"
+#include "kc_region.hpp"
 
 namespace kc {
 
@@ -80,13 +82,6 @@ struct RawEntry {
     uint32_t lo, hi;
 };
 
-// Element at a 32-bit byte offset from a wavefront-uniform base: the address
-// is the base's scalar registers plus one 32-bit vector register, not a
-// 64-bit address per thread.
-template <typename T>
-__device__ __forceinline__ T &at_byte(T *base, uint32_t byte_off) {
-    return *(T *)((char *)base + byte_off);
-}
 static_assert(kStage == (1 << kStageLog), "stage size");
 static_assert(kRegionCounters == (1 << kLocalBits), "region size");
 static_assert(kMaxRegions == (1u << kPartLog), "partition size");
@@ -786,64 +781,6 @@ __global__ void __launch_bounds__(kThreads) k_bin_bucket_list(const uint64_t *__
     }
 }
 
-// Where the region pass puts a first-seen occurrence (chunk-relative t and
-// its mark: 1 distinct, 3 distinct and trustworthy): its flag byte, or, in
-// records mode, a record in the region's own entry segment (whose entries
-// the workgroup has read by then: every winner is one of them), which the
-// winner passes below turn into flag bytes written in whole 16-byte groups.
-struct WinnerSink {
-    uint8_t *flags;
-    uint64_t c0;
-    uint32_t *rec_t;  // records or carry mode: the records' word array (null: flag mode)
-    uint16_t *rec_m;  // ... and half array: the mark, or in carry mode the local counter
-    uint64_t e0;      // the region's first record
-    uint32_t *count;  // LDS: records written so far
-    bool carry;       // carry mode: the half is the local counter id
-};
-
-__device__ __forceinline__ void put_winner(const WinnerSink &o, uint32_t t, uint32_t mark,
-                                           uint32_t local) {
-    if (!o.rec_t) {
-        o.flags[o.c0 + t] = (uint8_t)mark;
-        return;
-    }
-    const uint32_t i = atomicAdd(o.count, 1u);  // < the region's entries
-    at_byte(o.rec_t + o.e0, 4u * i) = t;
-    at_byte(o.rec_m + o.e0, 2u * i) = (uint16_t)(o.carry ? local : mark);
-}
-
-// Counter update of cell w of the region (pre = its value before the
-// chunk); returns the cell's new value.  Leaves the cell's counters clean
-// (hits 0, first kIdle) for the next region.
-__device__ __forceinline__ uint64_t region_cell(const FilterArgs &F, const BinPlan &B,
-                                                uint64_t wbase, uint32_t w, uint64_t pre,
-                                                uint32_t *hits, uint32_t *first,
-                                                const WinnerSink &out, int classify,
-                                                uint32_t tau) {
-    // counters are at most 32 bits wide: the field arithmetic is 32-bit
-    const uint32_t fm = (uint32_t)F.field_max;
-    uint64_t next = pre;
-    for (uint32_t l = 0; l < F.eta; l++) {
-        const uint32_t idx = (l << B.region_shift) | w;
-        const uint32_t h = hits[idx];
-        if (h == 0)
-            continue;
-        const uint32_t t = first[idx];
-        hits[idx] = 0;
-        first[idx] = kIdle;
-        const uint32_t sh = F.alpha * l;
-        const uint32_t pf = (uint32_t)(pre >> sh) & fm;
-        const uint32_t room = fm - pf;
-        const uint32_t nf = pf + (h < room ? h : room);
-        next += (uint64_t)(nf - pf) << sh;  // the field grows without carrying out
-        if (pf == 0)
-            put_winner(out, t, (classify && nf > tau) ? 3u : 1u, idx);
-    }
-    if (next != pre)
-        F.words[wbase + w] = next;
-    return next;
-}
-
 // s_waitcnt vmcnt(0) in the gfx9 encoding, with expcnt and lgkmcnt left
 // open: a wavefront's vector loads and stores all complete.
 constexpr int kWaitVmem = 0x0F70;
@@ -1119,14 +1056,14 @@ __global__ void __launch_bounds__(kRegionWG) k_region(FilterArgs F, uint64_t c0,
                     const uint32_t w = threadIdx.x + (uint32_t)k * kRegionWG;
                     if (w < R.nw) {
                         const uint64_t next =
-                            region_cell(F, B, R.wbase, w, cell[k], hits, first, out, classify, tau);
+                            region_cell(F, B.region_shift, R.wbase, w, cell[k], hits, first, out, classify, tau);
                         if (kTile && C.mode == Carry::kIn)
                             s_cell[w] = next;
                     }
                 }
             } else {
                 for (uint32_t w = threadIdx.x; w < R.nw; w += kRegionWG)
-                    region_cell(F, B, R.wbase, w, F.words[R.wbase + w], hits, first, out,
+                    region_cell(F, B.region_shift, R.wbase, w, F.words[R.wbase + w], hits, first, out,
                                 classify, tau);
             }
         }
@@ -1460,11 +1397,12 @@ bool records_mode(uint64_t len) {
 }
 
 // The winner passes of one chunk [c0, c0 + len): its records, region r's
-// n_win[r] of them at offsets[r * off_stride] of the word and half arrays.
+// n_win[r] of them at offsets[r * off_stride] of the word and half arrays;
+// area_a, area_b: the entry buffers, the records' own not the first.
 hipError_t winner_passes(uint32_t n_regions, const uint32_t *offsets, uint64_t off_stride,
                          const uint32_t *n_win, const uint32_t *rec_word,
-                         const uint16_t *rec_half, uint64_t c0, uint64_t len, const Workspace &W,
-                         hipStream_t s, Profiler *P) {
+                         const uint16_t *rec_half, uint64_t c0, uint64_t len, uint32_t *area_a,
+                         uint32_t *area_b, const Workspace &W, hipStream_t s, Profiler *P) {
     uint32_t *cursors = W.win_cursors;  // kWinBuckets level-A, then the blocks' level-B cursors
     const uint32_t n_a = (uint32_t)((len + (1ull << kWinA) - 1) >> kWinA);
     const uint32_t n_blocks = (uint32_t)((len + (1ull << kWinB) - 1) >> kWinB);
@@ -1475,18 +1413,18 @@ hipError_t winner_passes(uint32_t n_regions, const uint32_t *offsets, uint64_t o
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_win_a, dim3((n_regions + kWinRegions - 1) / kWinRegions),
                            dim3(kWinThreads), 0, s, n_regions, offsets, off_stride, n_win,
-                           rec_word, rec_half, cursors, (uint32_t *)W.bucketed);
+                           rec_word, rec_half, cursors, area_a);
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_win_b, dim3(n_a, kWinSlices), dim3(kWinThreads), 0, s,
-                           (const uint32_t *)W.bucketed, (const uint32_t *)cursors,
-                           cursors + kWinBuckets, (uint32_t *)W.entries);
+                           (const uint32_t *)area_a, (const uint32_t *)cursors,
+                           cursors + kWinBuckets, area_b);
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_win_flags, dim3(n_blocks), dim3(kWinThreads), 0, s,
-                           (const uint32_t *)W.entries, (const uint32_t *)(cursors + kWinBuckets),
+                           (const uint32_t *)area_b, (const uint32_t *)(cursors + kWinBuckets),
                            c0, len, W.flags8);
         e = hipGetLastError();
     }
@@ -1501,7 +1439,15 @@ hipError_t launch_winner_passes(const BinPlan &Q, uint64_t c0, uint64_t len, con
                                 const uint32_t *n_win, hipStream_t s, Profiler *P) {
     const uint32_t *e_word = (const uint32_t *)W.entries;
     return winner_passes(Q.n_regions, (const uint32_t *)W.matrix, Q.G, n_win, e_word,
-                         (const uint16_t *)(e_word + Q.entries_cap), c0, len, W, s, P);
+                         (const uint16_t *)(e_word + Q.entries_cap), c0, len,
+                         (uint32_t *)W.bucketed, (uint32_t *)W.entries, W, s, P);
+}
+
+hipError_t launch_record_winners(uint32_t n_regions, const uint32_t *off, const uint32_t *n,
+                                 const uint32_t *word, const uint16_t *half, uint64_t c0,
+                                 uint64_t len, const Workspace &W, hipStream_t s, Profiler *P) {
+    return winner_passes(n_regions, off, 1, n, word, half, c0, len, (uint32_t *)W.entries,
+                         (uint32_t *)W.bucketed, W, s, P);
 }
 
 bool carry_fits(const BinPlan &plan) {
@@ -1534,7 +1480,7 @@ hipError_t launch_carried_winners(const BinPlan &plan, const Carry &carry, uint3
     const uint64_t at = (uint64_t)j * carry.stride;
     return winner_passes(plan.n_regions, carry.off + at, 1, carry.n + at,
                          carry.word + (uint64_t)j * carry.cap, carry.half + (uint64_t)j * carry.cap,
-                         c0, len, W, s, P);
+                         c0, len, (uint32_t *)W.bucketed, (uint32_t *)W.entries, W, s, P);
 }
 
 // ---------------------------------------------------------------------------
@@ -1792,6 +1738,10 @@ hipError_t launch_binned_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
         return launch_parts_chunk(F, R, c0, c1, plan, W, classify, tau, carry, s, P);
     if (c1 - c0 > kBinChunk || (c1 - c0) * F.k_h >= (1ull << 32))
         return hipErrorInvalidValue;  // the level-1 pass indexes in 32 bits
+    BlockPlan blocks;
+    if (block_plan(plan, F.k_h, c1 - c0, blocks))
+        return launch_blocks_chunk(F, R, c0, c1, plan, blocks, W, classify, tau, carry,
+                                   carry.mode != Carry::kOut && records_mode(c1 - c0), s, P);
     BinPlan B = plan;
     B.G = (uint32_t)((c1 - c0 + B.tile - 1) / B.tile);
     B.n_slices = (B.G + B.slice - 1) / B.slice;

@@ -1,0 +1,51 @@
+// Block-sorted entry lists of the binned insertion (host view).
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "kc_kernels.hpp"
+
+namespace kc {
+
+constexpr uint32_t kBlockLog = 15;  // a block holds at most 2^15 entries
+constexpr uint32_t kBlockEntries = 1u << kBlockLog;
+// Regions of a countBF the one-level form takes: the block's histogram fits
+// beside its entries in LDS, for two hashing workgroups of 16384 entries per
+// CU, or one of 32768.
+constexpr uint32_t kHalfRegions = 3584;
+constexpr uint32_t kBlockRegions = 7168;
+constexpr uint32_t kBlockPad = 80;  // entries of a block's stride beyond its room
+// Runs of up to this many entries (a block's room / regions) are short: the
+// region pass takes 64 blocks' runs at a time.
+constexpr uint32_t kShortRun = 16;
+
+// Blocks of one chunk: block b holds the entries of positions [b << pos_log,
+// (b + 1) << pos_log) of the chunk (every hash function's), sorted by region.
+struct BlockPlan {
+    uint32_t pos_log;   // log2(positions per block)
+    uint32_t cap;       // entries a block has room for (its stride in the list)
+    uint32_t n_blocks;
+    uint32_t row;       // 16-bit offsets per block in the table (regions + 1, even)
+    uint32_t kh;        // hash functions, rounded up to a power of two
+    uint32_t ept;       // entries per thread of the hashing kernel
+    uint32_t wg;        // threads of the hashing kernel
+    uint32_t turned;    // short runs: 16-bit offsets per region of the turned table, else 0
+};
+
+// Whether the one-level form takes a plan, and its blocks for `len` positions.
+bool block_plan(const BinPlan &plan, uint32_t k_h, uint64_t len, BlockPlan &B);
+
+// hash + sort + region pass of chunk [c0, c1).
+hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t c0, uint64_t c1,
+                               const BinPlan &plan, const BlockPlan &B, const Workspace &W,
+                               bool classify, uint32_t tau, const Carry &carry, bool records,
+                               hipStream_t s, Profiler *P);
+
+// The winner passes of chunk [c0, c0 + len) over records whose arrays lie in
+// W.bucketed (kc_binned.hip).
+hipError_t launch_record_winners(uint32_t n_regions, const uint32_t *off, const uint32_t *n,
+                                 const uint32_t *word, const uint16_t *half, uint64_t c0,
+                                 uint64_t len, const Workspace &W, hipStream_t s, Profiler *P);
+
+}  // namespace kc
