@@ -338,13 +338,13 @@ typedef enum {
     KC_PHASE_CLASSIFY_SCATTER = 8,/* ordered trustworthy / erroneous output */
     KC_PHASE_QUERY = 9,           /* kc_query */
     KC_PHASE_RESET = 10,          /* kc_reset / kc_create clears */
-    KC_PHASE_BIN_COUNT = 11,      /* binned path: per-region entry counts */
-    KC_PHASE_BIN_BUCKET = 12,     /* binned path: entries grouped by bucket of regions */
+    KC_PHASE_BIN_COUNT = 11,      /* binned path: hashing, entries sorted within blocks */
+    KC_PHASE_BIN_BUCKET = 12,     /* batched form: entries grouped by region */
     KC_PHASE_REGION = 13,         /* binned path: LDS counting + first-seen per region */
     KC_PHASE_TILE_COUNT = 14,     /* per-tile distinct / trustworthy / window counts */
-    KC_PHASE_BIN_REGION = 15,     /* binned path: bucket slices -> region segments */
-    KC_PHASE_BIN_PART = 16,       /* partitioned path: entries grouped by partition */
-    KC_PHASE_PART_COUNT = 17,     /* partitioned path: per-partition region counts */
+    KC_PHASE_BIN_REGION = 15,     /* binned path: runs of the blocks arranged by region */
+    KC_PHASE_BIN_PART = 16,       /* partitioned path: hashing, entries sorted by bucket */
+    KC_PHASE_PART_COUNT = 17,     /* partitioned path: buckets counted and sorted by region */
     KC_PHASE_VALID = 18,          /* binned paths: valid-window bitmap of the call's k */
     KC_PHASE_WINNERS = 19,        /* binned paths, chunks beyond 2^28 positions: first-seen
                                      records -> flag bytes */

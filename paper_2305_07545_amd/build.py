@@ -2,7 +2,10 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -19,23 +22,38 @@ FLAGS = [
     "-O3",
     "-std=c++17",
     "-fPIC",
-    "-shared",
     "-Wall",
     # keep the compiler from forming packed fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 
 
-def _compile(sources, out, verbose):
-    tmp = out + ".tmp"
-    cmd = [HIPCC, *FLAGS, "-I", INCLUDE, "-I", CSRC,
-           *[os.path.join(CSRC, s) for s in sources], "-o", tmp]
+def _run(cmd, what, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed for {out}:\n{r.stdout}")
-    os.replace(tmp, out)
+        raise RuntimeError(f"hipcc failed for {what}:\n{r.stdout}")
+
+
+def _compile(sources, out, verbose):
+    """Compile the sources side by side and link them into ``out``."""
+    work = tempfile.mkdtemp(prefix="kmerco_build_")
+    try:
+        objects = [os.path.join(work, s + ".o") for s in sources]
+
+        def one(pair):
+            src, obj = pair
+            _run([HIPCC, *FLAGS, "-I", INCLUDE, "-I", CSRC, "-c", os.path.join(CSRC, src), "-o", obj],
+                 src, verbose)
+
+        with ThreadPoolExecutor(max_workers=min(8, len(sources))) as pool:
+            list(pool.map(one, zip(sources, objects)))
+        tmp = out + ".tmp"
+        _run([HIPCC, *FLAGS, "-shared", *objects, "-o", tmp], out, verbose)
+        os.replace(tmp, out)
+    finally:
+        shutil.rmtree(work, ignore_errors=True)
     return out
 
 

@@ -18,6 +18,8 @@
 // position.
 #include <hip/hip_runtime.h>
 
+#include <utility>
+
 #include "kc_bin_hash.hpp"
 #include "kc_blocks.hpp"
 #include "kc_device.hpp"
@@ -29,6 +31,17 @@ namespace kc {
 namespace {
 
 static_assert(kBlockLog + kLocalBits <= 32, "an entry holds the counter and the position");
+constexpr int kSubShift = kBlockLog + kLocalBits;  // two-level form: the region within the bucket
+static_assert(kSubShift + kMaxSubLog <= 40, "a 5-byte entry holds it");
+static_assert(kLocalBits + kSuperLog <= 40, "a 5-byte entry holds the counter and a position");
+
+// fn(0) .. fn(n - 1), each with its number as a constant: the hashing steps
+// keep their results in registers, so they have to be unrolled whatever the
+// size of one.
+template <int... kJ, typename Fn>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, kJ...>, Fn fn) {
+    (fn(std::integral_constant<int, kJ>{}), ...);
+}
 
 // Inclusive sum over the wavefront (row shifts, then row broadcasts).
 __device__ __forceinline__ uint32_t wave_inclusive(uint32_t x) {
@@ -44,7 +57,9 @@ __device__ __forceinline__ uint32_t wave_inclusive(uint32_t x) {
 }  // namespace
 
 // Hash every valid window of the block once and write the block's entries
-// sorted by region.  kEpt: entries per thread (kKh hash functions x
+// sorted by bin: by region, or, in the two-level form (kTwo), by bucket of
+// 2^sub_log regions, the region within the bucket being the 11 high bits of a
+// 5-byte entry (the fifth bytes in an array of their own).  kEpt: entries per thread (kKh hash functions x
 // positions); kFast, kWide as k_bin_count.
 //
 // The block's valid windows are first listed in LDS (in the space the sorted
@@ -54,22 +69,22 @@ __device__ __forceinline__ uint32_t wave_inclusive(uint32_t x) {
 // its vector instructions (82% busy; 144 per 64 windows, 117 of them the
 // hash): 0.55 ms for the bacterial workload's 116 M windows, where hashing
 // alone and writing slot ids took 0.42.
-template <int kWG, int kEpt, int kKh, bool kFast, bool kWide>
+template <int kWG, int kEpt, int kKh, bool kFast, bool kWide, bool kTwo>
 __global__ void __launch_bounds__(kWG, 4)
 k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t c0, uint64_t c1, BlockPlan B, uint32_t shift,
-            uint32_t n_regions, uint32_t *__restrict__ list, uint16_t *__restrict__ table,
-            unsigned long long *__restrict__ n_valid) {
+            uint32_t *__restrict__ list, uint8_t *__restrict__ list_hi,
+            uint16_t *__restrict__ table, unsigned long long *__restrict__ n_valid) {
     constexpr int kSteps = kEpt / kKh;
     constexpr uint32_t kPos = kSteps * kWG;    // positions per block
     constexpr uint32_t kEntries = kEpt * kWG;  // room for its entries
     static_assert(kEntries <= kBlockEntries, "entries are staged in LDS");
-    extern __shared__ uint32_t s_hist[];  // counts, then starts, per region
+    extern __shared__ uint32_t s_hist[];  // counts, then starts, per bin
     __shared__ __align__(16) uint32_t s_stage[kEntries];
     __shared__ uint32_t s_wave[kWG / 64];
     uint16_t *s_list = reinterpret_cast<uint16_t *>(s_stage);
-    const uint32_t lane = threadIdx.x & 63u, wave = wave_id();
+    const uint32_t lane = threadIdx.x & 63u, wave = wave_id(), n_bins = B.n_bins;
     constexpr uint32_t kWaves = kWG / 64;
-    for (uint32_t i = threadIdx.x; i < n_regions; i += kWG)
+    for (uint32_t i = threadIdx.x; i < n_bins; i += kWG)
         s_hist[i] = 0;
     const uint64_t p0 = c0 + (uint64_t)blockIdx.x * kPos;
     uint32_t nv;
@@ -109,7 +124,8 @@ k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t c0, uint64_t c1, BlockPlan B, ui
     const uint32_t *__restrict__ codes = R.codes + (p0 >> 4);
     const uint32_t K = R.k, k_h = kFast ? 1u : F.k_h;
     uint32_t ent[kEpt];  // counter | position << kLocalBits
-    uint32_t key[kEpt];  // region | rank << 16
+    uint32_t key[kEpt];  // bin | rank << 16
+    uint32_t high[kTwo ? (kEpt + 3) / 4 : 1];  // the entries' fifth bytes
     // A step's code words are requested a step before they are hashed, and a
     // rank is taken in a step after its atomic, so that neither is waited for.
     auto position = [&](int j) -> uint32_t {
@@ -119,8 +135,8 @@ k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t c0, uint64_t c1, BlockPlan B, ui
     uint32_t q = position(0), q_next = kSteps > 1 ? position(1) : 0u;
     WindowWords<kWide> w(codes, q);
     uint32_t rank[kKh];
-#pragma unroll
-    for (int j = 0; j < kSteps; j++) {
+    unrolled(std::make_integer_sequence<int, kSteps>{}, [&](auto step) {
+        constexpr int j = decltype(step)::value;
         const uint32_t i = (uint32_t)j * kWG + threadIdx.x;
         const WindowWords<kWide> wn(codes, q_next);
         const uint32_t q_after = j + 2 < kSteps ? position(j + 2) : 0u;
@@ -128,11 +144,21 @@ k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t c0, uint64_t c1, BlockPlan B, ui
         if (i < nv)
             window_entries<kFast, kWide, kKh>(
                 F, w, q, K, shift, [&](int a, uint32_t r, uint32_t local) {
-                    ent[j * kKh + a] = local | (q << kLocalBits);
-                    key[j * kKh + a] = r;
-                    old[a] = atomicAdd(&s_hist[r], 1u);
+                    constexpr int kFifth = 8;
+                    const int u = j * kKh + a;
+                    ent[u] = local | (q << kLocalBits);
+                    uint32_t bin = r;
+                    if (kTwo) {
+                        const uint32_t rl = r & ((1u << B.sub_log) - 1u);
+                        bin = r >> B.sub_log;
+                        ent[u] |= rl << kSubShift;
+                        const uint32_t hi = rl >> (32 - kSubShift);
+                        high[u / 4] = u % 4 ? high[u / 4] | (hi << (kFifth * (u % 4))) : hi;
+                    }
+                    key[u] = bin;
+                    old[a] = atomicAdd(&s_hist[bin], 1u);
                 });
-        if (j > 0) {
+        if constexpr (j > 0) {
 #pragma unroll
             for (int a = 0; a < kKh; a++)
                 key[(j - 1) * kKh + a] |= rank[a] << 16;
@@ -144,21 +170,21 @@ k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t c0, uint64_t c1, BlockPlan B, ui
         q_next = q_after;
         w = wn;
         __builtin_amdgcn_sched_barrier(0);
-    }
+    });
 #pragma unroll
     for (int a = 0; a < kKh; a++)
         key[(kSteps - 1) * kKh + a] |= rank[a] << 16;
     __syncthreads();
     {  // counts -> starts, in place: each wavefront scans a share of the
        // regions, 64 at a time, then adds the shares before its own
-        const uint32_t share = (n_regions + kWG - 1) / kWG * 64u;
+        const uint32_t share = (n_bins + kWG - 1) / kWG * 64u;
         const uint32_t r0 = wave * share;
         uint32_t run = 0;
         for (uint32_t u = 0; u < share; u += 64) {
             const uint32_t r = r0 + u + lane;
-            const uint32_t c = r < n_regions ? s_hist[r] : 0u;
+            const uint32_t c = r < n_bins ? s_hist[r] : 0u;
             const uint32_t incl = wave_inclusive(c);
-            if (r < n_regions)
+            if (r < n_bins)
                 s_hist[r] = run + incl - c;
             run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         }
@@ -171,15 +197,15 @@ k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t c0, uint64_t c1, BlockPlan B, ui
             before += w < wave ? s_wave[w] : 0u;
         for (uint32_t u = 0; u < share; u += 64) {
             const uint32_t r = r0 + u + lane;
-            if (r < n_regions)
+            if (r < n_bins)
                 s_hist[r] += before;
         }
     }
     __syncthreads();
     const uint32_t total = nv * k_h;
     uint16_t *__restrict__ trow = table + (uint64_t)blockIdx.x * B.row;
-    for (uint32_t i = threadIdx.x; i <= n_regions; i += kWG)
-        trow[i] = (uint16_t)(i < n_regions ? s_hist[i] : total);
+    for (uint32_t i = threadIdx.x; i <= n_bins; i += kWG)
+        trow[i] = (uint16_t)(i < n_bins ? s_hist[i] : total);
 #pragma unroll
     for (int j = 0; j < kSteps; j++)
         if ((uint32_t)j * kWG + threadIdx.x < nv) {
@@ -195,6 +221,25 @@ k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t c0, uint64_t c1, BlockPlan B, ui
     const uint4 *src = reinterpret_cast<const uint4 *>(s_stage);
     for (uint32_t i = threadIdx.x; i < (total + 3u) / 4u; i += kWG)
         out[i] = src[i];
+    if (kTwo) {  // the fifth bytes, sorted the same way in the same room
+        __syncthreads();
+        uint8_t *s_byte = reinterpret_cast<uint8_t *>(s_stage);
+#pragma unroll
+        for (int j = 0; j < kSteps; j++)
+            if ((uint32_t)j * kWG + threadIdx.x < nv) {
+#pragma unroll
+                for (int a = 0; a < kKh; a++)
+                    if (kKh == 1 || (uint32_t)a < k_h) {
+                        const int u = j * kKh + a;
+                        s_byte[s_hist[key[u] & 0xFFFFu] + (key[u] >> 16)] =
+                            (uint8_t)(high[u / 4] >> (8 * (u % 4)));
+                    }
+            }
+        __syncthreads();
+        uint4 *__restrict__ outb = reinterpret_cast<uint4 *>(list_hi + (uint64_t)blockIdx.x * B.cap);
+        for (uint32_t i = threadIdx.x; i < (total + 15u) / 16u; i += kWG)
+            outb[i] = src[i];
+    }
     if (threadIdx.x == 0)
         atomicAdd(n_valid, (unsigned long long)nv);
 }
@@ -221,6 +266,160 @@ k_turn_table(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, uint32
                 (uint32_t)t[2 * x][j] | ((uint32_t)t[2 * x + 1][j] << 16);
 }
 
+// Second level: the entries of bucket b in superblock sb (`super` blocks) ->
+// sorted by region, entries of 5 bytes again (the counter and the position
+// within the superblock).  Their place in the list needs no scan: the
+// superblock's room is its blocks' room, and the buckets before b hold as many
+// of its entries as b's runs start at, summed over the blocks.  starts[sb]
+// receives the place of every region's run.
+//
+// A team of 16 lanes takes a block's run, four entries a lane and step.  The
+// runs are read twice (count, then place; the second time from the caches),
+// which needs neither ranks nor entries held in registers.  More entries than
+// the LDS holds (a bucket favoured by the input) are placed straight in the
+// list.  Workgroups of one XCD take neighbouring buckets of a superblock at a
+// time, whose runs and table rows share cache lines.
+__global__ void __launch_bounds__(kMergeWG)
+k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
+        const uint8_t *__restrict__ list_hi, const uint16_t *__restrict__ table,
+        uint32_t *__restrict__ out, uint8_t *__restrict__ out_hi, uint32_t *__restrict__ starts) {
+    __shared__ __align__(16) uint32_t s_word[kMergeTile];
+    __shared__ uint8_t s_high[kMergeTile];
+    __shared__ uint32_t s_cursor[1u << kMaxSubLog];
+    __shared__ uint32_t s_wave[kMergeWG / 64];
+    __shared__ uint32_t s_sum;
+    constexpr uint32_t kTeam = 16, kTeams = kMergeWG / kTeam;
+    const uint32_t lane = threadIdx.x & 63u, wave = wave_id();
+    const uint32_t per = (B.n_bins + 7u) / 8u;  // buckets per XCD
+    const uint32_t b = (blockIdx.x & 7u) * per + (blockIdx.x >> 3) % per;
+    const uint32_t sb = (blockIdx.x >> 3) / per;
+    if (b >= B.n_bins)
+        return;
+    const uint32_t n_sub = 1u << B.sub_log;
+    for (uint32_t i = threadIdx.x; i < n_sub; i += kMergeWG)
+        s_cursor[i] = 0;
+    if (threadIdx.x == 0)
+        s_sum = 0;
+    __syncthreads();
+    const uint32_t k0 = sb * B.super;
+    const uint32_t k1 = k0 + B.super < B.n_blocks ? k0 + B.super : B.n_blocks;
+    const uint32_t team = threadIdx.x / kTeam, sub = threadIdx.x % kTeam;
+    // visit(word, fifth byte, block - k0) for every entry
+    auto each = [&](auto visit, uint32_t &sum) {
+        uint32_t s = 0, e = 0;
+        auto bounds = [&](uint32_t k) {
+            s = e = 0;
+            if (k < k1) {
+                const uint16_t *t = table + (uint64_t)k * B.row + b;
+                s = t[0];
+                e = t[1];
+            }
+        };
+        bounds(k0 + team);
+        for (uint32_t k = k0 + team; k < k1; k += kTeams) {
+            const uint32_t s0 = s, e0 = e;
+            const uint64_t base = (uint64_t)k * B.cap;
+            sum += sub == 0 ? s0 : 0u;
+            uint32_t g = (s0 & ~3u) + 4u * sub;
+            uint4 x = make_uint4(0u, 0u, 0u, 0u);
+            uint32_t h = 0;
+            if (g < e0) {
+                x = *reinterpret_cast<const uint4 *>(list + base + g);
+                h = *reinterpret_cast<const uint32_t *>(list_hi + base + g);
+            }
+            bounds(k + kTeams);
+            while (g < e0) {
+                const uint32_t gn = g + 4u * kTeam;
+                uint4 y = make_uint4(0u, 0u, 0u, 0u);
+                uint32_t hn = 0;
+                if (gn < e0) {
+                    y = *reinterpret_cast<const uint4 *>(list + base + gn);
+                    hn = *reinterpret_cast<const uint32_t *>(list_hi + base + gn);
+                }
+                if (g >= s0)
+                    visit(x.x, h & 0xFFu, k - k0);
+                if (g + 1u >= s0 && g + 1u < e0)
+                    visit(x.y, (h >> 8) & 0xFFu, k - k0);
+                if (g + 2u >= s0 && g + 2u < e0)
+                    visit(x.z, (h >> 16) & 0xFFu, k - k0);
+                if (g + 3u >= s0 && g + 3u < e0)
+                    visit(x.w, h >> 24, k - k0);
+                x = y;
+                h = hn;
+                g = gn;
+            }
+        }
+    };
+    auto sub_of = [](uint32_t w, uint32_t h) -> uint32_t {
+        return (w >> kSubShift) | (h << (32 - kSubShift));
+    };
+    uint32_t sum = 0;
+    each([&](uint32_t w, uint32_t h, uint32_t) { atomicAdd(&s_cursor[sub_of(w, h)], 1u); }, sum);
+    if (sum)
+        atomicAdd(&s_sum, sum);
+    __syncthreads();
+    const uint32_t base = k0 * B.cap + s_sum;  // list places are below 2^32
+    // counts -> starts: each wavefront a share of the regions
+    const uint32_t share = (n_sub + kMergeWG - 1) / kMergeWG * 64u;
+    uint32_t run = 0;
+    for (uint32_t u = 0; u < share; u += 64) {
+        const uint32_t i = wave * share + u + lane;
+        const uint32_t c = i < n_sub ? s_cursor[i] : 0u;
+        const uint32_t incl = wave_inclusive(c);
+        if (i < n_sub)
+            s_cursor[i] = run + incl - c;
+        run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    }
+    if (lane == 0)
+        s_wave[wave] = run;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kMergeWG / 64; w++) {
+        before += w < wave ? s_wave[w] : 0u;
+        total += s_wave[w];
+    }
+    uint32_t *__restrict__ row = starts + (uint64_t)sb * (n_regions + 1u);
+    const uint32_t r0 = b << B.sub_log;
+    for (uint32_t u = 0; u < share; u += 64) {
+        const uint32_t i = wave * share + u + lane;
+        if (i < n_sub) {
+            const uint32_t c = s_cursor[i] + before;
+            s_cursor[i] = c;
+            if (r0 + i < n_regions)
+                row[r0 + i] = base + c;
+        }
+    }
+    if (threadIdx.x == 0 && b + 1u == B.n_bins)
+        row[n_regions] = base + total;
+    __syncthreads();
+    const bool staged = total <= kMergeTile;  // uniform
+    uint32_t *__restrict__ o = out + base;
+    uint8_t *__restrict__ oh = out_hi + base;
+    each(
+        [&](uint32_t w, uint32_t h, uint32_t k) {
+            const uint32_t at = atomicAdd(&s_cursor[sub_of(w, h)], 1u);
+            const uint32_t t = (k << B.pos_log) | ((w >> kLocalBits) & ((1u << kBlockLog) - 1u));
+            const uint32_t word = (w & ((1u << kLocalBits) - 1u)) | (t << kLocalBits);
+            const uint8_t high = (uint8_t)(t >> (32 - kLocalBits));
+            if (staged) {
+                s_word[at] = word;
+                s_high[at] = high;
+            } else {
+                o[at] = word;
+                oh[at] = high;
+            }
+        },
+        sum);
+    if (!staged)
+        return;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < total; i += kMergeWG) {
+        o[i] = s_word[i];
+        oh[i] = s_high[i];
+    }
+}
+
 // The region pass over the blocks' runs.  kCounters: counters per region (as
 // k_region).  kCells: the cells each thread updates, held in registers (the
 // plan's region has kCells * kRegionWG cells), or 0 for regions of fewer cells than
@@ -240,11 +439,12 @@ k_turn_table(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, uint32
 //
 // The next region's cells and first bounds are requested before the current
 // region's stores, since a wavefront's loads and stores complete in order.
-template <int kCounters, int kCells, int kLanes>
+template <int kCounters, int kCells, int kLanes, bool kTwo>
 __global__ void __launch_bounds__(kRegionWG)
 k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
-              const uint32_t *__restrict__ list, const uint16_t *__restrict__ table,
-              uint8_t *__restrict__ flags, int classify, uint32_t tau, RecordSpace rec, Carry C) {
+              const uint32_t *__restrict__ list, const uint8_t *__restrict__ list_hi,
+              const void *__restrict__ table, uint8_t *__restrict__ flags,
+              int classify, uint32_t tau, RecordSpace rec, Carry C) {
     constexpr uint32_t kSparseCells = kCounters / 8;
     constexpr bool kTile = (uint32_t)kCells * kRegionWG <= kSparseCells;
     constexpr int kHold = kCells ? kCells : 1;
@@ -277,9 +477,10 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
     }
     const uint32_t grid = gridDim.x;
     const uint32_t lane = threadIdx.x & 63u, wave = wave_id();
-    auto count = [&](uint32_t e, uint32_t tb) {
+    // entry of word e and (kTwo) fifth byte h, its position counted from tb
+    auto count = [&](uint32_t e, uint32_t h, uint32_t tb) {
         const uint32_t local = e & ((1u << kLocalBits) - 1u);
-        const uint32_t t = tb + (e >> kLocalBits);
+        const uint32_t t = tb + ((e >> kLocalBits) | (h << (32 - kLocalBits)));
         atomicAdd(&hits[local], 1u);
         // most entries are not the first of their counter: a plain read (any
         // value read is at least the minimum so far) saves their atomic
@@ -295,14 +496,22 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
             cell[k] = (kCells && r < P.n_regions && wbase + w < n_words) ? F.words[wbase + w] : 0ull;
         }
     };
-    // bounds of the run of region r in block b
+    // bounds of the run of region r in block b (kTwo: in superblock b)
+    const uint32_t n_blocks = kTwo ? B.n_super : B.n_blocks;
     auto bounds = [&](uint32_t r, uint32_t b, uint32_t &s, uint32_t &e) {
         s = e = 0;
-        if (b < B.n_blocks && r < P.n_regions) {
-            const uint16_t *t = kLanes == 0 ? table + (uint64_t)r * B.turned + b
-                                            : table + (uint64_t)b * B.row + r;
-            s = t[0];
-            e = t[kLanes == 0 ? B.turned : 1u];
+        if (b < n_blocks && r < P.n_regions) {
+            if (kTwo) {
+                const uint32_t *t = (const uint32_t *)table + (uint64_t)b * (P.n_regions + 1u) + r;
+                s = t[0];
+                e = t[1];
+            } else {
+                const uint16_t *t = (const uint16_t *)table + (kLanes == 0
+                                                                   ? (uint64_t)r * B.turned + b
+                                                                   : (uint64_t)b * B.row + r);
+                s = t[0];
+                e = t[kLanes == 0 ? B.turned : 1u];
+            }
         }
     };
     constexpr int kTeam = kLanes ? kLanes : 64;
@@ -375,46 +584,58 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
 #pragma unroll
                     for (int c = 0; c < kChunks; c++)
                         if (w0 + 64u * c + lane < n)
-                            count(x[c], tb[c]);
+                            count(x[c], 0u, tb[c]);
                     __builtin_amdgcn_wave_barrier();
                 }
             }
         } else {
-            for (uint32_t b0 = team; b0 < B.n_blocks; b0 += kUnroll * kTeams) {
+            for (uint32_t b0 = team; b0 < n_blocks; b0 += kUnroll * kTeams) {
                 // a first 16-byte group of entries of every run, and the next
                 // runs' bounds, are requested before any entry is counted
-                uint32_t s[kUnroll], e[kUnroll], g[kUnroll];
+                uint32_t s[kUnroll], e[kUnroll], g[kUnroll], h[kUnroll];
                 uint4 x[kUnroll];
 #pragma unroll
                 for (int u = 0; u < kUnroll; u++) {
+                    const uint32_t b = b0 + (uint32_t)u * kTeams;
                     s[u] = ns[u];
                     e[u] = ne[u];
                     g[u] = (s[u] & ~3u) + 4u * sub;
-                    if (g[u] < e[u])
-                        x[u] = *reinterpret_cast<const uint4 *>(
-                            list + (uint64_t)(b0 + (uint32_t)u * kTeams) * B.cap + g[u]);
+                    if (g[u] < e[u]) {
+                        const uint64_t at = (kTwo ? 0ull : (uint64_t)b * B.cap) + g[u];
+                        x[u] = *reinterpret_cast<const uint4 *>(list + at);
+                        if (kTwo)
+                            h[u] = *reinterpret_cast<const uint32_t *>(list_hi + at);
+                    }
                     mine += sub == 0 ? e[u] - s[u] : 0u;
                     bounds(r, b0 + (uint32_t)(u + kUnroll) * kTeams, ns[u], ne[u]);
                 }
 #pragma unroll
                 for (int u = 0; u < kUnroll; u++) {
                     const uint32_t b = b0 + (uint32_t)u * kTeams;
-                    const uint32_t tb = b << B.pos_log;
-                    const uint32_t *blk = list + (uint64_t)b * B.cap;
+                    const uint32_t tb = kTwo ? (b * B.super) << B.pos_log : b << B.pos_log;
+                    const uint64_t at0 = kTwo ? 0ull : (uint64_t)b * B.cap;
                     while (g[u] < e[u]) {
                         const uint32_t gn = g[u] + 4u * kTeam;
                         uint4 y = make_uint4(0u, 0u, 0u, 0u);
-                        if (gn < e[u])
-                            y = *reinterpret_cast<const uint4 *>(blk + gn);
+                        uint32_t hn = 0;
+                        if (gn < e[u] && gn > g[u]) {
+                            y = *reinterpret_cast<const uint4 *>(list + at0 + gn);
+                            if (kTwo)
+                                hn = *reinterpret_cast<const uint32_t *>(list_hi + at0 + gn);
+                        }
+                        const uint32_t hu = kTwo ? h[u] : 0u;
                         if (g[u] >= s[u])
-                            count(x[u].x, tb);
+                            count(x[u].x, hu & 0xFFu, tb);
                         if (g[u] + 1u >= s[u] && g[u] + 1u < e[u])
-                            count(x[u].y, tb);
+                            count(x[u].y, (hu >> 8) & 0xFFu, tb);
                         if (g[u] + 2u >= s[u] && g[u] + 2u < e[u])
-                            count(x[u].z, tb);
+                            count(x[u].z, (hu >> 16) & 0xFFu, tb);
                         if (g[u] + 3u >= s[u] && g[u] + 3u < e[u])
-                            count(x[u].w, tb);
+                            count(x[u].w, hu >> 24, tb);
                         x[u] = y;
+                        h[u] = hn;
+                        if (gn < g[u])
+                            break;  // past the last 32-bit place
                         g[u] = gn;
                     }
                 }
@@ -489,21 +710,28 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
 namespace {
 
 using SortKernel = void (*)(FilterArgs, ReadsArgs, uint64_t, uint64_t, BlockPlan, uint32_t,
-                            uint32_t, uint32_t *, uint16_t *, unsigned long long *);
+                            uint32_t *, uint8_t *, uint16_t *, unsigned long long *);
 using RunsKernel = void (*)(FilterArgs, uint64_t, BinPlan, BlockPlan, const uint32_t *,
-                            const uint16_t *, uint8_t *, int, uint32_t, RecordSpace, Carry);
+                            const uint8_t *, const void *, uint8_t *, int, uint32_t, RecordSpace,
+                            Carry);
 
-template <int kKh, bool kFast, bool kWide>
+template <int kKh, bool kFast, bool kWide, bool kTwo>
 SortKernel sort_kernel_of(const BlockPlan &B) {
     if (B.wg == 1024)
-        return k_hash_sort<1024, 32, kKh, kFast, kWide>;
-    return B.ept == 32 ? k_hash_sort<512, 32, kKh, kFast, kWide>
-                       : k_hash_sort<512, 8, kKh, kFast, kWide>;
+        return k_hash_sort<1024, 32, kKh, kFast, kWide, kTwo>;
+    if constexpr (!kTwo)
+        if (B.ept == 32)
+            return k_hash_sort<512, 32, kKh, kFast, kWide, false>;
+    return k_hash_sort<512, 8, kKh, kFast, kWide, kTwo>;
 }
 
 template <int kKh, bool kFast>
 SortKernel sort_kernel_for(const BlockPlan &B, uint32_t k) {
-    return k > 32 ? sort_kernel_of<kKh, kFast, true>(B) : sort_kernel_of<kKh, kFast, false>(B);
+    if (B.two)
+        return k > 32 ? sort_kernel_of<kKh, kFast, true, true>(B)
+                      : sort_kernel_of<kKh, kFast, false, true>(B);
+    return k > 32 ? sort_kernel_of<kKh, kFast, true, false>(B)
+                  : sort_kernel_of<kKh, kFast, false, false>(B);
 }
 
 SortKernel sort_kernel(const FilterArgs &F, uint32_t k, const BlockPlan &B) {
@@ -520,43 +748,47 @@ SortKernel sort_kernel(const FilterArgs &F, uint32_t k, const BlockPlan &B) {
 }
 
 template <int kCounters, int kCells>
-RunsKernel runs_kernel_of(const BinPlan &P, const BlockPlan &B) {
+RunsKernel runs_kernel_of(const BlockPlan &B) {
+    if (B.two)
+        return B.lanes == 4 ? k_region_runs<kCounters, kCells, 4, true>
+                            : k_region_runs<kCounters, kCells, 16, true>;
     if (B.turned)
-        return k_region_runs<kCounters, kCells, 0>;
-    return B.cap / P.n_regions <= 64 ? k_region_runs<kCounters, kCells, 4>
-                                     : k_region_runs<kCounters, kCells, 16>;
+        return k_region_runs<kCounters, kCells, 0, false>;
+    return B.lanes == 4 ? k_region_runs<kCounters, kCells, 4, false>
+                        : k_region_runs<kCounters, kCells, 16, false>;
 }
 
 // The region pass's instance: counters per region, cells per thread, and
-// lanes per run by the run's expected length.
+// lanes per run.
 template <int kCounters>
 RunsKernel runs_kernel(const BinPlan &P, const BlockPlan &B) {
     switch ((1u << P.region_shift) / kRegionWG) {
     case 0:
-        return runs_kernel_of<kCounters, 0>(P, B);
+        return runs_kernel_of<kCounters, 0>(B);
     case 1:
-        return runs_kernel_of<kCounters, 1>(P, B);
+        return runs_kernel_of<kCounters, 1>(B);
     case 2:
-        return runs_kernel_of<kCounters, 2>(P, B);
+        return runs_kernel_of<kCounters, 2>(B);
     case 4:
-        return runs_kernel_of<kCounters, 4>(P, B);
+        return runs_kernel_of<kCounters, 4>(B);
     default:  // two counters a cell
-        return runs_kernel_of<kCounters, 8>(P, B);
+        return runs_kernel_of<kCounters, 8>(B);
     }
 }
 
 }  // namespace
 
 bool block_plan(const BinPlan &plan, uint32_t k_h, uint64_t len, BlockPlan &B) {
-    if (plan.n_parts || plan.n_regions > kBlockRegions || len == 0)
+    if (len == 0)
         return false;
     B = BlockPlan{};
     B.kh = 1;
     while (B.kh < k_h)
         B.kh *= 2;
+    B.two = plan.n_parts || plan.n_regions > kBlockRegions;
     // large blocks make long runs; chunks that would leave the chip idle take
     // small ones
-    B.wg = plan.n_regions > kHalfRegions ? 1024u : 512u;
+    B.wg = B.two || plan.n_regions > kHalfRegions ? 1024u : 512u;
     B.ept = 32;
     if (len * B.kh < 512ull * 32 * 512) {
         B.wg = 512;
@@ -564,13 +796,38 @@ bool block_plan(const BinPlan &plan, uint32_t k_h, uint64_t len, BlockPlan &B) {
     }
     while ((1u << B.pos_log) < B.ept * B.wg / B.kh)
         B.pos_log++;
-    // a multiple of 4 (blocks start at 16-byte boundaries), and no power of
-    // two: the same region's runs of consecutive blocks fall on different
-    // memory channels
-    B.cap = (k_h << B.pos_log) + kBlockPad;
+    B.cap = k_h << B.pos_log;  // a multiple of 16: blocks' lists start at 16-byte boundaries
     B.n_blocks = (uint32_t)((len + (1ull << B.pos_log) - 1) >> B.pos_log);
-    B.row = (plan.n_regions + 2u) & ~1u;
-    B.turned = B.cap / plan.n_regions <= kShortRun ? (B.n_blocks + 1u) & ~1u : 0u;
+    if (!B.two) {
+        // no power of two: the same region's runs of consecutive blocks fall
+        // on different memory channels
+        B.cap += kBlockPad;
+        B.n_bins = plan.n_regions;
+        B.row = (B.n_bins + 2u) & ~1u;
+        B.turned = B.cap / B.n_bins <= kShortRun ? (B.n_blocks + 1u) & ~1u : 0u;
+        B.lanes = B.cap / B.n_bins <= 64 ? 4u : 16u;
+        return true;
+    }
+    // about as many buckets as regions in a bucket, at most 512 buckets of at
+    // most 2^kMaxSubLog regions (then more buckets); small forced partitions
+    // (tests) make buckets of as many regions
+    while (((plan.n_regions - 1u) >> B.sub_log) >= 512u && B.sub_log < kMaxSubLog)
+        B.sub_log++;
+    if (plan.n_parts && plan.part_log < B.sub_log)
+        B.sub_log = plan.part_log;
+    B.n_bins = (plan.n_regions + (1u << B.sub_log) - 1u) >> B.sub_log;
+    if (B.n_bins > kMaxBins)
+        return false;
+    B.row = (B.n_bins + 2u) & ~1u;
+    // superblocks whose buckets about fill the second level's LDS when every
+    // window is valid
+    const uint32_t run = B.cap / B.n_bins + 1u;
+    uint32_t m = kMergeTile * 7u / 8u / run;
+    const uint32_t most = (1u << kSuperLog) >> B.pos_log;
+    m = m < 1u ? 1u : (m > most ? most : m);
+    B.super = m < B.n_blocks ? m : B.n_blocks;
+    B.n_super = (B.n_blocks + B.super - 1u) / B.super;
+    B.lanes = (uint64_t)run * B.super >> B.sub_log <= 32 ? 4u : 16u;
     return true;
 }
 
@@ -578,45 +835,76 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
                                const BinPlan &plan, const BlockPlan &B, const Workspace &W,
                                bool classify, uint32_t tau, const Carry &carry, bool records,
                                hipStream_t s, Profiler *P) {
-    // the table: in the count matrix's room, or in the slot ids' where that is
-    // larger (their rooms are sized for more than this path needs)
-    const uint64_t n_table = (uint64_t)B.n_blocks * B.row;
-    uint16_t *table = (uint16_t *)W.matrix;
-    if (n_table > 2 * W.matrix_cap) {
-        table = (uint16_t *)W.slots;
-        if (n_table > 2 * W.slots_cap)
-            return hipErrorInvalidValue;
-    }
-    // the list: about 4 of the 8 bytes per entry of W.entries; the turned
-    // table: in the second count matrix's room, or behind the list
+    // Rooms of the workspace (sized by the plan's count matrices and 8-byte
+    // entries, more than these lists need).  One-level form: the list in
+    // entries, the table in the count matrix's room or the slot ids', the
+    // turned table in the second matrix's or behind the list.  Two-level form:
+    // the blocks' list and table in bucketed, the superblocks' list and starts
+    // in entries (small calls: the table and starts in the matrices' rooms).
+    // Records take bucketed, which either form has read by then.
     const uint64_t last = c1 - c0 - ((uint64_t)(B.n_blocks - 1) << B.pos_log);
-    const uint64_t n_list = ((uint64_t)(B.n_blocks - 1) * B.cap + last * F.k_h + 3) / 4 * 4;
-    if (n_list > (W.entries_cap + 1) / 2 * 4 || n_list >= (1ull << 32))
+    const uint64_t n_list = ((uint64_t)(B.n_blocks - 1) * B.cap + last * F.k_h + 15) / 16 * 16;
+    const uint64_t room = 8 * W.entries_cap;  // bytes of entries, and of bucketed
+    const uint64_t table_bytes = 2ull * B.n_blocks * B.row;
+    const uint64_t turned_bytes = 2ull * B.turned * B.row;
+    const uint64_t starts_bytes = 4ull * B.n_super * (plan.n_regions + 1u);
+    if (n_list > (1ull << 32))
         return hipErrorInvalidValue;
-    uint32_t *list = (uint32_t *)W.entries;
-    const uint64_t n_turned = (uint64_t)B.turned * B.row;
-    uint16_t *turned = (uint16_t *)W.matrix_t;
-    if (n_turned > 2 * W.matrix_cap) {
-        turned = (uint16_t *)(list + n_list);
-        if (4 * n_list + 2 * n_turned > 8 * W.entries_cap)
+    uint32_t *list = (uint32_t *)(B.two ? W.bucketed : W.entries), *merged = (uint32_t *)W.entries;
+    uint8_t *list_hi = nullptr, *merged_hi = nullptr;
+    uint16_t *table = (uint16_t *)W.matrix, *turned = (uint16_t *)W.matrix_t;
+    uint32_t *starts = W.matrix;
+    if (B.two) {
+        if (5 * n_list > (room + 255) / 256 * 256)
             return hipErrorInvalidValue;
+        list_hi = (uint8_t *)(list + n_list);
+        merged_hi = (uint8_t *)(merged + n_list);
+        table = (uint16_t *)(W.matrix_t + 2ull * plan.n_regions);
+        if (5 * n_list + table_bytes <= room)
+            table = (uint16_t *)(list_hi + n_list);
+        else if (8ull * plan.n_regions + table_bytes > 4 * W.matrix_cap)
+            return hipErrorInvalidValue;
+        if (5 * n_list + starts_bytes <= room)
+            starts = (uint32_t *)(merged_hi + n_list);
+        else if (starts_bytes > 4 * W.matrix_cap)
+            return hipErrorInvalidValue;
+    } else {
+        if (4 * n_list > (room + 255) / 256 * 256)
+            return hipErrorInvalidValue;
+        if (table_bytes > 4 * W.matrix_cap) {
+            table = (uint16_t *)W.slots;
+            if (table_bytes > 4 * W.slots_cap)
+                return hipErrorInvalidValue;
+        }
+        if (turned_bytes > 4 * W.matrix_cap) {
+            turned = (uint16_t *)(list + n_list);
+            if (4 * n_list + turned_bytes > room)
+                return hipErrorInvalidValue;
+        }
     }
-    const size_t lds = (size_t)plan.n_regions * sizeof(uint32_t);
+    // partitioned plans (more than kMaxRegions regions) name their phases so
     if (P)
-        P->begin(kPhBinCount, s);
-    hipLaunchKernelGGL(sort_kernel(F, R.k, B), dim3(B.n_blocks), dim3(B.wg), lds, s, F, R, c0,
-                       c1, B, plan.region_shift, plan.n_regions, list, table,
-                       (unsigned long long *)(W.totals + 5));
+        P->begin(plan.n_parts ? kPhBinPart : kPhBinCount, s);
+    hipLaunchKernelGGL(sort_kernel(F, R.k, B), dim3(B.n_blocks), dim3(B.wg),
+                       B.n_bins * sizeof(uint32_t), s, F, R, c0, c1, B, plan.region_shift, list,
+                       list_hi, table, (unsigned long long *)(W.totals + 5));
     if (P)
         P->end(s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    if (B.turned) {
+    if (B.two || B.turned) {
         if (P)
-            P->begin(kPhBinRegion, s);
-        hipLaunchKernelGGL(k_turn_table, dim3((B.row + 63) / 64, (B.n_blocks + 63) / 64), dim3(256),
-                           0, s, (const uint16_t *)table, turned, B.n_blocks, B.row, B.turned);
+            P->begin(plan.n_parts ? kPhPartCount : kPhBinRegion, s);
+        if (B.two)
+            hipLaunchKernelGGL(k_merge, dim3((B.n_bins + 7) / 8 * 8 * B.n_super), dim3(kMergeWG),
+                               0, s, B, plan.n_regions, (const uint32_t *)list,
+                               (const uint8_t *)list_hi, (const uint16_t *)table, merged,
+                               merged_hi, starts);
+        else
+            hipLaunchKernelGGL(k_turn_table, dim3((B.row + 63) / 64, (B.n_blocks + 63) / 64),
+                               dim3(256), 0, s, (const uint16_t *)table, turned, B.n_blocks, B.row,
+                               B.turned);
         if (P)
             P->end(s);
         if ((e = hipGetLastError()) != hipSuccess)
@@ -628,23 +916,26 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
         if ((e = fill_u32(rec.cursor, 1, 0u, s)) != hipSuccess)
             return e;
         if (records) {
-            if (2ull * plan.n_regions > W.coarse_cap)
+            uint32_t *index = B.two ? W.matrix_t : W.coarse;
+            if (2ull * plan.n_regions > (B.two ? W.matrix_cap : W.coarse_cap))
                 return hipErrorInvalidValue;
             rec.word = (uint32_t *)W.bucketed;
             rec.half = (uint16_t *)(rec.word + W.entries_cap);
-            rec.off = W.coarse;
-            rec.n = W.coarse + plan.n_regions;
+            rec.off = index;
+            rec.n = index + plan.n_regions;
         }
     }
+    const void *runs = B.two ? (const void *)starts
+                             : (const void *)(B.turned ? turned : table);
     if (P)
         P->begin(kPhRegion, s);
     hipLaunchKernelGGL(plan.region_counters == (uint32_t)kSmallRegionCounters
                            ? runs_kernel<kSmallRegionCounters>(plan, B)
                            : runs_kernel<kRegionCounters>(plan, B),
                        dim3(region_grid(plan.n_regions, plan.region_counters)), dim3(kRegionWG), 0,
-                       s, F, c0, plan, B, (const uint32_t *)list,
-                       (const uint16_t *)(B.turned ? turned : table), W.flags8,
-                       classify ? 1 : 0, tau, rec, carry);
+                       s, F, c0, plan, B, (const uint32_t *)(B.two ? merged : list),
+                       (const uint8_t *)merged_hi, runs, W.flags8, classify ? 1 : 0, tau, rec,
+                       carry);
     if (P)
         P->end(s);
     e = hipGetLastError();

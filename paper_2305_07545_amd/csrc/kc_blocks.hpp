@@ -19,21 +19,35 @@ constexpr uint32_t kBlockPad = 80;  // entries of a block's stride beyond its ro
 // Runs of up to this many entries (a block's room / regions) are short: the
 // region pass takes 64 blocks' runs at a time.
 constexpr uint32_t kShortRun = 16;
+// Two-level form
+constexpr uint32_t kMaxSubLog = 11;   // log2(regions per bucket), at most
+constexpr uint32_t kMaxBins = 2048;   // buckets, at most (4M regions)
+constexpr uint32_t kSuperLog = 26;    // log2(positions per superblock), at most
+constexpr int kMergeWG = 512;         // threads of the second level
+constexpr uint32_t kMergeTile = 12288;  // entries it stages in LDS (two workgroups per CU)
 
 // Blocks of one chunk: block b holds the entries of positions [b << pos_log,
-// (b + 1) << pos_log) of the chunk (every hash function's), sorted by region.
+// (b + 1) << pos_log) of the chunk (every hash function's), sorted by bin: a
+// region (one-level form) or a bucket of 2^sub_log regions, which the second
+// level sorts by region, `super` blocks at a time.
 struct BlockPlan {
     uint32_t pos_log;   // log2(positions per block)
-    uint32_t cap;       // entries a block has room for (its stride in the list)
+    uint32_t cap;       // a block's stride in the list (entries)
     uint32_t n_blocks;
-    uint32_t row;       // 16-bit offsets per block in the table (regions + 1, even)
+    uint32_t n_bins;
+    uint32_t row;       // 16-bit offsets per block in the table (bins + 1, even)
     uint32_t kh;        // hash functions, rounded up to a power of two
     uint32_t ept;       // entries per thread of the hashing kernel
     uint32_t wg;        // threads of the hashing kernel
     uint32_t turned;    // short runs: 16-bit offsets per region of the turned table, else 0
+    uint32_t lanes;     // lanes of the region pass per run
+    uint32_t two;       // two-level form
+    uint32_t sub_log;
+    uint32_t super;
+    uint32_t n_super;   // superblocks
 };
 
-// Whether the one-level form takes a plan, and its blocks for `len` positions.
+// The blocks of `len` positions (false: none, or more buckets than kMaxBins).
 bool block_plan(const BinPlan &plan, uint32_t k_h, uint64_t len, BlockPlan &B);
 
 // hash + sort + region pass of chunk [c0, c1).
