@@ -493,10 +493,8 @@ kc_status insert_core(kc_filter *f, const kc::Workspace &W, uint64_t n_bases, ui
                       uint64_t cap_te, hipStream_t s, kc::Profiler *P) {
     const bool split = trust != nullptr;
     hipError_t e = hipSuccess;
-    if (binned)
-        e = kc::launch_valid_windows(n_bases, k, W, s, P);
-    if (e == hipSuccess && binned)  // valid windows, accumulated by the bin passes
-        e = kc::fill_u64(W.totals + 5, 1, 0ull, s);
+    // either also clears the call's counters
+    e = binned ? kc::launch_valid_windows(n_bases, k, W, s, P) : kc::launch_clear_call(n_bases, W, s);
     if (e != hipSuccess)
         return KC_EDEVICE;
     kc::ReadsArgs R{W.codes, W.inv, W.rs, n_bases, k, W.valid};
@@ -535,7 +533,7 @@ kc_status insert_core(kc_filter *f, const kc::Workspace &W, uint64_t n_bases, ui
         f->zero = false;
     }
     for (uint32_t c = 0; c < carry.n_prev; c++)
-        if (kc::launch_carried_winners(plan, carry, c, (uint64_t)c * chunk, chunk, W, s, P) !=
+        if (kc::launch_carried_winners(plan, carry, c, (uint64_t)c * chunk, chunk, n_bases, W, s, P) !=
             hipSuccess)
             return KC_EDEVICE;
     if (split && !carry.n_prev) {
@@ -582,7 +580,7 @@ kc_status insert_impl(kc_filter *f, const uint8_t *reads, const uint64_t *offset
         return st;
     }
     f->k = k;  // every check passed: the filter now holds k-mers of this length
-    if (kc::launch_ingest(reads, n_bases, offsets, n_reads, *f->W, s, &f->prof) != hipSuccess)
+    if (kc::launch_ingest(reads, n_bases, offsets, n_reads, *f->W, false, s, &f->prof) != hipSuccess)
         return KC_EDEVICE;
     return insert_core(f, *f->W, n_bases, k, binned, plan, bchunk, distinct, cap_d, n_distinct,
                        n_windows, tau, trust, n_trust, err, n_err, cap_te, s, &f->prof);

@@ -565,7 +565,7 @@ hipError_t launch_batch(const BatchPlan &bp, const BatchBuffers &Bf, const Reads
     const dim3 grid((unsigned)(bp.n_tiles < (uint64_t)kTileGrid ? bp.n_tiles : kTileGrid));
     if (P)
         P->begin(kPhTileCount, s);
-    e = launch_tile_count(R, W, bp.n_tiles, s);
+    e = launch_tile_count(W, bp.n_tiles, s);
     if (P)
         P->end(s);
     if (P)

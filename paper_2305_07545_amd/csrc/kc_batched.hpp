@@ -65,8 +65,7 @@ struct BatchBuffers {
     Workspace *W = nullptr;           // per-position and per-tile buffers
 };
 
-hipError_t launch_tile_count(const ReadsArgs &R, const Workspace &W, uint64_t n_tiles,
-                             hipStream_t s);
+hipError_t launch_tile_count(const Workspace &W, uint64_t n_tiles, hipStream_t s);
 hipError_t launch_batch_bins(const BatchPlan &bp, const BatchBuffers &Bf, const ReadsArgs &R,
                              hipStream_t s, Profiler *P);
 hipError_t launch_batch(const BatchPlan &bp, const BatchBuffers &Bf, const ReadsArgs &R,

@@ -44,10 +44,10 @@ uint32_t region_grid(uint32_t n_regions, uint32_t counters) {
 
 // ---------------------------------------------------------------------------
 // winner passes (records mode): the region pass's first-seen records, grouped
-// by region, become flag bytes written in whole 16-byte groups.  Records are
+// by region, become distinct and trustworthy bits.  Records are
 // distributed by position in two counting-sort passes (by t >> 24, then by
-// the next 5 bits) into blocks of 2^19 positions, whose flags are built in
-// LDS bitmaps.  Runs are appended to each bucket at an atomic cursor (the
+// the next 5 bits) into blocks of 2^19 positions, whose bits are built in
+// LDS.  Runs are appended to each bucket at an atomic cursor (the
 // order of records inside a bucket does not matter: a bitmap is built from
 // them), in areas of the two entry buffers sized by the positions they
 // cover, so that they always fit.
@@ -228,64 +228,91 @@ __global__ void __launch_bounds__(kWinThreads) k_win_b(const uint32_t *__restric
     }
 }
 
-// The flag bytes of block g = blockIdx.x (positions [g << 19, ...) of the
-// chunk, flags at c0 + those) from its records: distinct and trustworthy
-// bitmaps in LDS, then every 16-position group with a mark written whole
-// (the others keep the zeros the ingest wrote).
-__global__ void __launch_bounds__(kWinThreads) k_win_flags(const uint32_t *__restrict__ in,
-                                                           const uint32_t *__restrict__ cursor_b,
-                                                           uint64_t c0, uint64_t len,
-                                                           uint8_t *__restrict__ flags) {
-    constexpr uint32_t kWords = (1u << kWinB) / 32;
-    __shared__ uint32_t s_d[kWords];
-    __shared__ uint32_t s_t[kWords];
+// The distinct and trustworthy bits of bucket g = blockIdx.x, the 2^log
+// positions from g << log of the chunk, and their tiles' counts, from the
+// bucket's cursor[g] records (position | mark << log, `room` apart): bitmaps
+// in LDS, every word of the bucket's tiles written.  clean: the cursor is left
+// zero for the next chunk.  c0 is a multiple of the tile.
+// Bound by its clears and LDS atomics at one or two workgroups per CU: 0.07 ms
+// over 280 M positions; the byte flags cost 0.20 ms to store at random and
+// 0.17 ms to read again in the compaction (0.07 from bits).
+// kLog: the bitmaps' room; the smaller ones leave room for several workgroups
+// per CU where a chunk's buckets are small.
+template <uint32_t kLog>  // log <= kLog
+__global__ void __launch_bounds__(kLog >= 17 ? 1024 : 256)
+k_marks(const uint32_t *__restrict__ in, uint64_t room, uint32_t log, uint32_t *__restrict__ cursor,
+        int clean, uint64_t c0, uint64_t len, uint32_t *__restrict__ dbits,
+        uint32_t *__restrict__ tbits, uint32_t *__restrict__ tile_d,
+        uint32_t *__restrict__ tile_t) {
+    __shared__ uint32_t s_bits[2u << (kLog - 5)];  // the distinct words, then the trustworthy ones
+    const uint32_t words = 1u << (log - 5);
+    uint32_t *s_d = s_bits, *s_t = s_bits + words;
     const uint32_t g = blockIdx.x;
-    for (uint32_t i = threadIdx.x; i < kWords; i += kWinThreads) {
-        s_d[i] = 0;
-        s_t[i] = 0;
-    }
+    for (uint32_t i = threadIdx.x; i < 2 * words; i += blockDim.x)
+        s_bits[i] = 0;
+    const uint32_t n = cursor[g];
     __syncthreads();
-    const uint32_t n = cursor_b[g];
-    const uint32_t *src = in + ((uint64_t)g << kWinB);
-    for (uint32_t i = threadIdx.x; i < n; i += kWinThreads) {
-        const uint32_t v = src[i];
-        const uint32_t p = v & ((1u << kWinB) - 1u);
-        atomicOr(&s_d[p >> 5], 1u << (p & 31u));
-        if ((v >> kWinB) & 2u)
-            atomicOr(&s_t[p >> 5], 1u << (p & 31u));
-    }
-    __syncthreads();
-    const uint64_t p0 = (uint64_t)g << kWinB;
-    uint4 *f128 = reinterpret_cast<uint4 *>(flags + c0 + p0);
-    const uint32_t groups = (uint32_t)((len - p0 < (1u << kWinB) ? len - p0 : (1u << kWinB)) + 15) / 16;
-    for (uint32_t q = threadIdx.x; q < groups; q += kWinThreads) {
-        const uint32_t d16 = (s_d[q >> 1] >> ((q & 1u) * 16)) & 0xFFFFu;
-        if (!d16)
-            continue;
-        const uint32_t t16 = (s_t[q >> 1] >> ((q & 1u) * 16)) & 0xFFFFu;
-        uint32_t w[4];
+    if (clean && threadIdx.x == 0)
+        cursor[g] = 0;
+    const uint32_t *src = in + (uint64_t)g * room;
+    constexpr int kUnroll = 4;
+    for (uint32_t i = threadIdx.x; i < n; i += kUnroll * blockDim.x) {
+        uint32_t v[kUnroll];
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-            uint32_t x = 0;
+        for (int u = 0; u < kUnroll; u++)
+            v[u] = i + u * blockDim.x < n ? src[i + u * blockDim.x] : 0u;  // no record has mark 0
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const uint32_t b = 4 * u + j;
-                x |= (((d16 >> b) & 1u) | (((t16 >> b) & 1u) << 1)) << (8 * j);
-            }
-            w[u] = x;
+        for (int u = 0; u < kUnroll; u++) {
+            const uint32_t mark = v[u] >> log, p = v[u] & ((1u << log) - 1u);
+            if (mark)
+                atomicOr(&s_d[p >> 5], 1u << (p & 31u));
+            if (mark & 2u)
+                atomicOr(&s_t[p >> 5], 1u << (p & 31u));
         }
-        f128[q] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+    __syncthreads();
+    const uint64_t p0 = (uint64_t)g << log;
+    const uint64_t left = (len - p0 + kTile - 1) / kTile * (kTile / 32);  // words to the chunk's end
+    const uint32_t nw = left < words ? (uint32_t)left : words;
+    const uint64_t w0 = (c0 + p0) / 32;
+    for (uint32_t i = threadIdx.x; i < nw; i += blockDim.x) {
+        const uint32_t d = s_d[i], t = s_t[i];
+        dbits[w0 + i] = d;
+        tbits[w0 + i] = t;
+        // a tile is 32 words: half a wavefront's
+        uint32_t nd = (uint32_t)__popc(d), nt = (uint32_t)__popc(t);
+        for (uint32_t k = 16; k >= 1; k >>= 1) {
+            nd += __shfl_xor(nd, k, 32);
+            nt += __shfl_xor(nt, k, 32);
+        }
+        if ((i & 31u) == 0) {
+            tile_d[(w0 + i) / 32] = nd;
+            tile_t[(w0 + i) / 32] = nt;
+        }
     }
 }
 
-// Records mode when a chunk's flag bytes are larger than the Infinity
-// Cache (256 MB): random single-byte flag stores into HBM-resident flags
-// cost the 8 Gbase insert's region pass about 20 ms; KMERCO_WINNER_RECORDS=1
-// forces records mode for every chunk (tests), 0 turns it off.
+// The marks of a chunk's n_buckets buckets.
+hipError_t launch_marks(const uint32_t *in, uint64_t room, uint32_t log, uint32_t *cursor,
+                        bool clean, uint64_t c0, uint64_t len, uint64_t n_bases,
+                        const Workspace &W, hipStream_t s) {
+    const uint32_t n = (uint32_t)((len + (1ull << log) - 1) >> log);
+    const auto kernel = log <= 13 ? k_marks<13> : log <= 15 ? k_marks<15> : log <= 17 ? k_marks<17>
+                                                                                     : k_marks<19>;
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(log > 15 ? 1024 : 256), 0, s, in, room, log, cursor,
+                       clean ? 1 : 0, c0, len, distinct_bits(W), trust_bits(W, n_bases), W.tile_a,
+                       W.tile_b);
+    return hipGetLastError();
+}
+
+// Records mode, in which the winner passes distribute the regions' records:
+// for chunks of more than 2^28 positions, whose records the region pass cannot
+// sort by bucket itself (512 buckets of 2^19 positions);
+// KMERCO_WINNER_RECORDS=1 forces it for every chunk (tests).
 bool records_mode(uint64_t len) {
     const char *e = std::getenv("KMERCO_WINNER_RECORDS");
-    if (e && *e)
-        return std::atoi(e) != 0;
+    if (e && *e && std::atoi(e) != 0)
+        return true;
     return len > (1ull << 28);
 }
 
@@ -294,11 +321,10 @@ bool records_mode(uint64_t len) {
 // area_a, area_b: the entry buffers, the records' own not the first.
 hipError_t winner_passes(uint32_t n_regions, const uint32_t *offsets, uint64_t off_stride,
                          const uint32_t *n_win, const uint32_t *rec_word,
-                         const uint16_t *rec_half, uint64_t c0, uint64_t len, uint32_t *area_a,
-                         uint32_t *area_b, const Workspace &W, hipStream_t s, Profiler *P) {
+                         const uint16_t *rec_half, uint64_t c0, uint64_t len, uint64_t n_bases,
+                         uint32_t *area_a, uint32_t *area_b, const Workspace &W, hipStream_t s, Profiler *P) {
     uint32_t *cursors = W.win_cursors;  // kWinBuckets level-A, then the blocks' level-B cursors
     const uint32_t n_a = (uint32_t)((len + (1ull << kWinA) - 1) >> kWinA);
-    const uint32_t n_blocks = (uint32_t)((len + (1ull << kWinB) - 1) >> kWinB);
     if (P)
         P->begin(kPhWinners, s);
     static_assert(kWinBuckets + kWinBuckets * kWinBlocksPerBucket == kWinCursors, "cursors");
@@ -316,10 +342,8 @@ hipError_t winner_passes(uint32_t n_regions, const uint32_t *offsets, uint64_t o
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_win_flags, dim3(n_blocks), dim3(kWinThreads), 0, s,
-                           (const uint32_t *)area_b, (const uint32_t *)(cursors + kWinBuckets),
-                           c0, len, W.flags8);
-        e = hipGetLastError();
+        e = launch_marks(area_b, 1ull << kWinB, kWinB, cursors + kWinBuckets, false, c0, len,
+                         n_bases, W, s);
     }
     if (P)
         P->end(s);
@@ -328,8 +352,9 @@ hipError_t winner_passes(uint32_t n_regions, const uint32_t *offsets, uint64_t o
 
 hipError_t launch_record_winners(uint32_t n_regions, const uint32_t *off, const uint32_t *n,
                                  const uint32_t *word, const uint16_t *half, uint64_t c0,
-                                 uint64_t len, const Workspace &W, hipStream_t s, Profiler *P) {
-    return winner_passes(n_regions, off, 1, n, word, half, c0, len, (uint32_t *)W.entries,
+                                 uint64_t len, uint64_t n_bases, const Workspace &W, hipStream_t s,
+                                 Profiler *P) {
+    return winner_passes(n_regions, off, 1, n, word, half, c0, len, n_bases, (uint32_t *)W.entries,
                          (uint32_t *)W.bucketed, W, s, P);
 }
 
@@ -359,11 +384,12 @@ Carry carry_of(const Workspace &W, const BinPlan &plan, uint64_t chunk_positions
 }
 
 hipError_t launch_carried_winners(const BinPlan &plan, const Carry &carry, uint32_t j, uint64_t c0,
-                                  uint64_t len, const Workspace &W, hipStream_t s, Profiler *P) {
+                                  uint64_t len, uint64_t n_bases, const Workspace &W, hipStream_t s,
+                                  Profiler *P) {
     const uint64_t at = (uint64_t)j * carry.stride;
     return winner_passes(plan.n_regions, carry.off + at, 1, carry.n + at,
                          carry.word + (uint64_t)j * carry.cap, carry.half + (uint64_t)j * carry.cap,
-                         c0, len, (uint32_t *)W.bucketed, (uint32_t *)W.entries, W, s, P);
+                         c0, len, n_bases, (uint32_t *)W.bucketed, (uint32_t *)W.entries, W, s, P);
 }
 
 // ---------------------------------------------------------------------------

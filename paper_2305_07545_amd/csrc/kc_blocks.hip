@@ -423,31 +423,39 @@ k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
 // The region pass over the blocks' runs.  kCounters: counters per region (as
 // k_region).  kCells: the cells each thread updates, held in registers (the
 // plan's region has kCells * kRegionWG cells), or 0 for regions of fewer cells than
-// threads.  kLanes: lanes that take a run together (by its expected length),
-// or 0 for short runs: a wavefront takes the runs of 64 blocks at once (their
-// starts are a segment of the turned table's rows) and lays their entries end
-// to end over its lanes, so that every lane counts an entry at each step; the
-// lane's run is found by counting the run heads at and before it.
+// threads.  kTwo: runs of superblocks, 5-byte entries.  kLanes (one-level form):
+// lanes that take a run together (by its expected length), or 0 for short
+// runs: a wavefront takes the runs of 64 blocks at once (their starts are a
+// segment of the turned table's rows) and lays their entries end to end over
+// its lanes, so that every lane counts an entry at each step; the lane's run is
+// found by counting the run heads at and before it.
 //
 // Persistent.  The regions that the workgroups of one XCD (every eighth
 // workgroup) hold at a time are consecutive, so that the blocks' neighbouring
 // runs, which share cache lines, are read through one L2.
-// On the bacterial workload's 3914 regions, 0.51 ms: 0.20 of it stores flag
-// bytes at random positions, the rest is LDS atomics and laying out the runs
-// (6 entries each).  A plain read before the minimum's atomic took off 0.06,
-// blocks of 32768 entries instead of 16384 0.2.
 //
-// The next region's cells and first bounds are requested before the current
-// region's stores, since a wavefront's loads and stores complete in order.
-template <int kCounters, int kCells, int kLanes, bool kTwo>
+// kSorted: first-seen occurrences leave as records sorted by bucket of positions
+// (LDS counting sort, runs appended by one atomic per region and bucket), which
+// k_marks turns into bits.  Byte flags stored at random positions (94 G/s)
+// took 0.20 of the 0.51 ms this pass had on 280 M windows over 3914 regions;
+// it is 0.375 ms now, and the marks 0.09.  Else the records are in room of the
+// region's own (RecordSpace, carried chunks).
+//
+// Bound: latency, with one 128 KiB workgroup per CU (vector units 49% busy,
+// LDS 25%, on 1.7 G entries over 122 K regions: 6.1 ms).  So what the next
+// region needs is requested before the current region's counters are updated
+// (its cells, its first bounds; kTwo: its entries, 7.2 -> 6.1 ms), and taken in
+// before the update's first store.
+template <int kCounters, int kCells, int kLanes, bool kTwo, bool kSorted>
 __global__ void __launch_bounds__(kRegionWG)
 k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
               const uint32_t *__restrict__ list, const uint8_t *__restrict__ list_hi,
-              const void *__restrict__ table, uint8_t *__restrict__ flags,
-              int classify, uint32_t tau, RecordSpace rec, Carry C) {
+              const void *__restrict__ table, int classify, uint32_t tau, RecordSpace rec, Carry C) {
     constexpr uint32_t kSparseCells = kCounters / 8;
     constexpr bool kTile = (uint32_t)kCells * kRegionWG <= kSparseCells;
     constexpr int kHold = kCells ? kCells : 1;
+    constexpr int kWin = kCounters / kRegionWG;  // counters whose outcome a thread takes
+    constexpr int kEta = kWin / kHold;           // counters per held cell, at most
     constexpr int kChunks = 8;  // kLanes = 0: 64-entry steps in flight
     constexpr uint32_t kWindow = 64u * kChunks;
     constexpr int kWaves = kRegionWG / 64;
@@ -461,16 +469,20 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
     unsigned long long *s_cell = s_mem;
     auto s_run = reinterpret_cast<uint2(*)[64]>(s_mem);
     __shared__ uint32_t s_nwin, s_total, s_base;
+    // records sorted by bucket: counts, then starts; list place less start; wavefronts' sums
+    __shared__ uint32_t s_bucket[kMarkBuckets], s_place[kMarkBuckets], s_sum[kWaves];
     __shared__ uint32_t s_head[kLanes ? 1 : kWaves][2 * kChunks];
     const uint32_t shift = P.region_shift, S = 1u << shift;
     const uint64_t n_words = F.X * F.Y;
-    const bool carry_out = C.mode == Carry::kOut;
+    const bool carry_out = !kSorted && C.mode == Carry::kOut;
     const bool carry_in = kTile && C.mode == Carry::kIn && C.n_prev > 0;
-    const bool records = carry_out || rec.n != nullptr;
+    constexpr bool by_region = !kSorted;  // records in room of the region's own
     for (uint32_t i = threadIdx.x; i < (uint32_t)kCounters; i += kRegionWG) {
         hits[i] = 0;
         first[i] = kIdle;
     }
+    for (uint32_t i = threadIdx.x; i < kMarkBuckets; i += kRegionWG)
+        s_bucket[i] = 0;
     if (threadIdx.x == 0) {
         s_nwin = 0;
         s_total = 0;
@@ -496,47 +508,228 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
             cell[k] = (kCells && r < P.n_regions && wbase + w < n_words) ? F.words[wbase + w] : 0ull;
         }
     };
-    // bounds of the run of region r in block b (kTwo: in superblock b)
-    const uint32_t n_blocks = kTwo ? B.n_super : B.n_blocks;
-    auto bounds = [&](uint32_t r, uint32_t b, uint32_t &s, uint32_t &e) {
-        s = e = 0;
-        if (b < n_blocks && r < P.n_regions) {
-            if (kTwo) {
-                const uint32_t *t = (const uint32_t *)table + (uint64_t)b * (P.n_regions + 1u) + r;
-                s = t[0];
-                e = t[1];
-            } else {
-                const uint16_t *t = (const uint16_t *)table + (kLanes == 0
-                                                                   ? (uint64_t)r * B.turned + b
-                                                                   : (uint64_t)b * B.row + r);
-                s = t[0];
-                e = t[kLanes == 0 ? B.turned : 1u];
-            }
-        }
-    };
-    constexpr int kTeam = kLanes ? kLanes : 64;
-    constexpr uint32_t kTeams = kRegionWG / kTeam;
-    const uint32_t team = threadIdx.x / kTeam, sub = threadIdx.x % kTeam;
-    constexpr int kUnroll = kLanes ? 2 : 1;  // runs a team of lanes has in flight
-    // the first block whose bounds a thread takes, and its step
-    const uint32_t b_first = kLanes ? team : threadIdx.x;
-    constexpr uint32_t b_step = kLanes ? kTeams : kRegionWG;
     uint32_t r = (grid & 7u) == 0 ? (blockIdx.x & 7u) * (grid >> 3) + (blockIdx.x >> 3) : blockIdx.x;
     uint64_t cell[kHold];
-    uint32_t ns[kUnroll], ne[kUnroll];
     load_cells(r, cell);
-#pragma unroll
-    for (int u = 0; u < kUnroll; u++)
-        bounds(r, b_first + u * b_step, ns[u], ne[u]);
-    __syncthreads();  // counters clean, sums zero
-    for (; r < P.n_regions; r += grid) {
+    // The end of region r, whose entries are counted (mine: those of the runs
+    // whose length this lane has); the next region's cells are in `cell` then.
+    // prefetch: the caller's loads for the next region.  A wavefront's loads
+    // and stores complete in order, so that a load waited for after a store
+    // waits for that store: every load in flight (settle: the caller's) is
+    // taken in before the first store.
+    auto finish = [&](uint32_t r, uint32_t mine, auto prefetch, auto settle) {
         const uint64_t wbase = (uint64_t)r << shift;
         const uint32_t nw = wbase + S <= n_words ? S : (uint32_t)(n_words - wbase);
-        uint32_t mine = 0;  // entries of the runs whose length this lane has
-        if constexpr (kLanes == 0) {
+        if (by_region && mine)
+            atomicAdd(&s_total, mine);
+        __syncthreads();
+        uint64_t celln[kHold];
+        load_cells(r + grid, celln);
+        prefetch();
+        // room for a record of every entry of the region, asked for before the
+        // counters' update and taken after it
+        uint32_t got = 0;
+        if (by_region && threadIdx.x == 0 && s_total)
+            got = atomicAdd(rec.cursor, s_total);
+        // The counters' update, and the thread's first-seen occurrences: bit j
+        // of won, its position wt[j], bit j of sure when it is trustworthy.
+        // Counters are left clean (hits 0, first kIdle).
+        uint32_t wt[kWin], won = 0, sure = 0;
+        uint32_t changed = 0;  // cells to be written
+        // the thread's number as a value of this region: else the compiler
+        // keeps every counter's address in a register across all regions
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const uint32_t fm = (uint32_t)F.field_max;  // counters are at most 32 bits wide
+        if constexpr (kCells != 0) {
+#pragma unroll
+            for (int k = 0; k < kHold; k++) {
+                const uint32_t w = tid + (uint32_t)k * kRegionWG;
+                const uint64_t pre = cell[k];
+                uint64_t next = pre;
+#pragma unroll
+                for (int l = 0; l < kEta; l++)
+                    if ((uint32_t)l < F.eta) {
+                        const int j = k * kEta + l;
+                        const uint32_t idx = ((uint32_t)l << shift) | w;
+                        const uint32_t h = hits[idx];
+                        wt[j] = first[idx];
+                        hits[idx] = 0;
+                        first[idx] = kIdle;
+                        const uint32_t sh = F.alpha * l;
+                        const uint32_t pf = (uint32_t)(pre >> sh) & fm;
+                        const uint32_t room = fm - pf;
+                        const uint32_t inc = h < room ? h : room;
+                        next += (uint64_t)inc << sh;  // the field grows without carrying out
+                        won |= (h != 0 && pf == 0) ? 1u << j : 0u;
+                        sure |= inc > tau ? 1u << j : 0u;
+                        if (j % 4 == 3)  // four counters' reads in flight: the registers' limit
+                            __builtin_amdgcn_sched_barrier(0);
+                    }
+                changed |= next != pre ? 1u << k : 0u;
+                cell[k] = next;
+                if (kTile && C.mode == Carry::kIn)
+                    s_cell[w] = next;
+            }
+        } else {
+            // fewer cells than threads: a cell's owner leaves each counter's
+            // outcome in place, and every thread then takes its share
+            for (uint32_t w = tid; w < nw; w += kRegionWG) {
+                const uint64_t pre = F.words[wbase + w];
+                uint64_t next = pre;
+                for (uint32_t l = 0; l < F.eta; l++) {
+                    const uint32_t idx = (l << shift) | w;
+                    const uint32_t h = hits[idx];
+                    if (h == 0)
+                        continue;
+                    const uint32_t sh = F.alpha * l;
+                    const uint32_t pf = (uint32_t)(pre >> sh) & fm;
+                    const uint32_t room = fm - pf;
+                    const uint32_t inc = h < room ? h : room;
+                    next += (uint64_t)inc << sh;
+                    hits[idx] = pf ? 0u : (inc > tau ? 3u : 1u);
+                }
+                if (next != pre)
+                    F.words[wbase + w] = next;
+                if (kTile && C.mode == Carry::kIn)
+                    s_cell[w] = next;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < kWin; j++) {
+                const uint32_t idx = tid + (uint32_t)j * kRegionWG;
+                const uint32_t h = hits[idx];
+                wt[j] = first[idx];
+                hits[idx] = 0;
+                first[idx] = kIdle;
+                won |= h ? 1u << j : 0u;
+                sure |= h == 3u ? 1u << j : 0u;
+            }
+        }
+        if (!classify)
+            sure = 0;
+        auto store_cells = [&]() {
+#pragma unroll
+            for (int k = 0; k < kHold; k++)
+                asm volatile("" : "+v"(celln[k]));
+            settle();
+#pragma unroll
+            for (int k = 0; k < kHold; k++) {
+                if ((changed >> k) & 1u)
+                    F.words[wbase + tid + (uint32_t)k * kRegionWG] = cell[k];
+                cell[k] = celln[k];
+            }
+        };
+        if constexpr (!by_region) {
+            // sorted by bucket of positions in the hits' room, then appended to
+            // the buckets in runs
+            uint32_t rank[(kWin + 1) / 2];
+#pragma unroll
+            for (int j = 0; j < kWin; j++) {
+                uint32_t x = 0;
+                if ((won >> j) & 1u)
+                    x = atomicAdd(&s_bucket[wt[j] >> rec.log], 1u);
+                rank[j / 2] = j % 2 ? rank[j / 2] | (x << 16) : x;
+            }
+            __syncthreads();
+            uint32_t incl = 0, c = 0;
+            if (tid < kMarkBuckets) {
+                c = s_bucket[tid];
+                incl = wave_inclusive(c);
+                if (lane == 63)
+                    s_sum[wave] = incl;
+            }
+            __syncthreads();
+            uint32_t total = 0;
+#pragma unroll
+            for (uint32_t w = 0; w < kMarkBuckets / 64; w++) {
+                incl += w < wave ? s_sum[w] : 0u;
+                total += s_sum[w];
+            }
+            uint32_t place = 0;
+            if (tid < kMarkBuckets) {
+                s_bucket[tid] = incl - c;
+                if (c)
+                    place = atomicAdd(&rec.cursor[tid], c);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < kWin; j++)
+                if ((won >> j) & 1u)
+                    hits[s_bucket[wt[j] >> rec.log] + ((rank[j / 2] >> (16 * (j % 2))) & 0xFFFFu)] =
+                        wt[j] | (((sure >> j) & 1u ? 3u : 1u) << 30);
+            if (tid < kMarkBuckets)
+                s_place[tid] =
+                    tid * (uint32_t)rec.room + place - s_bucket[tid];
+            __syncthreads();
+            store_cells();
+            for (uint32_t i = tid; i < total; i += kRegionWG) {
+                const uint32_t x = hits[i], t = x & 0x3FFFFFFFu;
+                hits[i] = 0;
+                rec.sorted[s_place[t >> rec.log] + i] =
+                    (t & ((1u << rec.log) - 1u)) | (x >> 30 << rec.log);
+            }
+            for (uint32_t i = tid; i < kMarkBuckets; i += kRegionWG)
+                s_bucket[i] = 0;
+        } else {
+            // a wavefront's records together, from one step of the LDS counter
+            const uint32_t mine_n = (uint32_t)__popc(won);
+            const uint32_t incl = wave_inclusive(mine_n);
+            uint32_t at = 0;
+            if (lane == 63 && incl)
+                at = atomicAdd(&s_nwin, incl);
+            at = (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + incl - mine_n;
+            if (tid == 0)
+                s_base = got;
+            __syncthreads();
+            store_cells();
+            uint32_t *word = (carry_out ? C.word + (uint64_t)C.chunk * C.cap : rec.word) + s_base;
+            uint16_t *half = (carry_out ? C.half + (uint64_t)C.chunk * C.cap : rec.half) + s_base;
+#pragma unroll
+            for (int j = 0; j < kWin; j++)
+                if ((won >> j) & 1u) {
+                    const uint32_t idx = kCells ? ((uint32_t)(j % kEta) << shift) |
+                                                      (tid + (uint32_t)(j / kEta) * kRegionWG)
+                                                : tid + (uint32_t)j * kRegionWG;
+                    word[at] = wt[j];
+                    half[at] = (uint16_t)(carry_out ? idx : ((sure >> j) & 1u ? 3u : 1u));
+                    at++;
+                }
+        }
+        __syncthreads();  // the counters are clean, the region's records counted
+        if (carry_in)
+            mark_carried(F, shift, C, r, s_cell, tau);
+        if (by_region && tid == 0) {
+            if (carry_out) {
+                C.off[(uint64_t)C.chunk * C.stride + r] = s_base;
+                C.n[(uint64_t)C.chunk * C.stride + r] = s_nwin;
+            } else {
+                rec.off[r] = s_base;
+                rec.n[r] = s_nwin;
+            }
+            s_nwin = 0;
+            s_total = 0;
+        }
+        if (by_region || carry_in)
+            __syncthreads();  // the sums and s_cell are rewritten by the next region
+    };
+    __syncthreads();  // counters clean, sums zero
+    if constexpr (kLanes == 0) {
+        const uint16_t *__restrict__ turned = (const uint16_t *)table;
+        auto bounds = [&](uint32_t r, uint32_t b, uint32_t &s, uint32_t &e) {
+            s = e = 0;
+            if (b < B.n_blocks && r < P.n_regions) {
+                s = turned[(uint64_t)r * B.turned + b];
+                e = turned[(uint64_t)(r + 1u) * B.turned + b];
+            }
+        };
+        uint32_t ns, ne;
+        bounds(r, threadIdx.x, ns, ne);
+        for (; r < P.n_regions; r += grid) {
+            uint32_t mine = 0;
             for (uint32_t b0 = wave * 64u; b0 < B.n_blocks; b0 += kRegionWG) {
                 const uint32_t b = b0 + lane;
-                const uint32_t s = ns[0], len = ne[0] - ns[0];
+                const uint32_t s = ns, len = ne - ns;
                 const uint32_t incl = wave_inclusive(len);
                 const uint32_t pre = incl - len;
                 const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
@@ -547,7 +740,7 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
                         (uint32_t)(some >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0u));
                     s_run[wave][i] = make_uint2(b * B.cap + s - pre, b << B.pos_log);
                 }
-                bounds(r, b + kRegionWG, ns[0], ne[0]);
+                bounds(r, b + kRegionWG, ns, ne);
                 for (uint32_t w0 = 0; w0 < n; w0 += kWindow) {
                     if (lane < 2u * kChunks)
                         s_head[wave][lane] = 0;
@@ -588,11 +781,143 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
                     __builtin_amdgcn_wave_barrier();
                 }
             }
-        } else {
-            for (uint32_t b0 = team; b0 < n_blocks; b0 += kUnroll * kTeams) {
+            finish(
+                r, mine, [&]() { bounds(r + grid, threadIdx.x, ns, ne); },
+                [&]() { asm volatile("" : "+v"(ns), "+v"(ne)); });
+        }
+    } else if constexpr (kTwo) {
+        // A wavefront takes every kWaves-th superblock's run, and lays their
+        // 16-byte groups of entries end to end over its lanes.  The groups of
+        // the next region (of as many as a step takes: nearly always all) are
+        // requested before the current region's counters are updated, and the
+        // bounds of the one after behind them.
+        constexpr int kGroups = 5;
+        constexpr uint32_t kSet = kWaves * 64;
+        const uint32_t *__restrict__ starts = (const uint32_t *)table;
+        uint32_t bs, be;  // the lane's run: its entries in the list
+        auto bounds = [&](uint32_t r, uint32_t b0) {
+            const uint32_t b = b0 + lane * kWaves + wave;
+            const bool in = b < B.n_super && r < P.n_regions;
+            const uint32_t *t = starts + (in ? (uint64_t)b * (P.n_regions + 1u) + r : 0ull);
+            bs = t[0];
+            be = in ? t[1] : bs;
+        };
+        uint32_t rs, re, incl, n;  // runs of a set: entries, groups up to and with the run, all groups
+        auto runs = [&]() {
+            rs = bs;
+            re = be;
+            incl = wave_inclusive(re > rs ? (re - 1u) / 4u + 1u - rs / 4u : 0u);
+            n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        };
+        uint4 x[kGroups];
+        uint32_t h[kGroups], which[kGroups];  // entries; run, and (from bit 28) those in the run
+        auto load = [&](uint32_t w0) {
+#pragma unroll
+            for (int c = 0; c < kGroups; c++) {
+                const uint32_t f0 = w0 + 64u * c, f = f0 + lane;
+                which[c] = 0;
+                if (f0 < n) {
+                    // the run: as many as end at or before the lane's group
+                    uint32_t j = (uint32_t)__popcll(__ballot(incl <= f0)), i = j;
+                    const uint32_t limit = f0 + 64u < n ? f0 + 64u : n;
+                    for (; j < 63u; j++) {
+                        const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)j);
+                        if (end >= limit)
+                            break;
+                        i += f >= end ? 1u : 0u;
+                    }
+                    i = i < 63u ? i : 63u;
+                    const uint32_t s = (uint32_t)__shfl((int)rs, (int)i);
+                    const uint32_t e = (uint32_t)__shfl((int)re, (int)i);
+                    const uint32_t last = (uint32_t)__shfl((int)incl, (int)i);
+                    // groups count back from the run's last
+                    const uint32_t g = ((e - 1u) / 4u + 1u - (last - f)) * 4u;
+                    if (f < n) {
+                        x[c] = *reinterpret_cast<const uint4 *>(list + g);
+                        h[c] = *reinterpret_cast<const uint32_t *>(list_hi + g);
+                        const uint32_t lo = g < s ? s - g : 0u, hi = e - g < 4u ? e - g : 4u;
+                        which[c] = i | (((1u << hi) - (1u << lo)) << 28);
+                    }
+                }
+            }
+        };
+        auto tally = [&](uint32_t b0) {
+#pragma unroll
+            for (int c = 0; c < kGroups; c++) {
+                const uint32_t m = which[c];
+                if (m >> 28) {
+                    const uint32_t b = b0 + (m & 63u) * kWaves + wave;
+                    const uint32_t tb = (b * B.super) << B.pos_log;
+                    if ((m >> 28) & 1u)
+                        count(x[c].x, h[c] & 0xFFu, tb);
+                    if ((m >> 29) & 1u)
+                        count(x[c].y, (h[c] >> 8) & 0xFFu, tb);
+                    if ((m >> 30) & 1u)
+                        count(x[c].z, (h[c] >> 16) & 0xFFu, tb);
+                    if (m >> 31)
+                        count(x[c].w, h[c] >> 24, tb);
+                }
+            }
+        };
+        bounds(r, 0);
+        runs();
+        load(0);
+        bounds(r + grid, 0);
+        for (; r < P.n_regions; r += grid) {
+            uint32_t mine = re - rs;
+            tally(0);
+            for (uint32_t w0 = 64u * kGroups; w0 < n; w0 += 64u * kGroups) {
+                load(w0);
+                tally(0);
+            }
+            for (uint32_t b0 = kSet; b0 < B.n_super; b0 += kSet) {
+                bounds(r, b0);
+                runs();
+                mine += re - rs;
+                for (uint32_t w0 = 0; w0 < n; w0 += 64u * kGroups) {
+                    load(w0);
+                    tally(b0);
+                }
+                if (b0 + kSet >= B.n_super)
+                    bounds(r + grid, 0);
+            }
+            runs();
+            load(0);
+            bounds(r + 2u * grid, 0);
+            finish(
+                r, mine, [&]() {},
+                [&]() {
+#pragma unroll
+                    for (int c = 0; c < kGroups; c++)
+                        asm volatile(""
+                                     : "+v"(x[c].x), "+v"(x[c].y), "+v"(x[c].z), "+v"(x[c].w),
+                                       "+v"(h[c]));
+                    asm volatile("" : "+v"(bs), "+v"(be));
+                });
+        }
+    } else {
+        // a team of lanes takes a run, kUnroll runs in flight
+        constexpr uint32_t kTeams = kRegionWG / kLanes;
+        constexpr int kUnroll = 2;
+        const uint32_t team = threadIdx.x / kLanes, sub = threadIdx.x % kLanes;
+        uint32_t ns[kUnroll], ne[kUnroll];
+        auto bounds = [&](uint32_t r, uint32_t b, uint32_t &s, uint32_t &e) {
+            s = e = 0;
+            if (b < B.n_blocks && r < P.n_regions) {
+                const uint16_t *t = (const uint16_t *)table + (uint64_t)b * B.row + r;
+                s = t[0];
+                e = t[1];
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < kUnroll; u++)
+            bounds(r, team + u * kTeams, ns[u], ne[u]);
+        for (; r < P.n_regions; r += grid) {
+            uint32_t mine = 0;
+            for (uint32_t b0 = team; b0 < B.n_blocks; b0 += kUnroll * kTeams) {
                 // a first 16-byte group of entries of every run, and the next
                 // runs' bounds, are requested before any entry is counted
-                uint32_t s[kUnroll], e[kUnroll], g[kUnroll], h[kUnroll];
+                uint32_t s[kUnroll], e[kUnroll], g[kUnroll];
                 uint4 x[kUnroll];
 #pragma unroll
                 for (int u = 0; u < kUnroll; u++) {
@@ -600,110 +925,45 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
                     s[u] = ns[u];
                     e[u] = ne[u];
                     g[u] = (s[u] & ~3u) + 4u * sub;
-                    if (g[u] < e[u]) {
-                        const uint64_t at = (kTwo ? 0ull : (uint64_t)b * B.cap) + g[u];
-                        x[u] = *reinterpret_cast<const uint4 *>(list + at);
-                        if (kTwo)
-                            h[u] = *reinterpret_cast<const uint32_t *>(list_hi + at);
-                    }
+                    if (g[u] < e[u])
+                        x[u] = *reinterpret_cast<const uint4 *>(list + (uint64_t)b * B.cap + g[u]);
                     mine += sub == 0 ? e[u] - s[u] : 0u;
                     bounds(r, b0 + (uint32_t)(u + kUnroll) * kTeams, ns[u], ne[u]);
                 }
 #pragma unroll
                 for (int u = 0; u < kUnroll; u++) {
-                    const uint32_t b = b0 + (uint32_t)u * kTeams;
-                    const uint32_t tb = kTwo ? (b * B.super) << B.pos_log : b << B.pos_log;
-                    const uint64_t at0 = kTwo ? 0ull : (uint64_t)b * B.cap;
+                    const uint32_t b = b0 + (uint32_t)u * kTeams, tb = b << B.pos_log;
                     while (g[u] < e[u]) {
-                        const uint32_t gn = g[u] + 4u * kTeam;
+                        const uint32_t gn = g[u] + 4u * kLanes;
                         uint4 y = make_uint4(0u, 0u, 0u, 0u);
-                        uint32_t hn = 0;
-                        if (gn < e[u] && gn > g[u]) {
-                            y = *reinterpret_cast<const uint4 *>(list + at0 + gn);
-                            if (kTwo)
-                                hn = *reinterpret_cast<const uint32_t *>(list_hi + at0 + gn);
-                        }
-                        const uint32_t hu = kTwo ? h[u] : 0u;
+                        if (gn < e[u])
+                            y = *reinterpret_cast<const uint4 *>(list + (uint64_t)b * B.cap + gn);
                         if (g[u] >= s[u])
-                            count(x[u].x, hu & 0xFFu, tb);
+                            count(x[u].x, 0u, tb);
                         if (g[u] + 1u >= s[u] && g[u] + 1u < e[u])
-                            count(x[u].y, (hu >> 8) & 0xFFu, tb);
+                            count(x[u].y, 0u, tb);
                         if (g[u] + 2u >= s[u] && g[u] + 2u < e[u])
-                            count(x[u].z, (hu >> 16) & 0xFFu, tb);
+                            count(x[u].z, 0u, tb);
                         if (g[u] + 3u >= s[u] && g[u] + 3u < e[u])
-                            count(x[u].w, hu >> 24, tb);
+                            count(x[u].w, 0u, tb);
                         x[u] = y;
-                        h[u] = hn;
-                        if (gn < g[u])
-                            break;  // past the last 32-bit place
                         g[u] = gn;
                     }
                 }
             }
-        }
-        if (records && mine)
-            atomicAdd(&s_total, mine);
-        __syncthreads();
-        if (records) {
-            // room for a record of every entry of the region
-            if (threadIdx.x == 0)
-                s_base = s_total ? atomicAdd(rec.cursor, s_total) : 0u;
-            __syncthreads();
-        }
-        uint64_t celln[kHold];
-        load_cells(r + grid, celln);
+            finish(
+                r, mine,
+                [&]() {
 #pragma unroll
-        for (int u = 0; u < kUnroll; u++)
-            bounds(r + grid, b_first + u * b_step, ns[u], ne[u]);
-        const uint64_t base = records ? s_base : 0u;
-        const WinnerSink out{flags,
-                             c0,
-                             carry_out ? C.word + (uint64_t)C.chunk * C.cap
-                                       : (rec.n ? rec.word : nullptr),
-                             carry_out ? C.half + (uint64_t)C.chunk * C.cap : rec.half,
-                             base,
-                             &s_nwin,
-                             carry_out};
-        if (kCells) {
+                    for (int u = 0; u < kUnroll; u++)
+                        bounds(r + grid, team + u * kTeams, ns[u], ne[u]);
+                },
+                [&]() {
 #pragma unroll
-            for (int k = 0; k < kHold; k++) {
-                const uint32_t w = threadIdx.x + (uint32_t)k * kRegionWG;
-                if (w < nw) {
-                    const uint64_t next = region_cell(F, shift, wbase, w, cell[k], hits, first, out,
-                                                      classify, tau);
-                    if (kTile && C.mode == Carry::kIn)
-                        s_cell[w] = next;
-                }
-            }
-        } else {
-            for (uint32_t w = threadIdx.x; w < nw; w += kRegionWG) {
-                const uint64_t next = region_cell(F, shift, wbase, w, F.words[wbase + w], hits,
-                                                  first, out, classify, tau);
-                if (kTile && C.mode == Carry::kIn)
-                    s_cell[w] = next;
-            }
+                    for (int u = 0; u < kUnroll; u++)
+                        asm volatile("" : "+v"(ns[u]), "+v"(ne[u]));
+                });
         }
-        __syncthreads();  // the region's LDS work and its winner count are complete
-        if (carry_in)
-            mark_carried(F, shift, C, r, s_cell, tau);
-        if (records) {
-            if (threadIdx.x == 0) {
-                if (carry_out) {
-                    C.off[(uint64_t)C.chunk * C.stride + r] = (uint32_t)base;
-                    C.n[(uint64_t)C.chunk * C.stride + r] = s_nwin;
-                } else {
-                    rec.off[r] = (uint32_t)base;
-                    rec.n[r] = s_nwin;
-                }
-                s_nwin = 0;
-                s_total = 0;
-            }
-        }
-        if (records || carry_in)
-            __syncthreads();  // the sums and s_cell are rewritten by the next region
-#pragma unroll
-        for (int k = 0; k < kHold; k++)
-            cell[k] = celln[k];
     }
 }
 
@@ -712,8 +972,7 @@ namespace {
 using SortKernel = void (*)(FilterArgs, ReadsArgs, uint64_t, uint64_t, BlockPlan, uint32_t,
                             uint32_t *, uint8_t *, uint16_t *, unsigned long long *);
 using RunsKernel = void (*)(FilterArgs, uint64_t, BinPlan, BlockPlan, const uint32_t *,
-                            const uint8_t *, const void *, uint8_t *, int, uint32_t, RecordSpace,
-                            Carry);
+                            const uint8_t *, const void *, int, uint32_t, RecordSpace, Carry);
 
 template <int kKh, bool kFast, bool kWide, bool kTwo>
 SortKernel sort_kernel_of(const BlockPlan &B) {
@@ -747,32 +1006,31 @@ SortKernel sort_kernel(const FilterArgs &F, uint32_t k, const BlockPlan &B) {
     }
 }
 
-template <int kCounters, int kCells>
+template <int kCounters, int kCells, bool kSorted>
 RunsKernel runs_kernel_of(const BlockPlan &B) {
     if (B.two)
-        return B.lanes == 4 ? k_region_runs<kCounters, kCells, 4, true>
-                            : k_region_runs<kCounters, kCells, 16, true>;
+        return k_region_runs<kCounters, kCells, 1, true, kSorted>;
     if (B.turned)
-        return k_region_runs<kCounters, kCells, 0, false>;
-    return B.lanes == 4 ? k_region_runs<kCounters, kCells, 4, false>
-                        : k_region_runs<kCounters, kCells, 16, false>;
+        return k_region_runs<kCounters, kCells, 0, false, kSorted>;
+    return B.lanes == 4 ? k_region_runs<kCounters, kCells, 4, false, kSorted>
+                        : k_region_runs<kCounters, kCells, 16, false, kSorted>;
 }
 
 // The region pass's instance: counters per region, cells per thread, and
 // lanes per run.
-template <int kCounters>
+template <int kCounters, bool kSorted>
 RunsKernel runs_kernel(const BinPlan &P, const BlockPlan &B) {
     switch ((1u << P.region_shift) / kRegionWG) {
     case 0:
-        return runs_kernel_of<kCounters, 0>(B);
+        return runs_kernel_of<kCounters, 0, kSorted>(B);
     case 1:
-        return runs_kernel_of<kCounters, 1>(B);
+        return runs_kernel_of<kCounters, 1, kSorted>(B);
     case 2:
-        return runs_kernel_of<kCounters, 2>(B);
+        return runs_kernel_of<kCounters, 2, kSorted>(B);
     case 4:
-        return runs_kernel_of<kCounters, 4>(B);
+        return runs_kernel_of<kCounters, 4, kSorted>(B);
     default:  // two counters a cell
-        return runs_kernel_of<kCounters, 8>(B);
+        return runs_kernel_of<kCounters, 8, kSorted>(B);
     }
 }
 
@@ -827,7 +1085,6 @@ bool block_plan(const BinPlan &plan, uint32_t k_h, uint64_t len, BlockPlan &B) {
     m = m < 1u ? 1u : (m > most ? most : m);
     B.super = m < B.n_blocks ? m : B.n_blocks;
     B.n_super = (B.n_blocks + B.super - 1u) / B.super;
-    B.lanes = (uint64_t)run * B.super >> B.sub_log <= 32 ? 4u : 16u;
     return true;
 }
 
@@ -835,6 +1092,7 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
                                const BinPlan &plan, const BlockPlan &B, const Workspace &W,
                                bool classify, uint32_t tau, const Carry &carry, bool records,
                                hipStream_t s, Profiler *P) {
+    const uint64_t len = c1 - c0;
     // Rooms of the workspace (sized by the plan's count matrices and 8-byte
     // entries, more than these lists need).  One-level form: the list in
     // entries, the table in the count matrix's room or the slot ids', the
@@ -911,6 +1169,9 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
             return e;
     }
     RecordSpace rec{};
+    while ((len + (1ull << rec.log) - 1) >> rec.log > kMarkBuckets || rec.log < 12)
+        rec.log++;
+    rec.n_buckets = (uint32_t)((len + (1ull << rec.log) - 1) >> rec.log);
     if (records || carry.mode == Carry::kOut) {
         rec.cursor = W.n_entries + 3;
         if ((e = fill_u32(rec.cursor, 1, 0u, s)) != hipSuccess)
@@ -924,24 +1185,37 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
             rec.off = index;
             rec.n = index + plan.n_regions;
         }
+    } else {
+        // a position can be first seen by each of its hash functions
+        rec.room = (uint64_t)F.k_h << rec.log;
+        rec.sorted = (uint32_t *)W.bucketed;
+        rec.cursor = mark_cursors(W);
     }
     const void *runs = B.two ? (const void *)starts
                              : (const void *)(B.turned ? turned : table);
     if (P)
         P->begin(kPhRegion, s);
-    hipLaunchKernelGGL(plan.region_counters == (uint32_t)kSmallRegionCounters
-                           ? runs_kernel<kSmallRegionCounters>(plan, B)
-                           : runs_kernel<kRegionCounters>(plan, B),
+    const bool small = plan.region_counters == (uint32_t)kSmallRegionCounters;
+    hipLaunchKernelGGL(rec.sorted ? (small ? runs_kernel<kSmallRegionCounters, true>(plan, B)
+                                           : runs_kernel<kRegionCounters, true>(plan, B))
+                                  : (small ? runs_kernel<kSmallRegionCounters, false>(plan, B)
+                                           : runs_kernel<kRegionCounters, false>(plan, B)),
                        dim3(region_grid(plan.n_regions, plan.region_counters)), dim3(kRegionWG), 0,
                        s, F, c0, plan, B, (const uint32_t *)(B.two ? merged : list),
-                       (const uint8_t *)merged_hi, runs, W.flags8, classify ? 1 : 0, tau, rec,
-                       carry);
+                       (const uint8_t *)merged_hi, runs, classify ? 1 : 0, tau, rec, carry);
     if (P)
         P->end(s);
     e = hipGetLastError();
     if (e == hipSuccess && records)
-        e = launch_record_winners(plan.n_regions, rec.off, rec.n, rec.word, rec.half, c0, c1 - c0,
-                                  W, s, P);
+        return launch_record_winners(plan.n_regions, rec.off, rec.n, rec.word, rec.half, c0, len,
+                                     R.n_bases, W, s, P);
+    if (e == hipSuccess && rec.sorted) {
+        if (P)
+            P->begin(kPhWinners, s);
+        e = launch_marks(rec.sorted, rec.room, rec.log, rec.cursor, true, c0, len, R.n_bases, W, s);
+        if (P)
+            P->end(s);
+    }
     return e;
 }
 

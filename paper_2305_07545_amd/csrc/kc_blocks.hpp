@@ -60,6 +60,13 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
 // W.bucketed (kc_binned.hip).
 hipError_t launch_record_winners(uint32_t n_regions, const uint32_t *off, const uint32_t *n,
                                  const uint32_t *word, const uint16_t *half, uint64_t c0,
-                                 uint64_t len, const Workspace &W, hipStream_t s, Profiler *P);
+                                 uint64_t len, uint64_t n_bases, const Workspace &W, hipStream_t s,
+                                 Profiler *P);
+// The distinct and trustworthy bits and tile counts of chunk [c0, c0 + len)
+// from records sorted by bucket of 2^log positions (bucket g's cursor[g]
+// records at in + g * room: position | mark << log).
+hipError_t launch_marks(const uint32_t *in, uint64_t room, uint32_t log, uint32_t *cursor,
+                        bool clean, uint64_t c0, uint64_t len, uint64_t n_bases,
+                        const Workspace &W, hipStream_t s);
 
 }  // namespace kc

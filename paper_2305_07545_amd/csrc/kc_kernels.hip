@@ -10,8 +10,8 @@
 //                 before the chunk: atomicMin(first[slot], t)
 //     increment   saturating counter increments (Algorithm 3)
 //     resolve     occurrence t is distinct iff first[slot] == t for one of
-//                 its slots; the winner resets the entry; per-position flag
-//                 bits and per-tile counts
+//                 its slots; the winner resets the entry; per-position bits
+//                 and per-tile counts
 //   (claim and increment are one kernel while the whole filter is zero)
 //   scan          exclusive scan of per-tile distinct counts
 //   scatter       distinct canonical keys written in position order
@@ -142,49 +142,77 @@ __global__ void __launch_bounds__(kWG) k_insert_phase(FilterArgs F, ReadsArgs R,
     }
 }
 
+// (the chunk's distinct bits are written whole, a wavefront's 64 positions at
+// a time)
 __global__ void __launch_bounds__(kWG) k_resolve(FilterArgs F, ReadsArgs R, uint64_t c0,
-                                                 uint64_t c1, uint8_t *__restrict__ flags) {
+                                                 uint64_t c1, uint32_t *__restrict__ dbits) {
     const uint64_t tile0 = c0 + (uint64_t)blockIdx.x * kTile;
 #pragma unroll 1
     for (int j = 0; j < kTile / kWG; j++) {
         uint64_t p = tile0 + (uint64_t)j * kWG + threadIdx.x;
-        if (p >= c1 || !window_valid(R, p))
-            continue;
-        uint64_t fwd = window_key(R.codes, p, R.k);
-        Canon c = canonical(fwd, R.k);
-        uint32_t t = (uint32_t)(p - c0);
         bool win = false;
-        for (uint32_t a = 1; a <= F.k_h; a++) {
-            uint64_t h = (a == 1) ? c.h1 : hash_a(c.b0, c.b1, a);
-            uint64_t word;
-            uint32_t l;
-            slot_of(F, h, word, l);
-            uint64_t idx = word * F.eta + l;
-            if (F.aux[idx] == t) {
-                win = true;
-                F.aux[idx] = kIdle;
+        if (p < c1 && window_valid(R, p)) {
+            uint64_t fwd = window_key(R.codes, p, R.k);
+            Canon c = canonical(fwd, R.k);
+            uint32_t t = (uint32_t)(p - c0);
+            for (uint32_t a = 1; a <= F.k_h; a++) {
+                uint64_t h = (a == 1) ? c.h1 : hash_a(c.b0, c.b1, a);
+                uint64_t word;
+                uint32_t l;
+                slot_of(F, h, word, l);
+                uint64_t idx = word * F.eta + l;
+                if (F.aux[idx] == t) {
+                    win = true;
+                    F.aux[idx] = kIdle;
+                }
             }
         }
-        if (win)
-            flags[p] = 1;
+        const uint64_t m = __ballot(win);
+        if ((threadIdx.x & 63u) == 0)
+            *reinterpret_cast<uint64_t *>(dbits + (p >> 5)) = m;
     }
 }
 
 // ---------------------------------------------------------------------------
 // ordered output of the distinct k-mers (and optionally of their
-// trustworthy / erroneous split): flag byte per position, 1 = distinct,
-// 3 = distinct and trustworthy
+// trustworthy / erroneous split): one distinct bit per position, and one
+// trustworthy bit (meaningful where the distinct bit is set)
 // ---------------------------------------------------------------------------
-// Per tile: distinct flags (bit 0 of a flag byte), trustworthy flags (bit 1)
-// and, when asked, valid windows.  kSuper tiles per iteration; one 32-bit
-// word (4 flag bytes) per thread and tile.
-__global__ void __launch_bounds__(kWG) k_tile_count(ReadsArgs R, const uint8_t *__restrict__ flags,
-                                                    uint64_t n_tiles, int count_valid,
+// Direct path: per tile, distinct bits and (added up for the call) valid
+// windows.  One wavefront per tile.
+__global__ void __launch_bounds__(kWG) k_bits_count(ReadsArgs R, const uint32_t *__restrict__ dbits,
+                                                    uint64_t n_tiles, uint32_t *__restrict__ tile_d,
+                                                    unsigned long long *__restrict__ n_valid) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t n_waves = (uint64_t)gridDim.x * (kWG / 64);
+    uint64_t nv = 0;  // the same on every lane
+    for (uint64_t tile = (uint64_t)blockIdx.x * (kWG / 64) + wave; tile < n_tiles;
+         tile += n_waves) {
+        uint32_t nd = lane < kTile / 32 ? (uint32_t)__popc(dbits[tile * (kTile / 32) + lane]) : 0u;
+#pragma unroll 1
+        for (int j = 0; j < kTile / 64; j++) {
+            const uint64_t pb = tile * kTile + 64u * (uint64_t)j;
+            WaveWords w;
+            wave_load(R, pb, w);
+            uint64_t fwd;
+            nv += (uint32_t)__popcll(__ballot(wave_window(w, pb, lane, R.k, R.n_bases, fwd)));
+        }
+        for (uint32_t d = 32; d >= 1; d >>= 1)
+            nd += __shfl_down(nd, d, 64);
+        if (lane == 0)
+            tile_d[tile] = nd;
+    }
+    if (lane == 0 && nv)
+        atomicAdd(n_valid, (unsigned long long)nv);
+}
+
+// Batched form: per tile, distinct flags (bit 0 of a flag byte) and
+// trustworthy flags (bit 1).  One wavefront per tile, 16 flag bytes per lane.
+__global__ void __launch_bounds__(kWG) k_tile_count(const uint8_t *__restrict__ flags,
+                                                    uint64_t n_tiles,
                                                     uint32_t *__restrict__ tile_d,
-                                                    uint32_t *__restrict__ tile_t,
-                                                    uint32_t *__restrict__ tile_v) {
-    // one wavefront per tile: 16 flag bytes per lane, counts reduced by
-    // shuffles, no LDS and no barriers
+                                                    uint32_t *__restrict__ tile_t) {
     static_assert(kTile == 64 * 16, "16 flag bytes per lane and tile");
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -197,17 +225,6 @@ __global__ void __launch_bounds__(kWG) k_tile_count(ReadsArgs R, const uint8_t *
                                  __popc(x.z & 0x01010101u) + __popc(x.w & 0x01010101u));
         uint32_t nt = (uint32_t)(__popc(x.x & 0x02020202u) + __popc(x.y & 0x02020202u) +
                                  __popc(x.z & 0x02020202u) + __popc(x.w & 0x02020202u));
-        uint32_t nv = 0;  // the same on every lane
-        if (count_valid) {
-#pragma unroll 1
-            for (int j = 0; j < kTile / 64; j++) {
-                const uint64_t pb = tile * kTile + 64u * (uint64_t)j;
-                WaveWords w;
-                wave_load(R, pb, w);
-                uint64_t fwd;
-                nv += (uint32_t)__popcll(__ballot(wave_window(w, pb, lane, R.k, R.n_bases, fwd)));
-            }
-        }
         for (uint32_t d = 32; d >= 1; d >>= 1) {
             nd += __shfl_down(nd, d, 64);
             nt += __shfl_down(nt, d, 64);
@@ -215,18 +232,18 @@ __global__ void __launch_bounds__(kWG) k_tile_count(ReadsArgs R, const uint8_t *
         if (lane == 0) {
             tile_d[tile] = nd;
             tile_t[tile] = nt;
-            tile_v[tile] = nv;
         }
     }
 }
 
-// Ordered output, one wavefront per tile.  The tile's flagged positions are
+// Ordered output, one wavefront per tile.  The tile's distinct positions are
 // first gathered into a wavefront-private list in position order (so that
 // only they are hashed), then each listed window's canonical key goes to the
 // distinct list and, when split, to the trustworthy or erroneous list.
 // kWide: k-mers of 33..64 bases, written as (low, high) word pairs.
 template <bool kWide>
-__global__ void __launch_bounds__(kWG) k_compact(ReadsArgs R, const uint8_t *__restrict__ flags,
+__global__ void __launch_bounds__(kWG) k_compact(ReadsArgs R, const uint32_t *__restrict__ dbits,
+                                                 const uint32_t *__restrict__ tbits,
                                                  uint64_t n_tiles,
                                                  const uint64_t *__restrict__ off_d,
                                                  const uint64_t *__restrict__ off_t,
@@ -235,48 +252,41 @@ __global__ void __launch_bounds__(kWG) k_compact(ReadsArgs R, const uint8_t *__r
                                                  uint64_t *__restrict__ trust,
                                                  uint64_t *__restrict__ err, uint64_t cap_te,
                                                  int split) {
-    static_assert(kTile == 64 * 16, "16 flag bytes per lane and tile");
+    static_assert(kTile == 64 * 16, "16 bits per lane and tile");
     static_assert(kTile <= 32768, "list entries are 15-bit");
-    __shared__ uint16_t s_pos[kWG / 64][kTile];  // tile position of the i-th flagged window
+    __shared__ uint16_t s_pos[kWG / 64][kTile];  // tile position of the i-th distinct window
     __shared__ uint16_t s_tb[kWG / 64][kTile];   // trustworthy windows before it; bit 15: it is one
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t n_waves = (uint64_t)gridDim.x * (kWG / 64);
-    const uint4 *f128 = reinterpret_cast<const uint4 *>(flags);
+    const uint16_t *d16 = reinterpret_cast<const uint16_t *>(dbits);
+    const uint16_t *t16 = reinterpret_cast<const uint16_t *>(tbits);
     const uint64_t base = split ? *call_base : 0;
     uint16_t *lpos = s_pos[wave];
     uint16_t *ltb = s_tb[wave];
-    // each wavefront's next tile: its flags and offsets are requested before
+    // each wavefront's next tile: its bits and offsets are requested before
     // the current tile's keys are written
     uint64_t tile = (uint64_t)blockIdx.x * (kWG / 64) + wave;
-    uint4 nx = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t nxd = 0, nxt = 0;
     uint64_t nd = 0, nt = 0;
-    if (tile < n_tiles) {
-        nx = f128[tile * 64 + lane];
-        nd = off_d[tile];
-        nt = split ? off_t[tile] : 0;
-    }
+    auto request = [&](uint64_t q) {
+        if (q < n_tiles) {
+            nxd = d16[q * 64 + lane];
+            nd = off_d[q];
+            nxt = split ? t16[q * 64 + lane] : 0u;
+            nt = split ? off_t[q] : 0;
+        }
+    };
+    request(tile);
     for (; tile < n_tiles; tile += n_waves) {
-        const uint4 x4 = nx;
+        const uint32_t xd = nxd, xt = nxt & nxd;
         const uint64_t od = nd;
         const uint64_t ot = nt;
-        const uint64_t next = tile + n_waves;
-        if (next < n_tiles) {
-            nx = f128[next * 64 + lane];
-            nd = off_d[next];
-            nt = split ? off_t[next] : 0;
-        }
-        const uint32_t x[4] = {x4.x, x4.y, x4.z, x4.w};
-        uint32_t cd = 0, ct = 0;
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-            cd += (uint32_t)__popc(x[u] & 0x01010101u);
-            ct += (uint32_t)__popc(x[u] & 0x02020202u);
-        }
+        request(tile + n_waves);
         uint32_t tot_d, tot_t;
-        uint32_t rd = wave_exclusive(cd, lane, tot_d);
-        uint32_t rt = wave_exclusive(ct, lane, tot_t);
-        list_flags(x, lane, rd, rt, lpos, ltb);
+        const uint32_t rd = wave_exclusive((uint32_t)__popc(xd), lane, tot_d);
+        const uint32_t rt = wave_exclusive((uint32_t)__popc(xt), lane, tot_t);
+        list_bits(xd, xt, lane, rd, rt, lpos, ltb);
         __builtin_amdgcn_wave_barrier();
         const uint64_t pos0 = tile * kTile;
         for (uint32_t i = lane; i < tot_d; i += 64) {
@@ -315,35 +325,6 @@ __global__ void __launch_bounds__(kWG) k_compact(ReadsArgs R, const uint8_t *__r
         }
         __builtin_amdgcn_wave_barrier();  // the list is rewritten by the next tile
     }
-}
-
-// totals[0] distinct, [1] trustworthy, [2] valid windows counted by the tile
-// pass, [5] valid windows counted by the insert passes
-__global__ void k_finish_insert(uint64_t *__restrict__ n_distinct, uint64_t *__restrict__ n_windows,
-                                uint64_t *__restrict__ n_trust, uint64_t *__restrict__ n_err,
-                                const uint64_t *__restrict__ totals, int windows_counted,
-                                uint64_t cap_d, uint64_t cap_te, uint32_t *__restrict__ status) {
-    if (threadIdx.x != 0 || blockIdx.x != 0)
-        return;
-    const uint64_t nd = *n_distinct + totals[0];
-    *n_distinct = nd;
-    if (n_windows)
-        *n_windows += windows_counted ? totals[5] : totals[2];
-    bool over = nd > cap_d;
-    if (n_trust) {
-        *n_trust = totals[1];
-        *n_err = totals[0] - totals[1];
-        over = over || totals[1] > cap_te || totals[0] - totals[1] > cap_te;
-    }
-    if (over)
-        atomicOr(status, kStatusRange);
-}
-
-// copies *src to *dst (device scalars), so that a later kernel sees a value
-// as it was at this point of the stream
-__global__ void k_copy_u64(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst) {
-    if (threadIdx.x == 0 && blockIdx.x == 0)
-        *dst = *src;
 }
 
 // ---------------------------------------------------------------------------
@@ -412,46 +393,39 @@ __device__ __forceinline__ uint64_t query_canon_wide(const FilterArgs &F, const 
     return best;
 }
 
-// Classification in the position domain (Algorithm 2 with Query-II): every
-// position of [0, n_tiles * kTile) flagged distinct (1) whose k-mer's
-// frequency in the countBF as it stands is above tau becomes 3 (distinct
-// and trustworthy), the mark the region pass gives the first-seen k-mers
-// whose final counter it knows; the ordered compaction then splits the
-// distinct list by the marks.  One wavefront per tile of 1024 flag bytes
-// (16 per lane): the flagged positions are listed in LDS, then each lane
-// takes one, rebuilds its canonical k-mer from the packed codes and reads
-// its k_h counters.  The marks go into an LDS copy of the tile, and a lane
-// whose 16 bytes changed writes them back as one 16-byte store (no single-
-// byte stores at scattered positions).
+// Classification in the position domain (Algorithm 2 with Query-II): the
+// trustworthy bits of every position of [0, n_tiles * kTile): a distinct
+// position whose k-mer's frequency in the countBF as it stands is above tau
+// (the mark the region pass gives the first-seen k-mers whose final counter
+// it knows); the ordered compaction then splits the distinct list by them.
+// One wavefront per tile: the distinct positions are listed in LDS, then
+// each lane takes one, rebuilds its canonical k-mer from the packed codes and
+// reads its k_h counters.
 template <bool kWide>
 __global__ void __launch_bounds__(kWG) k_classify_flags(FilterArgs F, ReadsArgs R,
-                                                        uint8_t *__restrict__ flags,
+                                                        const uint32_t *__restrict__ dbits,
+                                                        uint32_t *__restrict__ tbits,
+                                                        uint32_t *__restrict__ tile_t,
                                                         uint64_t n_tiles, uint32_t tau) {
-    static_assert(kTile == 64 * 16, "16 flag bytes per lane and tile");
+    static_assert(kTile == 64 * 16, "16 bits per lane and tile");
     __shared__ uint16_t s_pos[kWG / 64][kTile];
-    __shared__ uint16_t s_tb[kWG / 64][kTile];  // list_flags' second list (unused here)
-    __shared__ uint4 s_tile[kWG / 64][64];      // the tile's flag bytes, marked
+    __shared__ uint16_t s_tb[kWG / 64][kTile];  // list_bits' second list (unused here)
+    __shared__ uint32_t s_bits[kWG / 64][kTile / 32];
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t n_waves = (uint64_t)gridDim.x * (kWG / 64);
-    uint4 *f128 = reinterpret_cast<uint4 *>(flags);
+    const uint16_t *d16 = reinterpret_cast<const uint16_t *>(dbits);
     uint16_t *lpos = s_pos[wave];
     uint16_t *ltb = s_tb[wave];
-    uint8_t *lmark = reinterpret_cast<uint8_t *>(s_tile[wave]);
+    uint32_t *bits = s_bits[wave];
     for (uint64_t tile = (uint64_t)blockIdx.x * (kWG / 64) + wave; tile < n_tiles;
          tile += n_waves) {
-        const uint4 x4 = f128[tile * 64 + lane];
-        const uint32_t x[4] = {x4.x, x4.y, x4.z, x4.w};
-        uint32_t cd = 0;
-#pragma unroll
-        for (int u = 0; u < 4; u++)
-            cd += (uint32_t)__popc(x[u] & 0x01010101u);
+        const uint32_t xd = d16[tile * 64 + lane];
         uint32_t tot_d;
-        const uint32_t rd = wave_exclusive(cd, lane, tot_d);
-        if (tot_d == 0)
-            continue;
-        list_flags(x, lane, rd, 0, lpos, ltb);
-        s_tile[wave][lane] = x4;
+        const uint32_t rd = wave_exclusive((uint32_t)__popc(xd), lane, tot_d);
+        list_bits(xd, 0u, lane, rd, 0, lpos, ltb);
+        if (lane < kTile / 32)
+            bits[lane] = 0;
         __builtin_amdgcn_wave_barrier();
         const uint64_t pos0 = tile * kTile;
         for (uint32_t i = lane; i < tot_d; i += 64) {
@@ -461,13 +435,20 @@ __global__ void __launch_bounds__(kWG) k_classify_flags(FilterArgs F, ReadsArgs 
                 kWide ? query_canon_wide(F, canonical_wide(window_key_wide(R.codes, p, R.k), R.k))
                       : query_canon(F, canonical_fast(window_key(R.codes, p, R.k), R.k));
             if (f > (uint64_t)tau)
-                lmark[q] = 3;
+                atomicOr(&bits[q >> 5], 1u << (q & 31u));
         }
         __builtin_amdgcn_wave_barrier();
-        const uint4 y4 = s_tile[wave][lane];
-        if (y4.x != x4.x || y4.y != x4.y || y4.z != x4.z || y4.w != x4.w)
-            f128[tile * 64 + lane] = y4;
-        __builtin_amdgcn_wave_barrier();  // the list and the tile are rewritten by the next tile
+        uint32_t nt = 0;
+        if (lane < kTile / 32) {
+            const uint32_t x = bits[lane];
+            tbits[tile * (kTile / 32) + lane] = x;
+            nt = (uint32_t)__popc(x);
+        }
+        for (uint32_t d = 32; d >= 1; d >>= 1)
+            nt += __shfl_down(nt, d, 64);
+        if (lane == 0)
+            tile_t[tile] = nt;
+        __builtin_amdgcn_wave_barrier();  // the list and the bits are rewritten by the next tile
     }
 }
 
@@ -642,16 +623,34 @@ static hipError_t launch(Profiler *P, int phase, K kernel, dim3 grid, dim3 block
     return hipGetLastError();
 }
 
+// The counters a call starts from zero, by n threads, this one the i-th.
+__device__ __forceinline__ void clear_call(const CallState &c, uint64_t i, uint64_t n) {
+    for (uint64_t x = i; x < c.n_scan; x += n)
+        c.scan[x] = 0;
+    for (uint64_t x = i; x < kMarkBuckets; x += n)
+        c.cursors[x] = 0;
+    if (i == 0)
+        *c.n_valid = 0;
+}
+
+__global__ void __launch_bounds__(256) k_clear_call(CallState call) {
+    clear_call(call, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x,
+               (uint64_t)gridDim.x * blockDim.x);
+}
+
 // The valid-window bitmap of K-base windows (valid_word), one mask word per
 // thread.  Only the words of the call's tiles are written (n_out), so that a
 // read set inside a larger buffer leaves its neighbours' words alone; the
 // bin passes read no word past them.
+// Also clears the call's counters (clear_call): one launch fewer.
 __global__ void __launch_bounds__(256) k_valid_windows(const uint32_t *__restrict__ inv,
                                                        const uint32_t *__restrict__ rs,
                                                        uint64_t n_words, uint64_t n_out,
                                                        uint64_t n_bases, uint32_t K,
-                                                       uint32_t *__restrict__ valid) {
+                                                       uint32_t *__restrict__ valid,
+                                                       CallState call) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    clear_call(call, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride);
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_out; i += stride)
         valid[i] = valid_word(inv, rs, n_words, i, K, n_bases);
 }
@@ -664,23 +663,31 @@ hipError_t launch_valid_windows(uint64_t n_bases, uint32_t k, const Workspace &W
         P->begin(kPhValid, s);
     hipLaunchKernelGGL(k_valid_windows, dim3(grid_for(n_out, 256)), dim3(256), 0, s,
                        (const uint32_t *)W.inv, (const uint32_t *)W.rs, n_mask, n_out, n_bases,
-                       k, W.valid);
+                       k, W.valid, call_state(W, n_bases));
     if (P)
         P->end(s);
     return hipGetLastError();
 }
 
+hipError_t launch_clear_call(uint64_t n_bases, const Workspace &W, hipStream_t s) {
+    const CallState c = call_state(W, n_bases);
+    hipLaunchKernelGGL(k_clear_call, dim3(grid_for(c.n_scan + kMarkBuckets, 256)), dim3(256), 0, s,
+                       c);
+    return hipGetLastError();
+}
+
 hipError_t launch_ingest(const uint8_t *reads, uint64_t n_bases, const uint64_t *offsets,
-                         uint64_t n_reads, const Workspace &W, hipStream_t s, Profiler *P) {
+                         uint64_t n_reads, const Workspace &W, bool flag_bytes, hipStream_t s,
+                         Profiler *P) {
     uint64_t n_mask = mask_words(n_bases);
     if (P)
         P->begin(kPhIngest, s);
-    // k_ingest also clears the read-start words and the flag bytes of every
-    // tile of the call (n_mask * 32 positions cover them)
+    // k_ingest also clears the read-start words and, for the batched form, the
+    // flag bytes of every tile of the call (n_mask * 32 positions cover them)
     int aligned = ((uintptr_t)reads & 15u) == 0;
     hipLaunchKernelGGL(k_ingest, dim3(grid_for(n_mask, 256)), dim3(256), 0, s, reads, n_bases,
-                       W.codes, W.inv, W.rs, W.flags8, n_mask, tiles(n_bases) * (kTile / 32),
-                       aligned);
+                       W.codes, W.inv, W.rs, W.flags8, n_mask,
+                       flag_bytes ? tiles(n_bases) * (kTile / 32) : 0ull, aligned);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && n_reads > 0) {
         hipLaunchKernelGGL(k_read_starts, dim3(grid_for(n_reads, 256)), dim3(256), 0, s, offsets,
@@ -705,60 +712,55 @@ hipError_t launch_insert_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
     }
     if (e != hipSuccess)
         return e;
-    return launch(P, kPhResolve, k_resolve, grid, block, s, F, R, c0, c1, W.flags8);
+    return launch(P, kPhResolve, k_resolve, grid, block, s, F, R, c0, c1,
+                  distinct_bits(W));
 }
 
-hipError_t launch_tile_count(const ReadsArgs &R, const Workspace &W, uint64_t n_tiles,
-                             hipStream_t s) {
+hipError_t launch_tile_count(const Workspace &W, uint64_t n_tiles, hipStream_t s) {
     const dim3 grid((unsigned)(n_tiles < (uint64_t)kTileGrid ? n_tiles : kTileGrid));
-    hipLaunchKernelGGL(k_tile_count, grid, dim3(kWG), 0, s, R, (const uint8_t *)W.flags8, n_tiles,
-                       0, W.tile_a, W.tile_b, W.tile_c);
+    hipLaunchKernelGGL(k_tile_count, grid, dim3(kWG), 0, s, (const uint8_t *)W.flags8, n_tiles,
+                       W.tile_a, W.tile_b);
     return hipGetLastError();
 }
 
 hipError_t launch_distinct(const ReadsArgs &R, const Workspace &W, uint64_t *distinct,
                            uint64_t cap_d, uint64_t *n_distinct, uint64_t *n_windows,
                            uint64_t *trust, uint64_t *n_trust, uint64_t *err, uint64_t *n_err,
-                           uint64_t cap_te, uint32_t *status, bool windows_counted,
-                           hipStream_t s, Profiler *P) {
+                           uint64_t cap_te, uint32_t *status, bool counted, hipStream_t s,
+                           Profiler *P) {
     const uint64_t n_tiles = tiles(R.n_bases);
     const bool split = trust != nullptr;
     const dim3 grid((unsigned)(n_tiles < (uint64_t)kTileGrid ? n_tiles : kTileGrid));
-    hipError_t e = launch(P, kPhTileCount, k_tile_count, grid, dim3(kWG), s, R,
-                          (const uint8_t *)W.flags8, n_tiles, windows_counted ? 0 : 1, W.tile_a,
-                          W.tile_b, W.tile_c);
+    const uint32_t *dbits = distinct_bits(W), *tbits = trust_bits(W, R.n_bases);
+    hipError_t e = hipSuccess;
+    if (!counted)
+        e = launch(P, kPhTileCount, k_bits_count, grid, dim3(kWG), s, R, dbits, n_tiles, W.tile_a,
+                   (unsigned long long *)(W.totals + 5));
     if (P)
         P->begin(kPhScan, s);
-    if (e == hipSuccess)
-        e = scan_u32_u64(W.tile_a, W.off_a, n_tiles, n_distinct, W.totals + 0, W.partial64, s);
-    if (e == hipSuccess && split)
-        e = scan_u32_u64(W.tile_b, W.off_b, n_tiles, nullptr, W.totals + 1, W.partial64, s);
-    if (e == hipSuccess && !windows_counted)
-        e = scan_u32_u64(W.tile_c, W.off_c, n_tiles, nullptr, W.totals + 2, W.partial64, s);
-    if (e == hipSuccess) {  // the call's first distinct index, before k_finish_insert moves it
-        hipLaunchKernelGGL(k_copy_u64, dim3(1), dim3(64), 0, s, (const uint64_t *)n_distinct,
-                           W.totals + 3);
-        e = hipGetLastError();
+    if (e == hipSuccess) {
+        TileScan T{};
+        T.n_distinct = n_distinct;
+        T.n_windows = n_windows;
+        T.n_trust = split ? n_trust : nullptr;
+        T.n_err = n_err;
+        T.cap_d = cap_d;
+        T.cap_te = cap_te;
+        T.status = status;
+        e = launch_tile_scan(W, n_tiles, split, T, s);
     }
     if (P)
         P->end(s);
     if (e == hipSuccess && R.k > 32)
-        e = launch(P, kPhScatter, k_compact<true>, grid, dim3(kWG), s, R,
-                   (const uint8_t *)W.flags8, n_tiles, (const uint64_t *)W.off_a,
-                   (const uint64_t *)W.off_b, (const uint64_t *)(W.totals + 3), distinct, cap_d,
-                   trust, err, cap_te, split ? 1 : 0);
+        e = launch(P, kPhScatter, k_compact<true>, grid, dim3(kWG), s, R, dbits, tbits, n_tiles,
+                   (const uint64_t *)W.off_a, (const uint64_t *)W.off_b,
+                   (const uint64_t *)(W.totals + 3), distinct, cap_d, trust, err, cap_te,
+                   split ? 1 : 0);
     else if (e == hipSuccess)
-        e = launch(P, kPhScatter, k_compact<false>, grid, dim3(kWG), s, R,
-                   (const uint8_t *)W.flags8, n_tiles, (const uint64_t *)W.off_a,
-                   (const uint64_t *)W.off_b, (const uint64_t *)(W.totals + 3), distinct, cap_d,
-                   trust, err, cap_te, split ? 1 : 0);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_finish_insert, dim3(1), dim3(64), 0, s, n_distinct, n_windows,
-                           split ? n_trust : (uint64_t *)nullptr, n_err,
-                           (const uint64_t *)W.totals, windows_counted ? 1 : 0, cap_d, cap_te,
-                           status);
-        e = hipGetLastError();
-    }
+        e = launch(P, kPhScatter, k_compact<false>, grid, dim3(kWG), s, R, dbits, tbits, n_tiles,
+                   (const uint64_t *)W.off_a, (const uint64_t *)W.off_b,
+                   (const uint64_t *)(W.totals + 3), distinct, cap_d, trust, err, cap_te,
+                   split ? 1 : 0);
     return e;
 }
 
@@ -808,9 +810,9 @@ hipError_t launch_classify_flags(const FilterArgs &F, const ReadsArgs &R, const 
         return hipSuccess;
     const dim3 grid((unsigned)(n_tiles < (uint64_t)kTileGrid ? n_tiles : kTileGrid));
     return R.k > 32 ? launch(P, kPhClassifyMark, k_classify_flags<true>, grid, dim3(kWG), s, F, R,
-                             W.flags8, n_tiles, tau)
+                             distinct_bits(W), trust_bits(W, R.n_bases), W.tile_b, n_tiles, tau)
                     : launch(P, kPhClassifyMark, k_classify_flags<false>, grid, dim3(kWG), s, F,
-                             R, W.flags8, n_tiles, tau);
+                             R, distinct_bits(W), trust_bits(W, R.n_bases), W.tile_b, n_tiles, tau);
 }
 
 hipError_t launch_query(const FilterArgs &F, const uint64_t *keys, uint64_t n, uint32_t *freq,

@@ -73,7 +73,8 @@ struct Workspace {
     uint32_t *inv = nullptr;      // mask_words(cap) invalid-base bits
     uint32_t *rs = nullptr;       // mask_words(cap) read-start bits
     uint32_t *valid = nullptr;    // mask_words(cap) valid-window bits (binned paths)
-    uint8_t *flags8 = nullptr;    // tiles(cap)*kTile flag bytes
+    uint8_t *flags8 = nullptr;    // tiles(cap)*kTile bytes: flag bytes (batched form), or the
+                                  // distinct and trustworthy bits (distinct_bits, trust_bits)
     uint64_t cap = 0;
     // per-tile buffers (tile_cap tiles of positions or keys)
     uint32_t *tile_a = nullptr, *tile_b = nullptr, *tile_c = nullptr;
@@ -185,8 +186,62 @@ __device__ __forceinline__ void list_flags(const uint32_t (&x)[4], uint32_t lane
     }
 }
 
+// The set bits of a lane's 16 positions (d16 distinct, t16 trustworthy, a
+// subset), in position order: entry rd, rd + 1, ... of lpos gets the tile
+// position and of ltb the trustworthy count before it (from rt) with bit 15
+// set for a trustworthy one.
+__device__ __forceinline__ void list_bits(uint32_t d16, uint32_t t16, uint32_t lane, uint32_t rd,
+                                          uint32_t rt, uint16_t *lpos, uint16_t *ltb) {
+    while (d16) {
+        const uint32_t b = (uint32_t)__builtin_ctz(d16);
+        d16 &= d16 - 1u;
+        const uint32_t tr = (t16 >> b) & 1u;
+        lpos[rd] = (uint16_t)(16u * lane + b);
+        ltb[rd] = (uint16_t)(rt | (tr << 15));
+        rd++;
+        rt += tr;
+    }
+}
+
 inline uint64_t mask_words(uint64_t n) { return tiles(n) * (kTile / 32) + 2; }
 inline uint64_t code_words(uint64_t n) { return tiles(n) * (kTile / 16) + 4; }
+
+// The single-set pipeline's outcome per position, in the flag bytes' room: a
+// distinct bit, and a trustworthy bit (meaningful where the first is set), 32
+// positions a word, every word of the call's tiles written.
+inline uint32_t *distinct_bits(const Workspace &W) { return (uint32_t *)W.flags8; }
+inline uint32_t *trust_bits(const Workspace &W, uint64_t n_bases) {
+    return distinct_bits(W) + tiles(n_bases) * (kTile / 32);
+}
+
+// Buckets of positions that the region pass sorts its first-seen records by.
+constexpr uint32_t kMarkBuckets = 512;
+
+// What a call starts from zero: the tile scan's ticket and block states (in
+// off_c's room), the record buckets' cursors, the valid-window count.
+constexpr uint64_t kScanTiles = 4096;  // tiles per workgroup of the tile scan
+inline uint32_t *mark_cursors(const Workspace &W) { return (uint32_t *)W.tmask; }
+struct CallState {
+    uint64_t *scan;
+    uint64_t n_scan;  // words
+    uint32_t *cursors;
+    uint64_t *n_valid;
+};
+inline CallState call_state(const Workspace &W, uint64_t n_bases) {
+    const uint64_t blocks = (tiles(n_bases) + kScanTiles - 1) / kScanTiles;
+    return CallState{W.off_c, 1 + 2 * blocks, mark_cursors(W), W.totals + 5};
+}
+hipError_t launch_clear_call(uint64_t n_bases, const Workspace &W, hipStream_t s);
+
+// Exclusive sums of the tiles' distinct counts (tile_a, onto *n_distinct) and
+// trustworthy counts (tile_b) into off_a and off_b, and the call's counters.
+struct TileScan {
+    uint64_t *n_distinct, *n_windows, *n_trust, *n_err;
+    uint64_t cap_d, cap_te;
+    uint32_t *status;
+};
+hipError_t launch_tile_scan(const Workspace &W, uint64_t n_tiles, bool split, const TileScan &T,
+                            hipStream_t s);
 
 // Phase ids for the profiler (same values as kc_phase in kmerco.h).
 enum Phase {
@@ -196,15 +251,6 @@ enum Phase {
 };
 
 hipError_t fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
-// out[c * rows + r] = in[r * cols + c]: a rows x cols matrix, row-major, to
-// its transpose (rows / 64 <= 65535)
-hipError_t transpose_u32(const uint32_t *in, uint32_t *out, uint64_t rows, uint64_t cols,
-                         hipStream_t s);
-// The same for consecutive rows x cols blocks of a rows x total_cols matrix
-// stored block by block (block z: columns z*cols .. , the last one cut at
-// total_cols); out is the total_cols x rows transpose.
-hipError_t transpose_u32_blocks(const uint32_t *in, uint32_t *out, uint64_t rows, uint64_t cols,
-                                uint64_t total_cols, hipStream_t s);
 hipError_t fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t s);
 
 uint64_t scan_partials(uint64_t n);
@@ -214,9 +260,10 @@ hipError_t scan_u32_u32(const uint32_t *in, uint32_t *out, uint64_t n, uint32_t 
                         uint32_t *partial, hipStream_t s);
 
 hipError_t launch_ingest(const uint8_t *reads, uint64_t n_bases, const uint64_t *offsets,
-                         uint64_t n_reads, const Workspace &W, hipStream_t s, Profiler *P);
+                         uint64_t n_reads, const Workspace &W, bool flag_bytes, hipStream_t s,
+                         Profiler *P);
 // The valid-window bitmap of k-base windows into W.valid (binned paths),
-// from the bitmaps launch_ingest wrote.
+// from the bitmaps launch_ingest wrote; also clears the call's counters.
 hipError_t launch_valid_windows(uint64_t n_bases, uint32_t k, const Workspace &W, hipStream_t s,
                                 Profiler *P);
 hipError_t launch_insert_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t c0, uint64_t c1,
@@ -258,21 +305,22 @@ hipError_t launch_binned_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
 // The winner passes of carried chunk j (positions [c0, c0 + len)) after the
 // last chunk's region pass has marked its records.
 hipError_t launch_carried_winners(const BinPlan &plan, const Carry &carry, uint32_t j, uint64_t c0,
-                                  uint64_t len, const Workspace &W, hipStream_t s, Profiler *P);
-// windows_counted: the insert passes already added this call's valid-window
-// count to W.totals[5] (else the tile pass counts them)
+                                  uint64_t len, uint64_t n_bases, const Workspace &W, hipStream_t s,
+                                  Profiler *P);
+// counted: the insert passes already wrote the tiles' counts and added this
+// call's valid windows to W.totals[5] (else a pass over the bits does)
 hipError_t launch_distinct(const ReadsArgs &R, const Workspace &W, uint64_t *distinct,
                            uint64_t cap_d, uint64_t *n_distinct, uint64_t *n_windows,
                            uint64_t *trust, uint64_t *n_trust, uint64_t *err, uint64_t *n_err,
-                           uint64_t cap_te, uint32_t *status, bool windows_counted,
-                           hipStream_t s, Profiler *P);
+                           uint64_t cap_te, uint32_t *status, bool counted, hipStream_t s,
+                           Profiler *P);
 hipError_t launch_classify(const FilterArgs &F, const uint64_t *keys, const uint64_t *n_keys,
                            const uint64_t *key_base, uint64_t grid_cap, uint64_t cap,
                            uint32_t tau, uint64_t *trust, uint64_t *n_trust, uint64_t *err,
                            uint64_t *n_err, uint64_t cap_out, uint32_t *status,
                            const Workspace &W, hipStream_t s, Profiler *P, bool wide = false);
-// Marks the distinct flags of positions [0, n_positions) (a multiple of
-// kTile, or the call's end) trustworthy where the k-mer's frequency in the
+// Writes the trustworthy bits (and tile counts) of positions [0, n_positions)
+// (a multiple of kTile, or the call's end): distinct ones where the k-mer's frequency in the
 // countBF is above tau (Query-II), so that launch_distinct splits the list.
 hipError_t launch_classify_flags(const FilterArgs &F, const ReadsArgs &R, const Workspace &W,
                                  uint64_t n_positions, uint32_t tau, hipStream_t s, Profiler *P);

@@ -133,50 +133,137 @@ hipError_t scan_impl(const TIn *in, TOut *out, uint64_t n, const TOut *base, TOu
     return hipGetLastError();
 }
 
-// 64 x 64 tiles through LDS (one pad word per row: no bank conflicts on the
-// column reads); reads and writes are 256-byte rows.  Batch z transposes the
-// rows x cols block at in + z*rows*cols into out + z*cols*rows, its columns
-// cut at total_cols - z*cols (the last block may be narrower).
-__global__ void __launch_bounds__(256) k_transpose_u32(const uint32_t *__restrict__ in,
-                                                       uint32_t *__restrict__ out, uint64_t rows,
-                                                       uint64_t cols, uint64_t total_cols) {
-    __shared__ uint32_t t[64][65];
-    const uint64_t z0 = (uint64_t)blockIdx.z * cols;
-    const uint64_t cz = total_cols - z0 < cols ? total_cols - z0 : cols;
-    const uint32_t *__restrict__ src = in + (uint64_t)blockIdx.z * rows * cols;
-    uint32_t *__restrict__ dst = out + z0 * rows;
-    const uint64_t c0 = (uint64_t)blockIdx.x * 64, r0 = (uint64_t)blockIdx.y * 64;
-    const uint32_t tx = threadIdx.x & 63u, ty = threadIdx.x >> 6;
-    for (uint32_t j = ty; j < 64; j += 4) {
-        const uint64_t r = r0 + j, c = c0 + tx;
-        if (r < rows && c < cz)
-            t[j][tx] = src[r * cols + c];
+// Exclusive sums of the tiles' distinct and trustworthy counts in one pass
+// (decoupled look-back): a workgroup sums its kScanTiles tiles, publishes the
+// sums, adds up what the workgroups before it published (their own sums, or
+// already the sums up to them) and writes its tiles' offsets.  Workgroups
+// number themselves by a ticket, so that every workgroup another one waits
+// for has started, and each publishes its own sums before it waits.
+// Bound by its launch and the chain of workgroups: 13 us for 280 M positions.
+// It replaces two scans of two launches each, the copy of the running count
+// and the launch that moved the counters (97 us there, 31 of 112 us of a call
+// of 30 K bases).
+//
+// state: [0] the ticket, then per workgroup a distinct and a trustworthy word:
+// kind << 62 | value (0 nothing yet, 1 the workgroup's own sum, 2 the sum up
+// to and with it).
+constexpr uint64_t kOwn = 1ull << 62, kUpTo = 2ull << 62, kValue = kOwn - 1;
+
+__device__ __forceinline__ void publish(uint64_t *p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t published(const uint64_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sum of what workgroups 0 .. id - 1 published at state[stride * block]
+// (a wavefront, 64 workgroups at a time, nearest first).
+__device__ uint64_t look_back(const uint64_t *state, uint32_t id) {
+    const uint32_t lane = threadIdx.x & 63u;
+    uint64_t sum = 0;
+    for (int64_t top = (int64_t)id - 1; top >= 0; top -= 64) {
+        const int64_t at = top - (int64_t)lane;
+        uint64_t v = kUpTo;  // before the first workgroup: nothing
+        if (at >= 0)
+            do {
+                v = published(state + 2 * at);
+            } while ((v >> 62) == 0);
+        // the nearest workgroup that knows the sum up to it ends the search
+        const uint64_t ends = __ballot((v >> 62) == 2);
+        const uint32_t end = ends ? (uint32_t)__builtin_ctzll(ends) : 63u;
+        uint64_t x = lane <= end ? v & kValue : 0ull;
+        for (uint32_t d = 32; d >= 1; d >>= 1)
+            x += __shfl_xor(x, d, 64);
+        sum += x;
+        if (ends)
+            break;
+    }
+    return sum;
+}
+
+__global__ void __launch_bounds__(kScanThreads)
+k_tile_scan(const uint32_t *__restrict__ tile_d, const uint32_t *__restrict__ tile_t,
+            uint64_t n_tiles, int split, uint64_t *__restrict__ state,
+            uint64_t *__restrict__ off_d, uint64_t *__restrict__ off_t,
+            uint64_t *__restrict__ totals, TileScan T) {
+    constexpr int kPer = (int)(kScanTiles / kScanThreads);
+    __shared__ uint64_t s_wave[kScanThreads / 64];
+    __shared__ uint64_t s_base[2];
+    __shared__ uint32_t s_id;
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    if (threadIdx.x == 0) {
+        s_id = (uint32_t)atomicAdd((unsigned long long *)state, 1ull);
+        s_base[0] = *T.n_distinct;  // read before this workgroup publishes anything
     }
     __syncthreads();
-    for (uint32_t j = ty; j < 64; j += 4) {
-        const uint64_t c = c0 + j, r = r0 + tx;
-        if (c < cz && r < rows)
-            dst[c * rows + r] = t[tx][j];
+    const uint32_t id = s_id;
+    const uint64_t call_base = s_base[0];
+    __syncthreads();
+    // a tile has at most 1024 of either: a workgroup's sums fit 32 bits each
+    const uint64_t t0 = (uint64_t)id * kScanTiles + threadIdx.x * kPer;
+    uint64_t v[kPer], sum = 0;  // trustworthy << 32 | distinct
+#pragma unroll
+    for (int u = 0; u < kPer; u++) {
+        const uint64_t t = t0 + u;
+        v[u] = t < n_tiles ? (uint64_t)tile_d[t] | (split ? (uint64_t)tile_t[t] << 32 : 0ull) : 0ull;
+        sum += v[u];
+    }
+    uint64_t total;
+    const uint64_t before = wg_exclusive_sum<uint64_t>(sum, s_wave, total);
+    const uint64_t own_d = total & 0xFFFFFFFFull, own_t = total >> 32;
+    uint64_t *mine = state + 1 + 2 * (uint64_t)id;
+    if (wave < 2) {  // wavefront 0: distinct, 1: trustworthy
+        const uint64_t own = wave ? own_t : own_d;
+        if (lane == 0)
+            publish(mine + wave, (id ? kOwn : kUpTo) | own);
+        const uint64_t pre = id ? look_back(state + 1 + wave, id) : 0ull;
+        if (lane == 0) {
+            if (id)
+                publish(mine + wave, kUpTo | (pre + own));
+            s_base[wave] = pre;
+        }
+    }
+    __syncthreads();
+    uint64_t run_d = call_base + s_base[0] + (before & 0xFFFFFFFFull);
+    uint64_t run_t = s_base[1] + (before >> 32);
+#pragma unroll
+    for (int u = 0; u < kPer; u++) {
+        const uint64_t t = t0 + u;
+        if (t < n_tiles) {
+            off_d[t] = run_d;
+            if (split)
+                off_t[t] = run_t;
+        }
+        run_d += v[u] & 0xFFFFFFFFull;
+        run_t += v[u] >> 32;
+    }
+    // the last workgroup knows the totals; every other one has read the
+    // running count by then (it published its sums afterwards)
+    if (threadIdx.x == 0 && id + 1 == gridDim.x) {
+        const uint64_t nd = s_base[0] + own_d, nt = s_base[1] + own_t;
+        totals[3] = call_base;
+        *T.n_distinct = call_base + nd;
+        if (T.n_windows)
+            *T.n_windows += totals[5];
+        bool over = call_base + nd > T.cap_d;
+        if (T.n_trust) {
+            *T.n_trust = nt;
+            *T.n_err = nd - nt;
+            over = over || nt > T.cap_te || nd - nt > T.cap_te;
+        }
+        if (over)
+            atomicOr(T.status, kStatusRange);
     }
 }
 
 }  // namespace
 
-hipError_t transpose_u32(const uint32_t *in, uint32_t *out, uint64_t rows, uint64_t cols,
-                         hipStream_t s) {
-    return transpose_u32_blocks(in, out, rows, cols, cols, s);
-}
-
-hipError_t transpose_u32_blocks(const uint32_t *in, uint32_t *out, uint64_t rows, uint64_t cols,
-                                uint64_t total_cols, hipStream_t s) {
-    if (rows == 0 || cols == 0 || total_cols == 0)
-        return hipSuccess;
-    const uint64_t gx = (cols + 63) / 64, gy = (rows + 63) / 64;
-    const uint64_t gz = (total_cols + cols - 1) / cols;
-    if (gx > 0x7FFFFFFFull || gy > 65535 || gz > 65535)
-        return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_transpose_u32, dim3((unsigned)gx, (unsigned)gy, (unsigned)gz), dim3(256),
-                       0, s, in, out, rows, cols, total_cols);
+hipError_t launch_tile_scan(const Workspace &W, uint64_t n_tiles, bool split, const TileScan &T,
+                            hipStream_t s) {
+    const uint64_t blocks = (n_tiles + kScanTiles - 1) / kScanTiles;
+    hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)blocks), dim3(kScanThreads), 0, s,
+                       (const uint32_t *)W.tile_a, (const uint32_t *)W.tile_b, n_tiles,
+                       split ? 1 : 0, W.off_c, W.off_a, W.off_b, W.totals, T);
     return hipGetLastError();
 }
 

@@ -63,3 +63,36 @@ def test_block_form_against_the_oracle(n, X, Y, alpha, k_h, k):
     for name, a, b in zip(["words", "distinct", "trust", "err"], g[:4], c[:4]):
         assert np.array_equal(np.asarray(a, dtype=np.uint64), np.asarray(b, dtype=np.uint64)), name
     assert g[4] == c[4]
+
+
+# (bases, X, Y, alpha, k_h, k, by_records): the buckets of positions that the
+# first-seen records are sorted by grow from 2^12 to 2^19 positions with the
+# call, and the scan of the tiles' counts takes a second workgroup past 4096
+# tiles; the forced winner passes are the path they are compared with as well
+MARKS = [
+    (2_097_152, 601, 607, 8, 1, 25, False), (2_097_153, 601, 607, 8, 2, 25, False),
+    (4_194_304, 601, 607, 8, 1, 25, False), (4_194_305, 601, 607, 8, 1, 25, True),
+    (16_777_217, 2707, 2711, 8, 1, 31, False), (16_777_217, 2707, 2711, 8, 1, 31, True),
+]
+
+
+@pytest.mark.parametrize("n,X,Y,alpha,k_h,k,by_records", MARKS)
+def test_marks_against_the_oracle(n, X, Y, alpha, k_h, k, by_records, monkeypatch):
+    if by_records:
+        monkeypatch.setenv("KMERCO_WINNER_RECORDS", "1")
+    test_block_form_against_the_oracle(n, X, Y, alpha, k_h, k)
+
+
+def test_the_largest_marks_match_the_winner_passes(monkeypatch):
+    n, k = 67_108_865, 31  # buckets of 2^18 positions
+    print(f"case marks n={n}", flush=True)
+    rs = reads_of(5, n // 16, k)
+    reads = torch.from_numpy(np.tile(rs.reads, 17)[:n].copy()).cuda()
+    offs = torch.tensor([0, n // 3, n // 3 + 40, n], dtype=torch.int64).cuda()
+    out = []
+    for forced in (False, True):
+        if forced:
+            monkeypatch.setenv("KMERCO_WINNER_RECORDS", "1")
+        out.append([np.asarray(a) for a in P.run_kmerco(reads, offs, k, 2, 2707, 2711, 8, 1)[:4]])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
