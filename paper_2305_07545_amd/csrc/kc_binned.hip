@@ -234,7 +234,7 @@ __global__ void __launch_bounds__(kWinThreads) k_win_b(const uint32_t *__restric
 // in LDS, every word of the bucket's tiles written.  clean: the cursor is left
 // zero for the next chunk.  c0 is a multiple of the tile.
 // Bound by its clears and LDS atomics at one or two workgroups per CU: 0.07 ms
-// over 280 M positions; the byte flags cost 0.20 ms to store at random and
+// over 150 M positions; the byte flags cost 0.20 ms to store at random and
 // 0.17 ms to read again in the compaction (0.07 from bits).
 // kLog: the bitmaps' room; the smaller ones leave room for several workgroups
 // per CU where a chunk's buckets are small.

@@ -266,6 +266,42 @@ k_turn_table(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, uint32
                 (uint32_t)t[2 * x][j] | ((uint32_t)t[2 * x + 1][j] << 16);
 }
 
+// Up to 64 runs of entries, one a lane, whose aligned groups of four entries lie
+// end to end over a wavefront's lanes.
+struct LaneRuns {
+    uint32_t s, e;   // the lane's run
+    uint32_t incl;   // groups up to and with it
+    uint32_t n;      // groups of all runs (uniform)
+
+    __device__ __forceinline__ void set(uint32_t start, uint32_t end) {
+        s = start;
+        e = end;
+        incl = wave_inclusive(e > s ? (e - 1u) / 4u + 1u - s / 4u : 0u);
+        n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    }
+    // Group f0 + lane (f0 < n, uniform): its run i (< 64), first entry g, and
+    // which of its entries are the run's (none past the last group).
+    __device__ __forceinline__ uint32_t at(uint32_t f0, uint32_t lane, uint32_t &i,
+                                           uint32_t &g) const {
+        const uint32_t f = f0 + lane, limit = f0 + 64u < n ? f0 + 64u : n;
+        // as many runs as end at or before the group
+        uint32_t j = (uint32_t)__popcll(__ballot(incl <= f0));
+        i = j;
+        for (; j < 63u; j++) {
+            const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)j);
+            if (end >= limit)
+                break;
+            i += f >= end ? 1u : 0u;
+        }
+        i = i < 63u ? i : 63u;
+        const uint32_t rs = (uint32_t)__shfl((int)s, (int)i), re = (uint32_t)__shfl((int)e, (int)i);
+        // groups count back from the run's last
+        g = ((re - 1u) / 4u + 1u - ((uint32_t)__shfl((int)incl, (int)i) - f)) * 4u;
+        const uint32_t lo = g < rs ? rs - g : 0u, hi = re - g < 4u ? re - g : 4u;
+        return f < n ? (1u << hi) - (1u << lo) : 0u;
+    }
+};
+
 // Second level: the entries of bucket b in superblock sb (`super` blocks) ->
 // sorted by region, entries of 5 bytes again (the counter and the position
 // within the superblock).  Their place in the list needs no scan: the
@@ -273,22 +309,30 @@ k_turn_table(const uint16_t *__restrict__ in, uint16_t *__restrict__ out, uint32
 // of its entries as b's runs start at, summed over the blocks.  starts[sb]
 // receives the place of every region's run.
 //
-// A team of 16 lanes takes a block's run, four entries a lane and step.  The
-// runs are read twice (count, then place; the second time from the caches),
-// which needs neither ranks nor entries held in registers.  More entries than
-// the LDS holds (a bucket favoured by the input) are placed straight in the
+// Bound: memory latency behind the runs' short pieces (about 65 entries), so
+// every entry is requested at once (a wavefront takes every 16th block's run,
+// LaneRuns) and stays in registers with the rank that its region's count gives
+// it, two workgroups of 16 wavefronts per CU (1.7 G entries over 122 K regions in
+// 478 buckets: 4.3 ms, 4.0 TB/s; runs read twice by teams of 16 lanes, eight
+// wavefronts each, and stored entry by entry: 7.5 ms).  The sorted entries lie in LDS as
+// the list's 16-byte groups do, and leave in those.  Buckets of more entries
+// than fit (favoured by the input) are read again and placed straight in the
 // list.  Workgroups of one XCD take neighbouring buckets of a superblock at a
 // time, whose runs and table rows share cache lines.
-__global__ void __launch_bounds__(kMergeWG)
+__global__ void __launch_bounds__(kMergeWG, 8)
 k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
         const uint8_t *__restrict__ list_hi, const uint16_t *__restrict__ table,
         uint32_t *__restrict__ out, uint8_t *__restrict__ out_hi, uint32_t *__restrict__ starts) {
-    __shared__ __align__(16) uint32_t s_word[kMergeTile];
-    __shared__ uint8_t s_high[kMergeTile];
-    __shared__ uint32_t s_cursor[1u << kMaxSubLog];
+    // each with room for lanes without an entry behind it
+    constexpr uint32_t kNoPlace = kMergeTile + 4, kNoSub = 1u << kMaxSubLog;
+    __shared__ __align__(16) uint32_t s_word[kNoPlace + 64];
+    __shared__ __align__(16) uint8_t s_high[kNoPlace + 64];
+    __shared__ uint32_t s_cursor[kNoSub + 64];
     __shared__ uint32_t s_wave[kMergeWG / 64];
-    __shared__ uint32_t s_sum;
-    constexpr uint32_t kTeam = 16, kTeams = kMergeWG / kTeam;
+    __shared__ uint32_t s_sum, s_over;
+    constexpr uint32_t kWaves = kMergeWG / 64;
+    constexpr int kGroups = 4;
+    constexpr uint32_t kStep = 64u * kGroups;
     const uint32_t lane = threadIdx.x & 63u, wave = wave_id();
     const uint32_t per = (B.n_bins + 7u) / 8u;  // buckets per XCD
     const uint32_t b = (blockIdx.x & 7u) * per + (blockIdx.x >> 3) % per;
@@ -296,67 +340,84 @@ k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
     if (b >= B.n_bins)
         return;
     const uint32_t n_sub = 1u << B.sub_log;
+    const uint32_t k0 = sb * B.super;
+    const uint32_t n_k = B.n_blocks - k0 < B.super ? B.n_blocks - k0 : B.super;
+    // the lane's run (a superblock has at most 64 runs a wavefront)
+    uint32_t bs = 0, be = 0;
+    const uint32_t kl = lane * kWaves + wave;
+    if (kl < n_k) {
+        const uint16_t *t = table + (uint64_t)(k0 + kl) * B.row + b;
+        bs = t[0];
+        be = t[1];
+    }
     for (uint32_t i = threadIdx.x; i < n_sub; i += kMergeWG)
         s_cursor[i] = 0;
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
         s_sum = 0;
-    __syncthreads();
-    const uint32_t k0 = sb * B.super;
-    const uint32_t k1 = k0 + B.super < B.n_blocks ? k0 + B.super : B.n_blocks;
-    const uint32_t team = threadIdx.x / kTeam, sub = threadIdx.x % kTeam;
-    // visit(word, fifth byte, block - k0) for every entry
-    auto each = [&](auto visit, uint32_t &sum) {
-        uint32_t s = 0, e = 0;
-        auto bounds = [&](uint32_t k) {
-            s = e = 0;
-            if (k < k1) {
-                const uint16_t *t = table + (uint64_t)k * B.row + b;
-                s = t[0];
-                e = t[1];
-            }
-        };
-        bounds(k0 + team);
-        for (uint32_t k = k0 + team; k < k1; k += kTeams) {
-            const uint32_t s0 = s, e0 = e;
-            const uint64_t base = (uint64_t)k * B.cap;
-            sum += sub == 0 ? s0 : 0u;
-            uint32_t g = (s0 & ~3u) + 4u * sub;
-            uint4 x = make_uint4(0u, 0u, 0u, 0u);
-            uint32_t h = 0;
-            if (g < e0) {
-                x = *reinterpret_cast<const uint4 *>(list + base + g);
-                h = *reinterpret_cast<const uint32_t *>(list_hi + base + g);
-            }
-            bounds(k + kTeams);
-            while (g < e0) {
-                const uint32_t gn = g + 4u * kTeam;
-                uint4 y = make_uint4(0u, 0u, 0u, 0u);
-                uint32_t hn = 0;
-                if (gn < e0) {
-                    y = *reinterpret_cast<const uint4 *>(list + base + gn);
-                    hn = *reinterpret_cast<const uint32_t *>(list_hi + base + gn);
+        s_over = 0;
+    }
+    LaneRuns R;
+    R.set(bs, be);
+    uint4 x[kGroups];
+    uint32_t h[kGroups], which[kGroups];  // entries; block, and (from bit 28) those in the run
+    auto load = [&](uint32_t w0) {
+#pragma unroll
+        for (int c = 0; c < kGroups; c++) {
+            which[c] = 0;
+            if (w0 + 64u * c < R.n) {
+                uint32_t i, g;
+                const uint32_t m = R.at(w0 + 64u * c, lane, i, g);
+                const uint32_t k = i * kWaves + wave;
+                if (m) {
+                    const uint32_t at = (k0 + k) * B.cap + g;
+                    x[c] = *reinterpret_cast<const uint4 *>(list + at);
+                    h[c] = *reinterpret_cast<const uint32_t *>(list_hi + at);
+                    which[c] = k | (m << 28);
                 }
-                if (g >= s0)
-                    visit(x.x, h & 0xFFu, k - k0);
-                if (g + 1u >= s0 && g + 1u < e0)
-                    visit(x.y, (h >> 8) & 0xFFu, k - k0);
-                if (g + 2u >= s0 && g + 2u < e0)
-                    visit(x.z, (h >> 16) & 0xFFu, k - k0);
-                if (g + 3u >= s0 && g + 3u < e0)
-                    visit(x.w, h >> 24, k - k0);
-                x = y;
-                h = hn;
-                g = gn;
             }
         }
+    };
+    // visit(entry's number in the step, word, fifth byte, block - k0, is it
+    // the run's); lanes past their run's end visit too, so that a chunk's LDS
+    // operations are in flight together
+    auto each = [&](uint32_t w0, auto visit) {
+#pragma unroll
+        for (int c = 0; c < kGroups; c++)
+            if (w0 + 64u * c < R.n) {
+                const uint32_t m = which[c], k = m & 0xFFFFu;
+                visit(4 * c, x[c].x, h[c] & 0xFFu, k, ((m >> 28) & 1u) != 0);
+                visit(4 * c + 1, x[c].y, (h[c] >> 8) & 0xFFu, k, ((m >> 29) & 1u) != 0);
+                visit(4 * c + 2, x[c].z, (h[c] >> 16) & 0xFFu, k, ((m >> 30) & 1u) != 0);
+                visit(4 * c + 3, x[c].w, h[c] >> 24, k, (m >> 31) != 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
     };
     auto sub_of = [](uint32_t w, uint32_t h) -> uint32_t {
         return (w >> kSubShift) | (h << (32 - kSubShift));
     };
-    uint32_t sum = 0;
-    each([&](uint32_t w, uint32_t h, uint32_t) { atomicAdd(&s_cursor[sub_of(w, h)], 1u); }, sum);
-    if (sum)
+    __syncthreads();
+    uint32_t rank[kGroups * 2];  // of two entries a word: read for buckets of at most kMergeTile
+#pragma unroll
+    for (int j = 0; j < kGroups * 2; j++)
+        rank[j] = 0;
+    for (uint32_t w0 = kStep; w0 < R.n; w0 += kStep) {  // what is not held
+        load(w0);
+        each(w0, [&](int, uint32_t w, uint32_t h, uint32_t, bool in) {
+            if (in)
+                atomicAdd(&s_cursor[sub_of(w, h)], 1u);
+        });
+    }
+    load(0);
+    each(0, [&](int j, uint32_t w, uint32_t h, uint32_t, bool in) {
+        const uint32_t x = atomicAdd(&s_cursor[in ? sub_of(w, h) : kNoSub + lane], 1u);
+        rank[j / 2] = j % 2 ? rank[j / 2] | (x << 16) : x & 0xFFFFu;
+    });
+    const uint32_t sum = wave_inclusive(bs);
+    if (lane == 63) {
         atomicAdd(&s_sum, sum);
+        if (R.n > kStep)
+            s_over = 1;
+    }
     __syncthreads();
     const uint32_t base = k0 * B.cap + s_sum;  // list places are below 2^32
     // counts -> starts: each wavefront a share of the regions
@@ -375,7 +436,7 @@ k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
     __syncthreads();
     uint32_t before = 0, total = 0;
 #pragma unroll
-    for (uint32_t w = 0; w < kMergeWG / 64; w++) {
+    for (uint32_t w = 0; w < kWaves; w++) {
         before += w < wave ? s_wave[w] : 0u;
         total += s_wave[w];
     }
@@ -392,31 +453,56 @@ k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
     }
     if (threadIdx.x == 0 && b + 1u == B.n_bins)
         row[n_regions] = base + total;
+    const bool held = total <= kMergeTile && !s_over;  // uniform
     __syncthreads();
-    const bool staged = total <= kMergeTile;  // uniform
-    uint32_t *__restrict__ o = out + base;
-    uint8_t *__restrict__ oh = out_hi + base;
-    each(
-        [&](uint32_t w, uint32_t h, uint32_t k) {
-            const uint32_t at = atomicAdd(&s_cursor[sub_of(w, h)], 1u);
-            const uint32_t t = (k << B.pos_log) | ((w >> kLocalBits) & ((1u << kBlockLog) - 1u));
-            const uint32_t word = (w & ((1u << kLocalBits) - 1u)) | (t << kLocalBits);
-            const uint8_t high = (uint8_t)(t >> (32 - kLocalBits));
-            if (staged) {
-                s_word[at] = word;
-                s_high[at] = high;
-            } else {
-                o[at] = word;
-                oh[at] = high;
-            }
-        },
-        sum);
-    if (!staged)
+    // an entry of the superblock: its word and fifth byte
+    auto merged = [&](uint32_t w, uint32_t k, uint8_t &high) -> uint32_t {
+        const uint32_t t = (k << B.pos_log) | ((w >> kLocalBits) & ((1u << kBlockLog) - 1u));
+        high = (uint8_t)(t >> (32 - kLocalBits));
+        return (w & ((1u << kLocalBits) - 1u)) | (t << kLocalBits);
+    };
+    if (!held) {
+        uint32_t *__restrict__ o = out + base;
+        uint8_t *__restrict__ oh = out_hi + base;
+        for (uint32_t w0 = 0; w0 < R.n; w0 += kStep) {
+            load(w0);
+            each(w0, [&](int, uint32_t w, uint32_t h, uint32_t k, bool in) {
+                if (in) {
+                    const uint32_t at = atomicAdd(&s_cursor[sub_of(w, h)], 1u);
+                    o[at] = merged(w, k, oh[at]);
+                }
+            });
+        }
         return;
+    }
+    const uint32_t skew = base & 3u;  // the first entry's place in its 16-byte group
+    // the entries as new values: else their regions' numbers stay in registers
+    // beside them across the scan
+#pragma unroll
+    for (int c = 0; c < kGroups; c++)
+        asm volatile(""
+                     : "+v"(x[c].x), "+v"(x[c].y), "+v"(x[c].z), "+v"(x[c].w), "+v"(h[c]),
+                       "+v"(which[c]));
+    each(0, [&](int j, uint32_t w, uint32_t h, uint32_t k, bool in) {
+        const uint32_t r = (rank[j / 2] >> (16 * (j % 2))) & 0xFFFFu;
+        const uint32_t at =
+            in ? s_cursor[sub_of(w, h) & (kNoSub - 1u)] + r + skew : kNoPlace + lane;
+        s_word[at] = merged(w, k, s_high[at]);
+    });
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < total; i += kMergeWG) {
-        o[i] = s_word[i];
-        oh[i] = s_high[i];
+    uint32_t *__restrict__ o = out + (base - skew);
+    uint8_t *__restrict__ oh = out_hi + (base - skew);
+    const uint32_t end = skew + total;
+    for (uint32_t i = 4u * threadIdx.x; i < end; i += 4u * kMergeWG) {
+        if (i >= skew && i + 4u <= end) {
+            *reinterpret_cast<uint4 *>(o + i) = *reinterpret_cast<const uint4 *>(s_word + i);
+            *reinterpret_cast<uint32_t *>(oh + i) = *reinterpret_cast<const uint32_t *>(s_high + i);
+        } else {
+            for (uint32_t j = i < skew ? skew : i; j < i + 4u && j < end; j++) {
+                o[j] = s_word[j];
+                oh[j] = s_high[j];
+            }
+        }
     }
 }
 
@@ -437,7 +523,7 @@ k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
 // kSorted: first-seen occurrences leave as records sorted by bucket of positions
 // (LDS counting sort, runs appended by one atomic per region and bucket), which
 // k_marks turns into bits.  Byte flags stored at random positions (94 G/s)
-// took 0.20 of the 0.51 ms this pass had on 280 M windows over 3914 regions;
+// took 0.20 of the 0.51 ms this pass had on 120 M windows over 3914 regions;
 // it is 0.375 ms now, and the marks 0.09.  Else the records are in room of the
 // region's own (RecordSpace, carried chunks).
 //
@@ -791,7 +877,7 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
         // the next region (of as many as a step takes: nearly always all) are
         // requested before the current region's counters are updated, and the
         // bounds of the one after behind them.
-        constexpr int kGroups = 5;
+        constexpr int kGroups = kSorted ? 4 : 5;  // beside the records, what the registers hold
         constexpr uint32_t kSet = kWaves * 64;
         const uint32_t *__restrict__ starts = (const uint32_t *)table;
         uint32_t bs, be;  // the lane's run: its entries in the list
@@ -802,41 +888,20 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
             bs = t[0];
             be = in ? t[1] : bs;
         };
-        uint32_t rs, re, incl, n;  // runs of a set: entries, groups up to and with the run, all groups
-        auto runs = [&]() {
-            rs = bs;
-            re = be;
-            incl = wave_inclusive(re > rs ? (re - 1u) / 4u + 1u - rs / 4u : 0u);
-            n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-        };
+        LaneRuns R;
         uint4 x[kGroups];
         uint32_t h[kGroups], which[kGroups];  // entries; run, and (from bit 28) those in the run
         auto load = [&](uint32_t w0) {
 #pragma unroll
             for (int c = 0; c < kGroups; c++) {
-                const uint32_t f0 = w0 + 64u * c, f = f0 + lane;
                 which[c] = 0;
-                if (f0 < n) {
-                    // the run: as many as end at or before the lane's group
-                    uint32_t j = (uint32_t)__popcll(__ballot(incl <= f0)), i = j;
-                    const uint32_t limit = f0 + 64u < n ? f0 + 64u : n;
-                    for (; j < 63u; j++) {
-                        const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)j);
-                        if (end >= limit)
-                            break;
-                        i += f >= end ? 1u : 0u;
-                    }
-                    i = i < 63u ? i : 63u;
-                    const uint32_t s = (uint32_t)__shfl((int)rs, (int)i);
-                    const uint32_t e = (uint32_t)__shfl((int)re, (int)i);
-                    const uint32_t last = (uint32_t)__shfl((int)incl, (int)i);
-                    // groups count back from the run's last
-                    const uint32_t g = ((e - 1u) / 4u + 1u - (last - f)) * 4u;
-                    if (f < n) {
+                if (w0 + 64u * c < R.n) {
+                    uint32_t i, g;
+                    const uint32_t m = R.at(w0 + 64u * c, lane, i, g);
+                    if (m) {
                         x[c] = *reinterpret_cast<const uint4 *>(list + g);
                         h[c] = *reinterpret_cast<const uint32_t *>(list_hi + g);
-                        const uint32_t lo = g < s ? s - g : 0u, hi = e - g < 4u ? e - g : 4u;
-                        which[c] = i | (((1u << hi) - (1u << lo)) << 28);
+                        which[c] = i | (m << 28);
                     }
                 }
             }
@@ -860,28 +925,28 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
             }
         };
         bounds(r, 0);
-        runs();
+        R.set(bs, be);
         load(0);
         bounds(r + grid, 0);
         for (; r < P.n_regions; r += grid) {
-            uint32_t mine = re - rs;
+            uint32_t mine = R.e - R.s;
             tally(0);
-            for (uint32_t w0 = 64u * kGroups; w0 < n; w0 += 64u * kGroups) {
+            for (uint32_t w0 = 64u * kGroups; w0 < R.n; w0 += 64u * kGroups) {
                 load(w0);
                 tally(0);
             }
             for (uint32_t b0 = kSet; b0 < B.n_super; b0 += kSet) {
                 bounds(r, b0);
-                runs();
-                mine += re - rs;
-                for (uint32_t w0 = 0; w0 < n; w0 += 64u * kGroups) {
+                R.set(bs, be);
+                mine += R.e - R.s;
+                for (uint32_t w0 = 0; w0 < R.n; w0 += 64u * kGroups) {
                     load(w0);
                     tally(b0);
                 }
                 if (b0 + kSet >= B.n_super)
                     bounds(r + grid, 0);
             }
-            runs();
+            R.set(bs, be);
             load(0);
             bounds(r + 2u * grid, 0);
             finish(
@@ -1081,7 +1146,9 @@ bool block_plan(const BinPlan &plan, uint32_t k_h, uint64_t len, BlockPlan &B) {
     // window is valid
     const uint32_t run = B.cap / B.n_bins + 1u;
     uint32_t m = kMergeTile * 7u / 8u / run;
-    const uint32_t most = (1u << kSuperLog) >> B.pos_log;
+    // ... of at most 64 blocks for each of the second level's wavefronts
+    const uint32_t most = kMergeWG < (1u << kSuperLog) >> B.pos_log ? kMergeWG
+                                                                    : (1u << kSuperLog) >> B.pos_log;
     m = m < 1u ? 1u : (m > most ? most : m);
     B.super = m < B.n_blocks ? m : B.n_blocks;
     B.n_super = (B.n_blocks + B.super - 1u) / B.super;

@@ -23,7 +23,7 @@ constexpr uint32_t kShortRun = 16;
 constexpr uint32_t kMaxSubLog = 11;   // log2(regions per bucket), at most
 constexpr uint32_t kMaxBins = 2048;   // buckets, at most (4M regions)
 constexpr uint32_t kSuperLog = 26;    // log2(positions per superblock), at most
-constexpr int kMergeWG = 512;         // threads of the second level
+constexpr uint32_t kMergeWG = 1024;   // threads of the second level
 constexpr uint32_t kMergeTile = 12288;  // entries it stages in LDS (two workgroups per CU)
 
 // Blocks of one chunk: block b holds the entries of positions [b << pos_log,

@@ -139,7 +139,7 @@ hipError_t scan_impl(const TIn *in, TOut *out, uint64_t n, const TOut *base, TOu
 // already the sums up to them) and writes its tiles' offsets.  Workgroups
 // number themselves by a ticket, so that every workgroup another one waits
 // for has started, and each publishes its own sums before it waits.
-// Bound by its launch and the chain of workgroups: 13 us for 280 M positions.
+// Bound by its launch and the chain of workgroups: 13 us for 150 M positions.
 // It replaces two scans of two launches each, the copy of the running count
 // and the launch that moved the counters (97 us there, 31 of 112 us of a call
 // of 30 K bases).

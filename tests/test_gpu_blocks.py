@@ -96,3 +96,20 @@ def test_the_largest_marks_match_the_winner_passes(monkeypatch):
         out.append([np.asarray(a) for a in P.run_kmerco(reads, offs, k, 2, 2707, 2711, 8, 1)[:4]])
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+# (bases, bases of one repeated k-mer at their start): the second level holds a
+# superblock's entries of a bucket in registers and LDS unless one wavefront's
+# runs, or the bucket, hold more than that
+@pytest.mark.parametrize("n,hot", [(300_000, 1_000), (300_000, 5_000), (600_000, 60_000)])
+def test_uneven_buckets_against_the_oracle(n, hot):
+    print(f"case uneven n={n} hot={hot}", flush=True)
+    rs = reads_of(3, n, 31)
+    rs.reads[:hot] = ord("A")
+    reads = torch.from_numpy(rs.reads).cuda()
+    offs = torch.from_numpy(rs.offsets.view(np.int64)).cuda()
+    g = P.run_kmerco(reads, offs, 31, 2, 3833, 3837, 8, 1)
+    c = oracle.run_kmerco(rs.reads, rs.offsets, 31, 2, 3833, 3837, 8, 1)
+    for name, a, b in zip(["words", "distinct", "trust", "err"], g[:4], c[:4]):
+        assert np.array_equal(np.asarray(a, dtype=np.uint64), np.asarray(b, dtype=np.uint64)), name
+    assert g[4] == c[4]
