@@ -25,10 +25,6 @@ inline bool fast_layout(const FilterArgs &F) {
            F.X * F.Y <= (1ull << 32);
 }
 
-__device__ __forceinline__ uint32_t wave_id() {
-    return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-}
-
 // Forward key of the K-base window at 32-bit position q of codes (q % 16
 // bases into word q / 16; needs words q/16 .. q/16 + 2), as window_key: the
 // 64 bits from bit s = 2 (q % 16) of (w0:w1:w2) on are two funnel shifts

@@ -228,6 +228,70 @@ __global__ void __launch_bounds__(kWinThreads) k_win_b(const uint32_t *__restric
     }
 }
 
+// Dense records (position | mark << 30) -> their buckets of 2^log positions: a
+// tile is sorted in LDS and appended in runs, one atomic per tile and bucket.
+// Bound: its traffic, 12 bytes a record.
+__global__ void __launch_bounds__(1024)
+k_sort_records(const uint32_t *__restrict__ in, const uint32_t *__restrict__ n_in,
+               uint32_t *__restrict__ out, uint64_t room, uint32_t log,
+               uint32_t *__restrict__ cursor) {
+    constexpr int kPer = 8;
+    constexpr uint32_t kRecords = kPer * 1024;
+    static_assert(kMarkBuckets <= 1024, "a bucket a thread");
+    __shared__ uint32_t s_rec[kRecords];
+    __shared__ uint32_t s_count[kMarkBuckets], s_place[kMarkBuckets], s_sum[kMarkBuckets / 64];
+    const uint32_t n = *n_in, lane = threadIdx.x & 63u, wave = wave_id(), tid = threadIdx.x;
+    for (uint32_t q = blockIdx.x * kRecords; q < n; q += gridDim.x * kRecords) {
+        if (tid < kMarkBuckets)
+            s_count[tid] = 0;
+        uint32_t v[kPer], rank[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; u++) {
+            const uint32_t i = q + tid + (uint32_t)u * 1024u;
+            v[u] = i < n ? in[i] : 0u;  // no record is 0: its mark is not
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kPer; u++)
+            rank[u] = v[u] ? atomicAdd(&s_count[(v[u] & 0x3FFFFFFFu) >> log], 1u) : 0u;
+        __syncthreads();
+        uint32_t c = 0, incl = 0;
+        if (tid < kMarkBuckets) {
+            c = s_count[tid];
+            incl = wave_inclusive(c);
+            if (lane == 63)
+                s_sum[wave] = incl;
+        }
+        __syncthreads();
+        if (tid < kMarkBuckets) {
+#pragma unroll
+            for (uint32_t w = 0; w < kMarkBuckets / 64; w++)
+                incl += w < wave ? s_sum[w] : 0u;
+            s_count[tid] = incl - c;
+            const uint32_t place = c ? atomicAdd(&cursor[tid], c) : 0u;
+            s_place[tid] = tid * (uint32_t)room + place - (incl - c);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kPer; u++)
+            if (v[u])
+                s_rec[s_count[(v[u] & 0x3FFFFFFFu) >> log] + rank[u]] = v[u];
+        __syncthreads();
+        const uint32_t m = n - q < kRecords ? n - q : kRecords;
+        for (uint32_t i = tid; i < m; i += 1024u) {
+            const uint32_t x = s_rec[i], t = x & 0x3FFFFFFFu;
+            out[s_place[t >> log] + i] = (t & ((1u << log) - 1u)) | (x >> 30 << log);
+        }
+        __syncthreads();  // the next tile rewrites the sums and records
+    }
+}
+
+hipError_t launch_sort_records(const uint32_t *in, const uint32_t *n, uint32_t *out, uint64_t room,
+                               uint32_t log, uint32_t *cursor, hipStream_t s) {
+    hipLaunchKernelGGL(k_sort_records, dim3(512), dim3(1024), 0, s, in, n, out, room, log, cursor);
+    return hipGetLastError();
+}
+
 // The distinct and trustworthy bits of bucket g = blockIdx.x, the 2^log
 // positions from g << log of the chunk, and their tiles' counts, from the
 // bucket's cursor[g] records (position | mark << log, `room` apart): bitmaps

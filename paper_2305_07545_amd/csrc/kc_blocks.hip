@@ -43,17 +43,6 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, kJ...>, Fn f
     (fn(std::integral_constant<int, kJ>{}), ...);
 }
 
-// Inclusive sum over the wavefront (row shifts, then row broadcasts).
-__device__ __forceinline__ uint32_t wave_inclusive(uint32_t x) {
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
-    return x;
-}
-
 }  // namespace
 
 // Hash every valid window of the block once and write the block's entries
@@ -1032,6 +1021,230 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
     }
 }
 
+// The region pass of sparse regions (a few thousand entries over 16384
+// counters), two-level form: by entry instead of by counter.  Entries are
+// counted as above; then the one that holds its counter's first position
+// updates the cell, which the workgroup has in LDS, cleans the counter, and
+// leaves a record (position | mark << 30) if it found the counter zero.
+//
+// The sweep over all counters cost 5.8 us a region and workgroup however few
+// entries it had; this takes 3.1 with 50 and 4.0 with 1.9 K entries (62 K
+// regions: 1.67 -> 0.97 ms), bound by memory latency behind 32 KB of cells and
+// 20 KB of entries and records a region.  Two barriers a region here, and what the next region needs
+// (cells, entries; bounds of the one after) is requested before its entries
+// are counted.  The records' room is exact, so that they lie dense in `flat`:
+// asked for when a region's records are counted, and taken after the next
+// region's update, the records held in registers until then.
+template <int kCells>
+__global__ void __launch_bounds__(kRegionWG)
+k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict__ list,
+                const uint8_t *__restrict__ list_hi, const uint32_t *__restrict__ starts,
+                int classify, uint32_t tau, uint32_t *__restrict__ cursor,
+                uint32_t *__restrict__ flat) {
+    constexpr uint32_t kWaves = kRegionWG / 64;
+    constexpr int kGroups = 2, kHeld = 4 * kGroups;
+    constexpr uint32_t kStep = 64u * kGroups;
+    __shared__ uint32_t hits[kRegionCounters];
+    __shared__ uint32_t first[kRegionCounters];
+    __shared__ unsigned long long s_cell[kCells * kRegionWG];
+    __shared__ uint32_t s_n, s_base;
+    const uint32_t lane = threadIdx.x & 63u, wave = wave_id(), grid = gridDim.x;
+    const uint32_t shift = P.region_shift, S = 1u << shift;
+    const uint64_t n_words = F.X * F.Y;
+    const uint32_t fm = (uint32_t)F.field_max;  // counters are at most 32 bits wide
+    for (uint32_t i = threadIdx.x; i < (uint32_t)kRegionCounters; i += kRegionWG) {
+        hits[i] = 0;
+        first[i] = kIdle;
+    }
+    if (threadIdx.x == 0)
+        s_n = 0;
+    auto load_cells = [&](uint32_t r, uint64_t(&cell)[kCells]) {
+        const uint64_t wbase = (uint64_t)r << shift;
+#pragma unroll
+        for (int k = 0; k < kCells; k++) {
+            const uint32_t w = threadIdx.x + (uint32_t)k * kRegionWG;
+            cell[k] = r < P.n_regions && wbase + w < n_words ? F.words[wbase + w] : 0ull;
+        }
+    };
+    // Region r's cells into L2, a word of each line: they come from memory
+    // that nothing else has read for long, further off than a region's time.
+    auto touch = [&](uint32_t r) -> uint32_t {
+        const uint64_t w = ((uint64_t)r << shift) + 16u * threadIdx.x;
+        const bool in = threadIdx.x < kCells * 64u && r < P.n_regions && w < n_words;
+        return in ? *reinterpret_cast<const uint32_t *>(F.words + w) : 0u;
+    };
+    uint32_t bs, be;  // the lane's run: its entries in the list
+    auto bounds = [&](uint32_t r) {
+        const uint32_t b = lane * kWaves + wave;
+        const bool in = b < B.n_super && r < P.n_regions;
+        const uint32_t *t = starts + (in ? (uint64_t)b * (P.n_regions + 1u) + r : 0ull);
+        bs = t[0];
+        be = in ? t[1] : bs;
+    };
+    struct Held {
+        uint4 x[kGroups];
+        uint32_t h[kGroups], which[kGroups];  // entries; run, and (from bit 28) those in the run
+    };
+    auto load = [&](const LaneRuns &R, uint32_t w0, Held &H) {
+#pragma unroll
+        for (int c = 0; c < kGroups; c++) {
+            H.which[c] = 0;
+            if (w0 + 64u * c < R.n) {
+                uint32_t i, g;
+                const uint32_t m = R.at(w0 + 64u * c, lane, i, g);
+                if (m) {
+                    H.x[c] = *reinterpret_cast<const uint4 *>(list + g);
+                    H.h[c] = *reinterpret_cast<const uint32_t *>(list_hi + g);
+                    H.which[c] = i | (m << 28);
+                }
+            }
+        }
+    };
+    // visit(number, counter, position) of the entries held
+    auto each = [&](const LaneRuns &R, uint32_t w0, const Held &H, auto visit) {
+#pragma unroll
+        for (int c = 0; c < kGroups; c++)
+            if (w0 + 64u * c < R.n) {
+                const uint32_t m = H.which[c];
+                const uint32_t tb = (((m & 63u) * kWaves + wave) * B.super) << B.pos_log;
+                const uint32_t e[4] = {H.x[c].x, H.x[c].y, H.x[c].z, H.x[c].w};
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+                    if ((m >> (28 + q)) & 1u)
+                        visit(4 * c + q, e[q] & ((1u << kLocalBits) - 1u),
+                              tb + ((e[q] >> kLocalBits) |
+                                    (((H.h[c] >> (8 * q)) & 0xFFu) << (32 - kLocalBits))));
+            }
+    };
+    auto count = [&](int, uint32_t local, uint32_t t) {
+        atomicAdd(&hits[local], 1u);
+        if (t < first[local])
+            atomicMin(&first[local], t);
+    };
+    // the counter's update by its first entry; its record, or 0
+    auto update = [&](uint32_t local, uint32_t t) -> uint32_t {
+        if (first[local] != t)
+            return 0u;
+        // two hash functions may give one position the same counter
+        if (F.k_h > 1u) {
+            if (atomicExch(&first[local], kIdle) != t)
+                return 0u;
+        } else {
+            first[local] = kIdle;
+        }
+        const uint32_t h = hits[local];
+        hits[local] = 0;
+        const uint32_t w = local & (S - 1u), sh = F.alpha * (local >> shift);
+        const uint32_t pf = (uint32_t)(s_cell[w] >> sh) & fm;  // this entry's own field
+        const uint32_t room = fm - pf, inc = h < room ? h : room;
+        if (inc)  // the field grows without carrying out
+            atomicAdd(&s_cell[w], (unsigned long long)inc << sh);
+        return pf ? 0u : t | ((classify && inc > tau ? 3u : 1u) << 30);
+    };
+    uint32_t r = (grid & 7u) == 0 ? (blockIdx.x & 7u) * (grid >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    uint64_t cell[kCells];
+    Held H;
+    LaneRuns R;
+    load_cells(r, cell);
+    bounds(r);
+    R.set(bs, be);
+    load(R, 0, H);
+    bounds(r + grid);
+    uint32_t line = touch(r + grid);
+    uint32_t rec[kHeld], has = 0, at = 0, got = 0;  // records waiting for their room
+    auto store_records = [&](uint32_t base) {
+#pragma unroll
+        for (int j = 0; j < kHeld; j++)
+            if ((has >> j) & 1u)
+                flat[base + at + (uint32_t)__popc(has & ((1u << j) - 1u))] = rec[j];
+    };
+    __syncthreads();  // counters clean
+    for (; r < P.n_regions; r += grid) {
+        LaneRuns Rn;
+        Held Hn;
+        uint64_t celln[kCells];
+        Rn.set(bs, be);
+        load(Rn, 0, Hn);
+        load_cells(r + grid, celln);
+        bounds(r + 2u * grid);
+#pragma unroll
+        for (int k = 0; k < kCells; k++)
+            s_cell[threadIdx.x + (uint32_t)k * kRegionWG] = cell[k];
+        each(R, 0, H, count);
+        for (uint32_t w0 = kStep; w0 < R.n; w0 += kStep) {
+            Held X;
+            load(R, w0, X);
+            each(R, w0, X, count);
+        }
+        __syncthreads();  // counted
+        uint32_t fresh[kHeld], won = 0;
+#pragma unroll
+        for (int j = 0; j < kHeld; j++)
+            fresh[j] = 0;
+        each(R, 0, H, [&](int j, uint32_t local, uint32_t t) {
+            fresh[j] = update(local, t);
+            won |= fresh[j] ? 1u << j : 0u;
+        });
+        for (uint32_t w0 = kStep; w0 < R.n; w0 += kStep) {
+            // more than the registers hold: each record's room by itself
+            load(R, w0, H);
+            each(R, w0, H, [&](int, uint32_t local, uint32_t t) {
+                const uint32_t x = update(local, t);
+                if (x)
+                    flat[atomicAdd(cursor, 1u)] = x;
+            });
+        }
+        const uint32_t mine = (uint32_t)__popc(won), incl = wave_inclusive(mine);
+        uint32_t place = 0;
+        if (lane == 63 && incl)
+            place = atomicAdd(&s_n, incl);
+        place = (uint32_t)__builtin_amdgcn_readlane((int)place, 63) + incl - mine;
+        // every load in flight is taken in before the first store
+#pragma unroll
+        for (int c = 0; c < kGroups; c++)
+            asm volatile(""
+                         : "+v"(Hn.x[c].x), "+v"(Hn.x[c].y), "+v"(Hn.x[c].z), "+v"(Hn.x[c].w),
+                           "+v"(Hn.h[c]));
+#pragma unroll
+        for (int k = 0; k < kCells; k++)
+            asm volatile("" : "+v"(celln[k]));
+        asm volatile("" : "+v"(bs), "+v"(be), "+v"(line));
+        line = touch(r + 2u * grid);
+        if (threadIdx.x == 0)
+            s_base = got;
+        __syncthreads();  // updated, counters clean
+        const uint32_t base = s_base;
+        got = 0;
+        if (threadIdx.x == 0) {
+            if (s_n)
+                got = atomicAdd(cursor, s_n);
+            s_n = 0;
+        }
+        const uint64_t wbase = (uint64_t)r << shift;
+#pragma unroll
+        for (int k = 0; k < kCells; k++) {
+            const uint32_t w = threadIdx.x + (uint32_t)k * kRegionWG;
+            const uint64_t next = s_cell[w];
+            if (next != cell[k])
+                F.words[wbase + w] = next;
+            cell[k] = celln[k];
+        }
+        store_records(base);
+#pragma unroll
+        for (int j = 0; j < kHeld; j++)
+            rec[j] = fresh[j];
+        has = won;
+        at = place;
+        R = Rn;
+        H = Hn;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_base = got;
+    __syncthreads();
+    store_records(s_base);
+}
+
 namespace {
 
 using SortKernel = void (*)(FilterArgs, ReadsArgs, uint64_t, uint64_t, BlockPlan, uint32_t,
@@ -1239,11 +1452,21 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
     while ((len + (1ull << rec.log) - 1) >> rec.log > kMarkBuckets || rec.log < 12)
         rec.log++;
     rec.n_buckets = (uint32_t)((len + (1ull << rec.log) - 1) >> rec.log);
-    if (records || carry.mode == Carry::kOut) {
+    // Sparse regions are worked by entry: below kSparseEntries a region on
+    // average, for the forms whose cells fit beside the counters in LDS
+    const bool sparse = B.two && !records && carry.mode == Carry::kNone &&
+                        plan.region_counters == (uint32_t)kRegionCounters &&
+                        (plan.region_shift == 10 || plan.region_shift == 11) &&
+                        B.n_super <= kRegionWG && 8 * len * F.k_h <= room &&
+                        len * F.k_h <= kSparseEntries * plan.n_regions;
+    if (records || carry.mode == Carry::kOut || sparse) {
         rec.cursor = W.n_entries + 3;
         if ((e = fill_u32(rec.cursor, 1, 0u, s)) != hipSuccess)
             return e;
-        if (records) {
+        if (sparse) {
+            rec.room = (uint64_t)F.k_h << rec.log;
+            rec.word = (uint32_t *)W.bucketed;  // the sorted records; the dense ones after them
+        } else if (records) {
             uint32_t *index = B.two ? W.matrix_t : W.coarse;
             if (2ull * plan.n_regions > (B.two ? W.matrix_cap : W.coarse_cap))
                 return hipErrorInvalidValue;
@@ -1262,12 +1485,33 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
                              : (const void *)(B.turned ? turned : table);
     if (P)
         P->begin(kPhRegion, s);
+    const uint32_t grid = region_grid(plan.n_regions, plan.region_counters);
+    if (sparse) {
+        hipLaunchKernelGGL(plan.region_shift == 10 ? k_region_sparse<1> : k_region_sparse<2>,
+                           dim3(grid), dim3(kRegionWG), 0, s, F, plan, B, (const uint32_t *)merged,
+                           (const uint8_t *)merged_hi, (const uint32_t *)starts, classify ? 1 : 0,
+                           tau, rec.cursor, rec.word + len * F.k_h);
+        if (P)
+            P->end(s);
+        if ((e = hipGetLastError()) != hipSuccess)
+            return e;
+        if (P)
+            P->begin(kPhWinners, s);
+        e = launch_sort_records(rec.word + len * F.k_h, rec.cursor, rec.word, rec.room, rec.log,
+                                mark_cursors(W), s);
+        if (e == hipSuccess)
+            e = launch_marks(rec.word, rec.room, rec.log, mark_cursors(W), true, c0, len, R.n_bases,
+                             W, s);
+        if (P)
+            P->end(s);
+        return e;
+    }
     const bool small = plan.region_counters == (uint32_t)kSmallRegionCounters;
     hipLaunchKernelGGL(rec.sorted ? (small ? runs_kernel<kSmallRegionCounters, true>(plan, B)
                                            : runs_kernel<kRegionCounters, true>(plan, B))
                                   : (small ? runs_kernel<kSmallRegionCounters, false>(plan, B)
                                            : runs_kernel<kRegionCounters, false>(plan, B)),
-                       dim3(region_grid(plan.n_regions, plan.region_counters)), dim3(kRegionWG), 0,
+                       dim3(grid), dim3(kRegionWG), 0,
                        s, F, c0, plan, B, (const uint32_t *)(B.two ? merged : list),
                        (const uint8_t *)merged_hi, runs, classify ? 1 : 0, tau, rec, carry);
     if (P)

@@ -24,6 +24,12 @@ constexpr uint32_t kMaxSubLog = 11;   // log2(regions per bucket), at most
 constexpr uint32_t kMaxBins = 2048;   // buckets, at most (4M regions)
 constexpr uint32_t kSuperLog = 26;    // log2(positions per superblock), at most
 constexpr uint32_t kMergeWG = 1024;   // threads of the second level
+// Regions of up to this many entries on average are worked by entry, which the
+// pass holds in registers up to there: 150 M bases over 62 K regions (1.9 K
+// entries each) 1.77 -> 1.08 ms with the records, 100 M over 16 K (5 K) 0.59 ->
+// 0.52; 200 M over 16 K (10 K) 0.73 -> 0.68, but more entries than are held are
+// read twice.
+constexpr uint64_t kSparseEntries = 8192;
 constexpr uint32_t kMergeTile = 12288;  // entries it stages in LDS (two workgroups per CU)
 
 // Blocks of one chunk: block b holds the entries of positions [b << pos_log,
@@ -62,6 +68,10 @@ hipError_t launch_record_winners(uint32_t n_regions, const uint32_t *off, const 
                                  const uint32_t *word, const uint16_t *half, uint64_t c0,
                                  uint64_t len, uint64_t n_bases, const Workspace &W, hipStream_t s,
                                  Profiler *P);
+// *n records (position | mark << 30) at in, to buckets of 2^log positions:
+// appended to out + g * room as position | mark << log, cursor[g] moved.
+hipError_t launch_sort_records(const uint32_t *in, const uint32_t *n, uint32_t *out, uint64_t room,
+                               uint32_t log, uint32_t *cursor, hipStream_t s);
 // The distinct and trustworthy bits and tile counts of chunk [c0, c0 + len)
 // from records sorted by bucket of 2^log positions (bucket g's cursor[g]
 // records at in + g * room: position | mark << log).

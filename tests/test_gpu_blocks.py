@@ -113,3 +113,16 @@ def test_uneven_buckets_against_the_oracle(n, hot):
     for name, a, b in zip(["words", "distinct", "trust", "err"], g[:4], c[:4]):
         assert np.array_equal(np.asarray(a, dtype=np.uint64), np.asarray(b, dtype=np.uint64)), name
     assert g[4] == c[4]
+
+
+# (bases, X, Y, alpha, k_h, k): regions of few entries, which are worked by
+# entry: one and two cells a thread, positions that hit a counter twice,
+# saturating counters, a last region past the countBF's end
+@pytest.mark.parametrize("n,X,Y,alpha,k_h,k", [
+    (400_000, 3833, 3837, 8, 1, 55), (400_000, 3833, 3837, 8, 3, 25),
+    (400_000, 3833, 3837, 5, 2, 31), (400_000, 3833, 3837, 4, 8, 31),
+    (400_000, 3833, 3837, 16, 1, 31),  # its cells do not fit: by counter
+    (30_000, 5779, 5813, 8, 1, 31),    # 16404 regions: partitioned plan
+])
+def test_sparse_regions_against_the_oracle(n, X, Y, alpha, k_h, k):
+    test_block_form_against_the_oracle(n, X, Y, alpha, k_h, k)
