@@ -163,30 +163,35 @@ __global__ void __launch_bounds__(256) kb_transpose(const SetDesc *__restrict__ 
 // region in LDS per batch of kWriteStage entries.  The large batch keeps the
 // runs written per region long even for sets of 2048 regions (runs of the
 // smaller level-1 batches of the single-set path would be 2 entries there).
+// One workgroup fits a CU, so it has 16 wavefronts: 256 sets of 0.2 M bases
+// 0.231 -> 0.194 ms against eight; 64 sets of 3 M bases 0.99 -> 0.97, bound
+// there by the short runs' partial lines.
 constexpr int kWriteStage = 16384;  // 128 KiB of staged entries
 constexpr uint32_t kWriteStageLog = 14;
 static_assert(kWriteStage == (1 << kWriteStageLog), "stage size");
 
-__global__ void __launch_bounds__(kBinWG) kb_bin_write(const SetDesc *__restrict__ sets,
-                                                       const uint32_t *__restrict__ item_set,
-                                                       uint64_t tile,
-                                                       const uint32_t *__restrict__ slots,
-                                                       const uint32_t *__restrict__ offsets,
-                                                       uint64_t *__restrict__ entries,
-                                                       uint64_t cap) {
-    constexpr int kPer = kWriteStage / kBinWG;
-    constexpr int kScanPer = kBatchMaxRegions / kBinWG;
+constexpr uint32_t kWriteWG = 1024;
+
+__global__ void __launch_bounds__(kWriteWG) kb_bin_write(const SetDesc *__restrict__ sets,
+                                                         const uint32_t *__restrict__ item_set,
+                                                         uint64_t tile,
+                                                         const uint32_t *__restrict__ slots,
+                                                         const uint32_t *__restrict__ offsets,
+                                                         uint64_t *__restrict__ entries,
+                                                         uint64_t cap) {
+    constexpr int kPer = kWriteStage / kWriteWG;
+    constexpr int kScanPer = kBatchMaxRegions / kWriteWG;
     __shared__ uint64_t s_stage[kWriteStage];
     __shared__ uint32_t s_cnt[kBatchMaxRegions];
     __shared__ uint16_t s_start[kBatchMaxRegions];  // < kWriteStage
     __shared__ uint32_t s_cursor[kBatchMaxRegions];
-    __shared__ uint32_t s_wave[kBinWG / 64];
+    __shared__ uint32_t s_wave[kWriteWG / 64];
     __shared__ uint32_t s_total;
     const Item it = item_of(sets, item_set, blockIdx.x, tile);
     const SetDesc &S = sets[it.s];
     const uint32_t nr = S.n_regions;
     const uint32_t k_h = S.F.k_h;
-    for (uint32_t r = threadIdx.x; r < kBatchMaxRegions; r += kBinWG) {
+    for (uint32_t r = threadIdx.x; r < kBatchMaxRegions; r += kWriteWG) {
         s_cursor[r] = r < nr ? offsets[S.mat_base + (uint64_t)r * S.G + it.j] : 0u;
         s_cnt[r] = 0;
     }
@@ -209,8 +214,8 @@ __global__ void __launch_bounds__(kBinWG) kb_bin_write(const SetDesc *__restrict
     // pos_of: the batch index of a thread's entry u.
     static_assert(kPer % 4 == 0, "whole 16-byte loads per thread");
     auto pos_of = [&](bool vec, int u) -> uint32_t {
-        return vec ? (uint32_t)(u >> 2) * (4u * kBinWG) + 4u * threadIdx.x + (uint32_t)(u & 3)
-                   : threadIdx.x + (uint32_t)u * kBinWG;
+        return vec ? (uint32_t)(u >> 2) * (4u * kWriteWG) + 4u * threadIdx.x + (uint32_t)(u & 3)
+                   : threadIdx.x + (uint32_t)u * kWriteWG;
     };
     for (uint32_t q0 = q_lo; q0 < q_hi; q0 += batch) {
         const uint32_t nq = (q_hi - q0 < batch ? q_hi - q0 : batch);
@@ -220,7 +225,7 @@ __global__ void __launch_bounds__(kBinWG) kb_bin_write(const SetDesc *__restrict
             const uint4 *p4 = reinterpret_cast<const uint4 *>(sl + q0);
 #pragma unroll
             for (int v = 0; v < kPer / 4; v++) {
-                const uint4 x = p4[(uint32_t)v * kBinWG + threadIdx.x];
+                const uint4 x = p4[(uint32_t)v * kWriteWG + threadIdx.x];
                 id[4 * v] = x.x;
                 id[4 * v + 1] = x.y;
                 id[4 * v + 2] = x.z;
@@ -229,7 +234,7 @@ __global__ void __launch_bounds__(kBinWG) kb_bin_write(const SetDesc *__restrict
         } else {
 #pragma unroll
             for (int u = 0; u < kPer; u++) {
-                const uint32_t i = threadIdx.x + (uint32_t)u * kBinWG;
+                const uint32_t i = threadIdx.x + (uint32_t)u * kWriteWG;
                 const uint32_t a = i >> batch_log;
                 const uint32_t qq = i & (batch - 1u);
                 id[u] = (a < k_h && qq < nq) ? sl[a * nb + q0 + qq] : kNoSlot;
@@ -266,7 +271,7 @@ __global__ void __launch_bounds__(kBinWG) kb_bin_write(const SetDesc *__restrict
                 s_start[threadIdx.x * kScanPer + u] = (uint16_t)run;
                 run += v[u];
             }
-            if (threadIdx.x == kBinWG - 1)
+            if (threadIdx.x == kWriteWG - 1)
                 s_total = run;  // staged entries of this batch (<= kWriteStage)
         }
         __syncthreads();
@@ -281,7 +286,7 @@ __global__ void __launch_bounds__(kBinWG) kb_bin_write(const SetDesc *__restrict
             }
         __syncthreads();
         const uint32_t n_stage = s_total;
-        for (uint32_t j = threadIdx.x; j < n_stage; j += kBinWG) {
+        for (uint32_t j = threadIdx.x; j < n_stage; j += kWriteWG) {
             const uint64_t e = s_stage[j];
             const uint32_t r = (uint32_t)e >> kLocalBits;
             const uint64_t dst = (uint64_t)s_cursor[r] + (j - s_start[r]);
@@ -289,7 +294,7 @@ __global__ void __launch_bounds__(kBinWG) kb_bin_write(const SetDesc *__restrict
                 entries[dst] = e;
         }
         __syncthreads();
-        for (uint32_t r = threadIdx.x; r < kBatchMaxRegions; r += kBinWG) {
+        for (uint32_t r = threadIdx.x; r < kBatchMaxRegions; r += kWriteWG) {
             s_cursor[r] += s_cnt[r];
             s_cnt[r] = 0;
         }
@@ -298,6 +303,9 @@ __global__ void __launch_bounds__(kBinWG) kb_bin_write(const SetDesc *__restrict
 }
 
 // One workgroup per region of every set (as the single-set region kernel).
+// Bound: latency, one 128 KiB workgroup per CU, so that the region's first
+// entries and its cells are requested before the counters are cleared (256
+// sets of 0.2 M bases: 0.228 -> 0.201 ms; 64 sets of 3 M: 0.956 -> 0.940).
 __global__ void __launch_bounds__(kRegionWG) kb_region(const SetDesc *__restrict__ sets,
                                                        uint32_t n_sets,
                                                        const uint32_t *__restrict__ region_set,
@@ -306,6 +314,7 @@ __global__ void __launch_bounds__(kRegionWG) kb_region(const SetDesc *__restrict
                                                        const uint64_t *__restrict__ entries,
                                                        uint64_t cap,
                                                        uint8_t *__restrict__ flags) {
+    constexpr int kHold = 2;  // cells a thread holds (others are read when updated)
     __shared__ uint32_t hits[kRegionCounters];
     __shared__ uint32_t first[kRegionCounters];
     const uint32_t s = region_set[blockIdx.x];
@@ -314,11 +323,6 @@ __global__ void __launch_bounds__(kRegionWG) kb_region(const SetDesc *__restrict
     const uint32_t r = blockIdx.x - S.region_base;
     const uint32_t shift = S.region_shift;
     const uint32_t Sw = 1u << shift;
-    for (uint32_t i = threadIdx.x; i < Sw * F.eta; i += kRegionWG) {
-        hits[i] = 0;
-        first[i] = kIdle;
-    }
-    __syncthreads();
     const uint64_t e0 = offsets[S.mat_base + (uint64_t)r * S.G];
     uint64_t e1;
     if (r + 1 < S.n_regions)
@@ -327,50 +331,70 @@ __global__ void __launch_bounds__(kRegionWG) kb_region(const SetDesc *__restrict
         e1 = s + 1 < n_sets ? offsets[sets[s + 1].mat_base] : *n_entries;
     if (e1 > cap)
         e1 = cap;
+    const uint64_t wbase = (uint64_t)r << shift;
+    const uint64_t n_words = F.X * F.Y;
+    const uint32_t nw = wbase + Sw <= n_words ? Sw : (uint32_t)(n_words - wbase);
     constexpr int kUnroll = 8;
-    for (uint64_t e = e0 + threadIdx.x; e < e1; e += (uint64_t)kUnroll * kRegionWG) {
-        uint64_t v[kUnroll];
+    uint64_t v[kUnroll];
+    auto load = [&](uint64_t e) {
 #pragma unroll
         for (int u = 0; u < kUnroll; u++) {
             const uint64_t x = e + (uint64_t)u * kRegionWG;
             v[u] = x < e1 ? entries[x] : ~0ull;
         }
+    };
+    load(e0 + threadIdx.x);
+    uint64_t cell[kHold];
+#pragma unroll
+    for (int k = 0; k < kHold; k++) {
+        const uint32_t w = threadIdx.x + (uint32_t)k * kRegionWG;
+        cell[k] = w < nw ? F.words[wbase + w] : 0ull;
+    }
+    for (uint32_t i = threadIdx.x; i < Sw * F.eta; i += kRegionWG) {
+        hits[i] = 0;
+        first[i] = kIdle;
+    }
+    __syncthreads();
+    for (uint64_t e = e0 + threadIdx.x; e < e1; e += (uint64_t)kUnroll * kRegionWG) {
+        uint64_t x[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; u++)
+            x[u] = v[u];
+        load(e + (uint64_t)kUnroll * kRegionWG);
 #pragma unroll
         for (int u = 0; u < kUnroll; u++) {
-            if (v[u] == ~0ull)
+            if (x[u] == ~0ull)
                 continue;
-            const uint32_t local = (uint32_t)v[u] & (kRegionCounters - 1);
+            const uint32_t local = (uint32_t)x[u] & (kRegionCounters - 1);
             atomicAdd(&hits[local], 1u);
-            atomicMin(&first[local], (uint32_t)(v[u] >> 32));
+            atomicMin(&first[local], (uint32_t)(x[u] >> 32));
         }
     }
     __syncthreads();
-    const uint64_t wbase = (uint64_t)r << shift;
-    const uint64_t n_words = F.X * F.Y;
-    const uint32_t nw = wbase + Sw <= n_words ? Sw : (uint32_t)(n_words - wbase);
-    for (uint32_t w = threadIdx.x; w < nw; w += kRegionWG) {
-        const uint64_t pre = F.words[wbase + w];
+    const uint32_t fm = (uint32_t)F.field_max;  // counters are at most 32 bits wide
+    auto update = [&](uint32_t w, uint64_t pre) {
         uint64_t next = pre;
         for (uint32_t l = 0; l < F.eta; l++) {
             const uint32_t idx = (l << shift) | w;
-            const uint64_t h = hits[idx];
+            const uint32_t h = hits[idx];
             if (h == 0)
                 continue;
             const uint32_t sh = F.alpha * l;
-            const uint64_t pf = (pre >> sh) & F.field_max;
-            const uint64_t room = F.field_max - pf;
-            const uint64_t nf = pf + (h < room ? h : room);
-            next = (next & ~(F.field_max << sh)) | (nf << sh);
-            if (pf == 0) {
-                uint8_t flag = 1;
-                if (S.fused && nf > (uint64_t)S.tau)
-                    flag = 3;
-                flags[S.base + first[idx]] = flag;
-            }
+            const uint32_t pf = (uint32_t)(pre >> sh) & fm;
+            const uint32_t room = fm - pf, inc = h < room ? h : room;
+            next += (uint64_t)inc << sh;  // the field grows without carrying out
+            if (pf == 0)
+                flags[S.base + first[idx]] = S.fused && inc > S.tau ? 3 : 1;
         }
         if (next != pre)
             F.words[wbase + w] = next;
-    }
+    };
+#pragma unroll
+    for (int k = 0; k < kHold; k++)
+        if (threadIdx.x + (uint32_t)k * kRegionWG < nw)
+            update(threadIdx.x + (uint32_t)k * kRegionWG, cell[k]);
+    for (uint32_t w = threadIdx.x + kHold * kRegionWG; w < nw; w += kRegionWG)
+        update(w, F.words[wbase + w]);
 }
 
 // Per tile of every set, one wavefront per tile: the set's ordered outputs
@@ -525,7 +549,7 @@ hipError_t launch_batch_bins(const BatchPlan &bp, const BatchBuffers &Bf, const 
         return e;
     if (P)
         P->begin(kPhBinBucket, s);
-    hipLaunchKernelGGL(kb_bin_write, dim3(bp.n_items), dim3(kBinWG), 0, s, Bf.sets, Bf.item_set,
+    hipLaunchKernelGGL(kb_bin_write, dim3(bp.n_items), dim3(kWriteWG), 0, s, Bf.sets, Bf.item_set,
                        bp.tile, (const uint32_t *)Bf.slots, (const uint32_t *)Bf.matrix,
                        Bf.entries, bp.entries_cap);
     if (P)
