@@ -345,7 +345,7 @@ typedef enum {
     KC_PHASE_BIN_REGION = 15,     /* binned path: runs of the blocks arranged by region */
     KC_PHASE_BIN_PART = 16,       /* partitioned path: hashing, entries sorted by bucket */
     KC_PHASE_PART_COUNT = 17,     /* partitioned path: buckets counted and sorted by region */
-    KC_PHASE_VALID = 18,          /* binned paths: valid-window bitmap of the call's k */
+    KC_PHASE_VALID = 18,          /* batched form: valid-window bitmap of each set's k */
     KC_PHASE_WINNERS = 19,        /* binned paths, chunks beyond 2^28 positions: first-seen
                                      records -> flag bytes */
     KC_PHASE_COUNT = 20

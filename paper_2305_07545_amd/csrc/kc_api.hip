@@ -484,7 +484,7 @@ void init_filter(kc_filter *f, const kc_layout *layout) {
 
 // Everything of an insert after its reads are ingested into W's
 // per-position buffers (codes, bitmaps and flag bytes of positions
-// 0..n_bases): the valid-window bitmap, the chunks, the distinct output and
+// 0..n_bases) and the call's cleared counters: the chunks, the distinct output and
 // the split; W's other buffers are prepared for n_bases.  Kernels only.
 kc_status insert_core(kc_filter *f, const kc::Workspace &W, uint64_t n_bases, uint32_t k,
                       bool binned, const kc::BinPlan &plan, uint64_t bchunk, uint64_t *distinct,
@@ -493,10 +493,6 @@ kc_status insert_core(kc_filter *f, const kc::Workspace &W, uint64_t n_bases, ui
                       uint64_t cap_te, hipStream_t s, kc::Profiler *P) {
     const bool split = trust != nullptr;
     hipError_t e = hipSuccess;
-    // either also clears the call's counters
-    e = binned ? kc::launch_valid_windows(n_bases, k, W, s, P) : kc::launch_clear_call(n_bases, W, s);
-    if (e != hipSuccess)
-        return KC_EDEVICE;
     kc::ReadsArgs R{W.codes, W.inv, W.rs, n_bases, k, W.valid};
     const uint64_t chunk = binned ? bchunk : f->chunk;
     // The split is taken from marks on the distinct flags: the region pass
@@ -580,7 +576,8 @@ kc_status insert_impl(kc_filter *f, const uint8_t *reads, const uint64_t *offset
         return st;
     }
     f->k = k;  // every check passed: the filter now holds k-mers of this length
-    if (kc::launch_ingest(reads, n_bases, offsets, n_reads, *f->W, false, s, &f->prof) != hipSuccess)
+    if (kc::launch_ingest(reads, n_bases, offsets, n_reads, *f->W, false,
+                          kc::call_state(*f->W, n_bases), s, &f->prof) != hipSuccess)
         return KC_EDEVICE;
     return insert_core(f, *f->W, n_bases, k, binned, plan, bchunk, distinct, cap_d, n_distinct,
                        n_windows, tau, trust, n_trust, err, n_err, cap_te, s, &f->prof);
@@ -656,6 +653,8 @@ kc_status insert_range(kc_filter *f, const kc::Workspace &pos, uint64_t base, ui
     V.rs = pos.rs + base / 32;
     V.valid = pos.valid + base / 32;
     V.flags8 = pos.flags8 + base;
+    if (kc::launch_clear_call(n_bases, V, s) != hipSuccess)
+        return KC_EDEVICE;
     return insert_core(f, V, n_bases, k, binned, plan, bchunk, distinct, cap_d, n_distinct,
                        n_windows, tau, trust, n_trust, err, n_err, cap_te, s, P);
 }

@@ -320,8 +320,8 @@ kc_status launch_all(kc_batch *b, const kc::BatchPlan &P, const kc_set *sets, ui
                      const uint8_t *reads, const uint64_t *offsets, uint64_t n_reads,
                      uint64_t n_bases, bool reset, bool replayed, hipStream_t s,
                      kc::Profiler *prof) {
-    hipError_t e = kc::launch_ingest(reads, n_bases, offsets, n_reads, b->W, P.n_sets > 0, s,
-                                     prof);
+    hipError_t e = kc::launch_ingest(reads, n_bases, offsets, n_reads, b->W, P.n_sets > 0,
+                                     kc::CallState{}, s, prof);
     if (e != hipSuccess)
         return KC_EDEVICE;
     kc_status st = KC_OK;
@@ -472,7 +472,7 @@ kc_status autotune(kc_batch *b, const kc_set *sets, uint32_t n_sets, const uint8
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
         return KC_EDEVICE;
     kc_status st = KC_OK;
-    if (kc::launch_ingest(reads, n_bases, offsets, n_reads, b->W, false, s, nullptr) !=
+    if (kc::launch_ingest(reads, n_bases, offsets, n_reads, b->W, false, kc::CallState{}, s, nullptr) !=
         hipSuccess)
         st = KC_EDEVICE;
     float best = 1e30f;
@@ -678,7 +678,7 @@ kc_status kc_batch_insert(kc_batch *b, const kc_set *sets, uint32_t n_sets,
             (st = autotune(b, sets, n_sets, reads_dev, offsets_dev, n_reads, n_bases, s)) != KC_OK)
             return st;
         if (reset && !b->big.empty()) {
-            if (kc::launch_ingest(reads_dev, n_bases, offsets_dev, n_reads, b->W, false, s,
+            if (kc::launch_ingest(reads_dev, n_bases, offsets_dev, n_reads, b->W, false, kc::CallState{}, s,
                                   nullptr) != hipSuccess)
                 return KC_EDEVICE;
             if ((st = tune_side(b, sets, s)) != KC_OK)

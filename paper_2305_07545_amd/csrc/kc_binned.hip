@@ -535,8 +535,8 @@ bool bin_plan(const FilterArgs &F, uint64_t chunk_positions, BinPlan &B, uint32_
 hipError_t launch_binned_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t c0, uint64_t c1,
                                const BinPlan &plan, const Workspace &W, bool classify,
                                uint32_t tau, const Carry &carry, hipStream_t s, Profiler *P) {
-    if ((c0 & 63u) || !R.valid)
-        return hipErrorInvalidValue;  // waves read 64 bits of the valid-window bitmap
+    if (c0 & 63u)
+        return hipErrorInvalidValue;  // chunks start at whole words of the masks
     if (carry.mode != Carry::kNone && (!carry_fits(plan) || carry.stride != plan.n_regions))
         return hipErrorInvalidValue;  // the region pass stages the cells it classifies against
     // entries (positions x hash functions) are counted in 32 bits

@@ -60,7 +60,8 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, kJ...>, Fn f
 // alone and writing slot ids took 0.42.
 template <int kWG, int kEpt, int kKh, bool kFast, bool kWide, bool kTwo>
 __global__ void __launch_bounds__(kWG, 4)
-k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t c0, uint64_t c1, BlockPlan B, uint32_t shift,
+k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t n_words, uint64_t c0, uint64_t c1, BlockPlan B,
+            uint32_t shift,
             uint32_t *__restrict__ list, uint8_t *__restrict__ list_hi,
             uint16_t *__restrict__ table, unsigned long long *__restrict__ n_valid) {
     constexpr int kSteps = kEpt / kKh;
@@ -84,8 +85,11 @@ k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t c0, uint64_t c1, BlockPlan B, ui
         static_assert(kWords <= 64 && kWords % 2 == 0, "a word per lane, two per step");
         const uint32_t w0 = wave * kWords;
         uint32_t v = 0;
+        // validity of the words' windows, from the masks here (25 us over 150 M
+        // positions): a bitmap of its own took a launch and 28 us there, 5 us
+        // in calls of 1 M bases
         if (lane < kWords && p0 + 32u * (w0 + lane) < c1)
-            v = R.valid[(p0 >> 5) + w0 + lane];
+            v = valid_word(R.inv, R.rs, n_words, (p0 >> 5) + w0 + lane, R.k, R.n_bases);
         const uint32_t incl = wave_inclusive((uint32_t)__popc(v));
         if (lane == 63)
             s_wave[wave] = incl;
@@ -1247,7 +1251,7 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
 
 namespace {
 
-using SortKernel = void (*)(FilterArgs, ReadsArgs, uint64_t, uint64_t, BlockPlan, uint32_t,
+using SortKernel = void (*)(FilterArgs, ReadsArgs, uint64_t, uint64_t, uint64_t, BlockPlan, uint32_t,
                             uint32_t *, uint8_t *, uint16_t *, unsigned long long *);
 using RunsKernel = void (*)(FilterArgs, uint64_t, BinPlan, BlockPlan, const uint32_t *,
                             const uint8_t *, const void *, int, uint32_t, RecordSpace, Carry);
@@ -1424,7 +1428,8 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
     if (P)
         P->begin(plan.n_parts ? kPhBinPart : kPhBinCount, s);
     hipLaunchKernelGGL(sort_kernel(F, R.k, B), dim3(B.n_blocks), dim3(B.wg),
-                       B.n_bins * sizeof(uint32_t), s, F, R, c0, c1, B, plan.region_shift, list,
+                       B.n_bins * sizeof(uint32_t), s, F, R, mask_words(R.n_bases), c0, c1, B,
+                       plan.region_shift, list,
                        list_hi, table, (unsigned long long *)(W.totals + 5));
     if (P)
         P->end(s);

@@ -45,14 +45,28 @@ __global__ void k_fill_u64(uint64_t *__restrict__ p, uint64_t n, uint64_t v) {
         p[i] = v;
 }
 
+// The counters a call starts from zero, by n threads, this one the i-th.
+__device__ __forceinline__ void clear_call(const CallState &c, uint64_t i, uint64_t n) {
+    if (!c.scan)
+        return;
+    for (uint64_t x = i; x < c.n_scan; x += n)
+        c.scan[x] = 0;
+    for (uint64_t x = i; x < kMarkBuckets; x += n)
+        c.cursors[x] = 0;
+    if (i == 0)
+        *c.n_valid = 0;
+}
+
 // ---------------------------------------------------------------------------
 // ingest: one thread per 32 bases -> codes[2i], codes[2i+1], inv[i]
 // ---------------------------------------------------------------------------
 __global__ void k_ingest(const uint8_t *__restrict__ reads, uint64_t n_bases,
                          uint32_t *__restrict__ codes, uint32_t *__restrict__ inv,
                          uint32_t *__restrict__ rs, uint8_t *__restrict__ flags,
-                         uint64_t n_mask_words, uint64_t n_flag_words, int aligned16) {
+                         uint64_t n_mask_words, uint64_t n_flag_words, int aligned16,
+                         CallState call) {
     uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    clear_call(call, i, (uint64_t)gridDim.x * blockDim.x);
     if (i >= n_mask_words)
         return;
     // clear this word's read-start bits (set afterwards by k_read_starts) and
@@ -623,50 +637,9 @@ static hipError_t launch(Profiler *P, int phase, K kernel, dim3 grid, dim3 block
     return hipGetLastError();
 }
 
-// The counters a call starts from zero, by n threads, this one the i-th.
-__device__ __forceinline__ void clear_call(const CallState &c, uint64_t i, uint64_t n) {
-    for (uint64_t x = i; x < c.n_scan; x += n)
-        c.scan[x] = 0;
-    for (uint64_t x = i; x < kMarkBuckets; x += n)
-        c.cursors[x] = 0;
-    if (i == 0)
-        *c.n_valid = 0;
-}
-
 __global__ void __launch_bounds__(256) k_clear_call(CallState call) {
     clear_call(call, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x,
                (uint64_t)gridDim.x * blockDim.x);
-}
-
-// The valid-window bitmap of K-base windows (valid_word), one mask word per
-// thread.  Only the words of the call's tiles are written (n_out), so that a
-// read set inside a larger buffer leaves its neighbours' words alone; the
-// bin passes read no word past them.
-// Also clears the call's counters (clear_call): one launch fewer.
-__global__ void __launch_bounds__(256) k_valid_windows(const uint32_t *__restrict__ inv,
-                                                       const uint32_t *__restrict__ rs,
-                                                       uint64_t n_words, uint64_t n_out,
-                                                       uint64_t n_bases, uint32_t K,
-                                                       uint32_t *__restrict__ valid,
-                                                       CallState call) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    clear_call(call, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride);
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_out; i += stride)
-        valid[i] = valid_word(inv, rs, n_words, i, K, n_bases);
-}
-
-hipError_t launch_valid_windows(uint64_t n_bases, uint32_t k, const Workspace &W, hipStream_t s,
-                                Profiler *P) {
-    const uint64_t n_mask = mask_words(n_bases);
-    const uint64_t n_out = tiles(n_bases) * (kTile / 32);
-    if (P)
-        P->begin(kPhValid, s);
-    hipLaunchKernelGGL(k_valid_windows, dim3(grid_for(n_out, 256)), dim3(256), 0, s,
-                       (const uint32_t *)W.inv, (const uint32_t *)W.rs, n_mask, n_out, n_bases,
-                       k, W.valid, call_state(W, n_bases));
-    if (P)
-        P->end(s);
-    return hipGetLastError();
 }
 
 hipError_t launch_clear_call(uint64_t n_bases, const Workspace &W, hipStream_t s) {
@@ -677,17 +650,18 @@ hipError_t launch_clear_call(uint64_t n_bases, const Workspace &W, hipStream_t s
 }
 
 hipError_t launch_ingest(const uint8_t *reads, uint64_t n_bases, const uint64_t *offsets,
-                         uint64_t n_reads, const Workspace &W, bool flag_bytes, hipStream_t s,
-                         Profiler *P) {
+                         uint64_t n_reads, const Workspace &W, bool flag_bytes,
+                         const CallState &call, hipStream_t s, Profiler *P) {
     uint64_t n_mask = mask_words(n_bases);
     if (P)
         P->begin(kPhIngest, s);
-    // k_ingest also clears the read-start words and, for the batched form, the
-    // flag bytes of every tile of the call (n_mask * 32 positions cover them)
+    // k_ingest also clears the read-start words, the call's counters (call:
+    // none in the batched form) and, for the batched form, the flag bytes of
+    // every tile of the call (n_mask * 32 positions cover them)
     int aligned = ((uintptr_t)reads & 15u) == 0;
     hipLaunchKernelGGL(k_ingest, dim3(grid_for(n_mask, 256)), dim3(256), 0, s, reads, n_bases,
                        W.codes, W.inv, W.rs, W.flags8, n_mask,
-                       flag_bytes ? tiles(n_bases) * (kTile / 32) : 0ull, aligned);
+                       flag_bytes ? tiles(n_bases) * (kTile / 32) : 0ull, aligned, call);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && n_reads > 0) {
         hipLaunchKernelGGL(k_read_starts, dim3(grid_for(n_reads, 256)), dim3(256), 0, s, offsets,

@@ -72,7 +72,7 @@ struct Workspace {
     uint32_t *codes = nullptr;    // code_words(cap) 2-bit packed bases
     uint32_t *inv = nullptr;      // mask_words(cap) invalid-base bits
     uint32_t *rs = nullptr;       // mask_words(cap) read-start bits
-    uint32_t *valid = nullptr;    // mask_words(cap) valid-window bits (binned paths)
+    uint32_t *valid = nullptr;    // mask_words(cap) valid-window bits (batched form)
     uint8_t *flags8 = nullptr;    // tiles(cap)*kTile bytes: flag bytes (batched form), or the
                                   // distinct and trustworthy bits (distinct_bits, trust_bits)
     uint64_t cap = 0;
@@ -260,12 +260,8 @@ hipError_t scan_u32_u32(const uint32_t *in, uint32_t *out, uint64_t n, uint32_t 
                         uint32_t *partial, hipStream_t s);
 
 hipError_t launch_ingest(const uint8_t *reads, uint64_t n_bases, const uint64_t *offsets,
-                         uint64_t n_reads, const Workspace &W, bool flag_bytes, hipStream_t s,
-                         Profiler *P);
-// The valid-window bitmap of k-base windows into W.valid (binned paths),
-// from the bitmaps launch_ingest wrote; also clears the call's counters.
-hipError_t launch_valid_windows(uint64_t n_bases, uint32_t k, const Workspace &W, hipStream_t s,
-                                Profiler *P);
+                         uint64_t n_reads, const Workspace &W, bool flag_bytes,
+                         const CallState &call, hipStream_t s, Profiler *P);
 hipError_t launch_insert_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t c0, uint64_t c1,
                                bool zero_filter, const Workspace &W, hipStream_t s, Profiler *P);
 // Binned-path plan for chunks of chunk_positions; false when the countBF
