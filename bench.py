@@ -107,27 +107,26 @@ def algorithmic_bytes(phase: str, n_bases: int, n_windows: int, n_distinct: int,
     insert's classification covers in the position domain (None: the
     classification of a key list)."""
     entries = n_windows * k_h
-    if phase == "bin_count":         # packed input, a 4-byte slot id (+ partition byte)
-        return n_bases * (0.5 + (5 if partitioned else 4) * k_h)
-    if phase == "bin_part":          # slot ids + partition bytes in, 8-byte entries out
-        return n_bases * 5 * k_h + entries * 8
-    if phase == "part_count":        # entries of the partition lists in
-        return entries * 8
-    # bytes per entry: the single-level path's lists are 6-byte entries; the
-    # partitioned path's partition and bucket lists are 8-byte entries and its
-    # region lists 6-byte ones; the batched form's fused kernels keep 8
-    ent = entry_bytes or 6
-    if phase == "bin_bucket":        # slot ids (or partition-list entries) in, entries out
-        return entries * 16 if partitioned else n_bases * 4 * k_h + entries * ent
-    if phase == "bin_region":        # bucket-list entries in, region-list entries out
-        return entries * (8 + ent) if partitioned else entries * 2 * ent
+    # the batched form: slot ids, 8-byte entries, a flag byte per position; the
+    # single-set pipeline: entries of 4 bytes (5 in the two-level form) sorted
+    # by block, 4-byte first-seen records, two bits per position
+    batched = entry_bytes is not None
+    ent = entry_bytes or (5 if partitioned else 4)
+    if phase == "bin_count":         # packed input, slot ids or sorted entries out
+        return n_bases * (0.5 + 4 * k_h) if batched else n_bases * 0.5 + entries * ent
+    if phase == "bin_part":          # packed input, entries sorted by bucket out
+        return n_bases * 0.5 + entries * ent
+    if phase == "part_count":        # entries sorted by bucket in, by region out
+        return entries * 2 * ent
+    if phase == "bin_bucket":        # slot ids in, entries out
+        return n_bases * 4 * k_h + entries * ent
     if phase == "region":            # entries in, countBF cells read + written per chunk, flags
-        b = entries * ent + n_chunks * n_words * 16 + n_distinct
+        b = entries * ent + n_chunks * n_words * 16 + n_distinct * (1 if batched else 4)
         if carried:                  # carried records: 6 B written, then 2 B read + 2 B marked
             b += n_distinct * carried / n_bases * 10
         return b
-    if phase == "tile_count":        # flag byte per position (+ packed input when the
-        return n_bases * (1.0 if binned else 1.5)  # insert passes did not count windows)
+    if phase == "tile_count":        # flag byte per position; direct path: a bit, and the
+        return n_bases * (1.0 if binned else 0.625)  # packed input to count windows
     if phase == "claim_increment":   # cell RMW + first-seen entry RMW per slot, packed input
         return n_windows * k_h * (16 + 8) + n_bases * 0.5
     if phase == "claim":             # cell read + entry RMW per slot
@@ -136,20 +135,19 @@ def algorithmic_bytes(phase: str, n_bases: int, n_windows: int, n_distinct: int,
         return n_windows * k_h * 16 + n_bases * 0.5
     if phase == "resolve":           # entry read per slot, winner reset, flags
         return n_windows * k_h * 4 + n_distinct * 4 + n_bases * (0.5 + 0.125)
-    if phase == "winners":           # first-seen records: two distribution passes (6 B in,
-        return n_distinct * 22 + n_bases  # 4 B out, 4 B in and out), 4 B into the flag blocks,
-                                          # flag bytes written in 16-byte groups
+    if phase == "winners":           # first-seen records in (partitioned: distributed by two
+        return n_distinct * (22 if partitioned else 4) + n_bases / 4  # passes first), bits out
     if phase == "reset":             # the countBF's cells written (cleared)
         return n_words * 8
-    if phase == "ingest":            # ASCII in, packed codes + bitmaps out, flag bytes cleared
-        return n_bases * 2.5
+    if phase == "ingest":            # ASCII in, packed codes + bitmaps out (batched form: flag
+        return n_bases * (2.5 if batched else 1.5)  # bytes cleared)
     if phase == "valid_windows":     # invalid-base and read-start bits in, valid-window bits out
         return n_bases * 3 / 8
-    if phase == "scatter":           # flag byte + packed input, keys out (distinct + split)
-        return n_bases * 1.5 + n_distinct * 2 * key_bytes
+    if phase == "scatter":           # flags + packed input, keys out (distinct + split)
+        return n_bases * (1.5 if batched else 0.5) + n_distinct * 2 * key_bytes
     if phase == "classify_mark":
-        if classified is not None:   # flag byte + packed codes per position, a cell per
-            return classified * 1.25 + n_distinct * classified / n_bases * 8 * k_h  # slot
+        if classified is not None:   # bits + packed codes per position, a cell per slot
+            return classified * 0.5 + n_distinct * classified / n_bases * 8 * k_h
         return n_distinct * (key_bytes + 8 * k_h + 0.125)  # key + cell per slot, mask out
     if phase == "classify_scatter":  # key in, key out, mask
         return n_distinct * (2 * key_bytes + 0.125)
@@ -297,6 +295,10 @@ def ops_per_window(k_h: int, alpha: int, k: int = 31) -> int:
     return first + l_extra + (k_h - 1) * (extra + l_extra)
 
 
+# phases of the hashing kernel (partitioned plans name theirs apart)
+HASH_PHASES = ("bin_count", "bin_part")
+
+
 def roofline_of(phases, steps, n_bases, n_windows, n_distinct, k_h, n_words, workload,
                 n_chunks=1, partitioned=False, alpha=8, k=31, entry_bytes=None, classified=None,
                 carried=0):
@@ -309,7 +311,7 @@ def roofline_of(phases, steps, n_bases, n_windows, n_distinct, k_h, n_words, wor
     avg_s = phases[dom][0] / phases[dom][1] / 1e3
     per_step = phases[dom][1] / max(1, steps)
     traffic = traffic_for(dom, workload) if k <= 32 else None
-    if dom == "bin_count":
+    if dom in HASH_PHASES:
         ops = n_windows * ops_per_window(k_h, alpha, k) / per_step
         achieved = ops / avg_s / 1e9
         return {"bound": "alu", "achieved": round(achieved, 1), "peak": round(ALU_PEAK_GOPS, 1),
@@ -337,7 +339,7 @@ def hbm_rooflines(phases, steps, n_bases, n_windows, n_distinct, k_h, n_words, w
         b = algorithmic_bytes(ph, n_bases, n_windows, n_distinct, k_h, n_words, n_chunks,
                               partitioned, key_bytes=8 if k <= 32 else 16,
                               classified=classified, carried=carried)
-        if ph == "bin_count" or b <= 0:
+        if ph in HASH_PHASES or b <= 0:
             continue
         per_step = launches / max(1, steps)
         avg_s = ms / launches / 1e3
@@ -736,11 +738,11 @@ def step_roofline(phases, steps, n_bases, n_windows, n_distinct, k_h, n_words, n
     kb = 8 if k <= 32 else 16
     per_phase = {}
     for ph in phases:
-        if ph == "bin_count":
+        if ph in HASH_PHASES:
             t = n_windows * ops_per_window(k_h, alpha, k) / (ALU_PEAK_GOPS * 1e9)
         elif ph == "classify_mark":
             share = classified / max(1, n_bases)
-            t = share * n_distinct * k_h / rand_rate + classified * 1.25 / copy_Bps
+            t = share * n_distinct * k_h / rand_rate + classified * 0.5 / copy_Bps
         else:
             t = algorithmic_bytes(ph, n_bases, n_windows, n_distinct, k_h, n_words, n_chunks,
                                   partitioned, key_bytes=kb, carried=carried) / copy_Bps

@@ -178,10 +178,10 @@ void kc_destroy(kc_filter *f);
  * KC_ERANGE on a handle whose scratch is the caller's (kc_create_in) when
  * max_bases exceeds what it was laid out for.
  * Sizes, k_h = 1: countBFs of up to 16384 regions (256 MB at alpha = 8) take
- * the binned path, about 22 bytes per base (packed codes and bitmaps, a flag
- * byte, slot ids, two entry lists); larger countBFs take the partitioned
+ * the binned path, about 22 bytes per base (packed codes and bitmaps, the
+ * positions' bits, entry lists and their tables); larger countBFs take the partitioned
  * path, about 19 bytes per base of a chunk of up to 2^32 - 2^16 bases (two
- * 8-byte entry lists, each holding two kinds of data in turn); the direct
+ * entry buffers of 8 bytes, each holding two kinds of data in turn); the direct
  * path (forced, or beyond 256 partitions) takes 4 bytes per counter plus
  * about 2 bytes per base.  Scratch grows, and is never shrunk, by calls
  * larger than the reservation. */
@@ -346,8 +346,8 @@ typedef enum {
     KC_PHASE_BIN_PART = 16,       /* partitioned path: hashing, entries sorted by bucket */
     KC_PHASE_PART_COUNT = 17,     /* partitioned path: buckets counted and sorted by region */
     KC_PHASE_VALID = 18,          /* batched form: valid-window bitmap of each set's k */
-    KC_PHASE_WINNERS = 19,        /* binned paths, chunks beyond 2^28 positions: first-seen
-                                     records -> flag bytes */
+    KC_PHASE_WINNERS = 19,        /* binned paths: first-seen records -> distinct and
+                                     trustworthy bits, tile counts */
     KC_PHASE_COUNT = 20
 } kc_phase;
 
