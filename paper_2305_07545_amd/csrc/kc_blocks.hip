@@ -1039,19 +1039,24 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
 // are counted.  The records' room is exact, so that they lie dense in `flat`:
 // asked for when a region's records are counted, and taken after the next
 // region's update, the records held in registers until then.
-template <int kCells>
+//
+// kOwn (chunks above 2^28 positions, carried chunks): the records go to room of
+// the region's own for each of its entries, as k_region_runs' do.
+template <int kCells, bool kOwn>
 __global__ void __launch_bounds__(kRegionWG)
 k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict__ list,
                 const uint8_t *__restrict__ list_hi, const uint32_t *__restrict__ starts,
                 int classify, uint32_t tau, uint32_t *__restrict__ cursor,
-                uint32_t *__restrict__ flat) {
+                uint32_t *__restrict__ flat, RecordSpace own, Carry C) {
     constexpr uint32_t kWaves = kRegionWG / 64;
-    constexpr int kGroups = 2, kHeld = 4 * kGroups;
+    // larger chunks' runs are shorter: more groups of fewer entries
+    constexpr int kGroups = kOwn ? 3 : 2, kHeld = 4 * kGroups;
     constexpr uint32_t kStep = 64u * kGroups;
     __shared__ uint32_t hits[kRegionCounters];
     __shared__ uint32_t first[kRegionCounters];
     __shared__ unsigned long long s_cell[kCells * kRegionWG];
     __shared__ uint32_t s_n, s_base;
+    __shared__ uint32_t s_total[2], s_over[2];  // kOwn, by the region's parity
     const uint32_t lane = threadIdx.x & 63u, wave = wave_id(), grid = gridDim.x;
     const uint32_t shift = P.region_shift, S = 1u << shift;
     const uint64_t n_words = F.X * F.Y;
@@ -1061,7 +1066,9 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         first[i] = kIdle;
     }
     if (threadIdx.x == 0)
-        s_n = 0;
+        s_n = s_total[0] = s_total[1] = s_over[0] = s_over[1] = 0;
+    const bool carry_out = kOwn && C.mode == Carry::kOut;
+    const bool carry_in = kOwn && C.mode == Carry::kIn && C.n_prev > 0;
     auto load_cells = [&](uint32_t r, uint64_t(&cell)[kCells]) {
         const uint64_t wbase = (uint64_t)r << shift;
 #pragma unroll
@@ -1125,7 +1132,7 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         if (t < first[local])
             atomicMin(&first[local], t);
     };
-    // the counter's update by its first entry; its record, or 0
+    // the counter's update by its first entry; its record's mark, or 0
     auto update = [&](uint32_t local, uint32_t t) -> uint32_t {
         if (first[local] != t)
             return 0u;
@@ -1143,7 +1150,7 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         const uint32_t room = fm - pf, inc = h < room ? h : room;
         if (inc)  // the field grows without carrying out
             atomicAdd(&s_cell[w], (unsigned long long)inc << sh);
-        return pf ? 0u : t | ((classify && inc > tau ? 3u : 1u) << 30);
+        return pf ? 0u : (classify && inc > tau ? 3u : 1u);
     };
     uint32_t r = (grid & 7u) == 0 ? (blockIdx.x & 7u) * (grid >> 3) + (blockIdx.x >> 3) : blockIdx.x;
     uint64_t cell[kCells];
@@ -1162,8 +1169,13 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
             if ((has >> j) & 1u)
                 flat[base + at + (uint32_t)__popc(has & ((1u << j) - 1u))] = rec[j];
     };
+    // kOwn: the region's record `slot`, of position t and mark or counter
+    auto put = [&](uint32_t slot, uint32_t t, uint32_t half) {
+        (carry_out ? C.word + (uint64_t)C.chunk * C.cap : own.word)[slot] = t;
+        (carry_out ? C.half + (uint64_t)C.chunk * C.cap : own.half)[slot] = (uint16_t)half;
+    };
     __syncthreads();  // counters clean
-    for (; r < P.n_regions; r += grid) {
+    for (uint32_t turn = 0; r < P.n_regions; r += grid, turn ^= 1u) {
         LaneRuns Rn;
         Held Hn;
         uint64_t celln[kCells];
@@ -1180,22 +1192,52 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
             load(R, w0, X);
             each(R, w0, X, count);
         }
+        if constexpr (kOwn) {
+            const uint32_t n = wave_inclusive(R.e - R.s);
+            if (lane == 63) {
+                atomicAdd(&s_total[turn], n);
+                if (R.n > kStep)
+                    s_over[turn] = 1;
+            }
+        }
         __syncthreads();  // counted
-        uint32_t fresh[kHeld], won = 0;
+        if constexpr (kOwn) {  // room for a record of every entry
+            got = 0;
+            if (threadIdx.x == 0 && s_total[turn])
+                got = atomicAdd(cursor, s_total[turn]);
+        }
+        uint32_t fresh[kHeld], halves[kHeld / 2], won = 0;
 #pragma unroll
         for (int j = 0; j < kHeld; j++)
             fresh[j] = 0;
+#pragma unroll
+        for (int j = 0; j < kHeld / 2; j++)
+            halves[j] = 0;
         each(R, 0, H, [&](int j, uint32_t local, uint32_t t) {
-            fresh[j] = update(local, t);
-            won |= fresh[j] ? 1u << j : 0u;
+            const uint32_t mark = update(local, t);
+            if (kOwn) {
+                fresh[j] = t;
+                halves[j / 2] |= (carry_out ? local : mark) << (16 * (j % 2));
+            } else {
+                fresh[j] = t | (mark << 30);
+            }
+            won |= mark ? 1u << j : 0u;
         });
+        if constexpr (kOwn)
+            if (s_over[turn]) {
+                if (threadIdx.x == 0)
+                    s_base = got;
+                __syncthreads();
+            }
         for (uint32_t w0 = kStep; w0 < R.n; w0 += kStep) {
             // more than the registers hold: each record's room by itself
             load(R, w0, H);
             each(R, w0, H, [&](int, uint32_t local, uint32_t t) {
-                const uint32_t x = update(local, t);
-                if (x)
-                    flat[atomicAdd(cursor, 1u)] = x;
+                const uint32_t mark = update(local, t);
+                if (mark && kOwn)
+                    put(s_base + atomicAdd(&s_n, 1u), t, carry_out ? local : mark);
+                else if (mark)
+                    flat[atomicAdd(cursor, 1u)] = t | (mark << 30);
             });
         }
         const uint32_t mine = (uint32_t)__popc(won), incl = wave_inclusive(mine);
@@ -1218,10 +1260,15 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
             s_base = got;
         __syncthreads();  // updated, counters clean
         const uint32_t base = s_base;
-        got = 0;
         if (threadIdx.x == 0) {
-            if (s_n)
-                got = atomicAdd(cursor, s_n);
+            if constexpr (kOwn) {
+                const uint64_t x = carry_out ? (uint64_t)C.chunk * C.stride + r : r;
+                (carry_out ? C.off : own.off)[x] = base;
+                (carry_out ? C.n : own.n)[x] = s_n;
+                s_total[turn] = s_over[turn] = 0;
+            } else {
+                got = s_n ? atomicAdd(cursor, s_n) : 0u;
+            }
             s_n = 0;
         }
         const uint64_t wbase = (uint64_t)r << shift;
@@ -1233,20 +1280,34 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
                 F.words[wbase + w] = next;
             cell[k] = celln[k];
         }
-        store_records(base);
+        if constexpr (kOwn) {
+            uint32_t slot = base + place;
 #pragma unroll
-        for (int j = 0; j < kHeld; j++)
-            rec[j] = fresh[j];
-        has = won;
-        at = place;
+            for (int j = 0; j < kHeld; j++)
+                if ((won >> j) & 1u)
+                    put(slot++, fresh[j], (halves[j / 2] >> (16 * (j % 2))) & 0xFFFFu);
+            if (carry_in) {
+                mark_carried(F, shift, C, r, s_cell, tau);
+                __syncthreads();  // the cells are rewritten by the next region
+            }
+        } else {
+            store_records(base);
+#pragma unroll
+            for (int j = 0; j < kHeld; j++)
+                rec[j] = fresh[j];
+            has = won;
+            at = place;
+        }
         R = Rn;
         H = Hn;
     }
-    __syncthreads();
-    if (threadIdx.x == 0)
-        s_base = got;
-    __syncthreads();
-    store_records(s_base);
+    if constexpr (!kOwn) {
+        __syncthreads();
+        if (threadIdx.x == 0)
+            s_base = got;
+        __syncthreads();
+        store_records(s_base);
+    }
 }
 
 namespace {
@@ -1459,11 +1520,11 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
     rec.n_buckets = (uint32_t)((len + (1ull << rec.log) - 1) >> rec.log);
     // Sparse regions are worked by entry: below kSparseEntries a region on
     // average, for the forms whose cells fit beside the counters in LDS
-    const bool sparse = B.two && !records && carry.mode == Carry::kNone &&
-                        plan.region_counters == (uint32_t)kRegionCounters &&
-                        (plan.region_shift == 10 || plan.region_shift == 11) &&
-                        B.n_super <= kRegionWG && 8 * len * F.k_h <= room &&
-                        len * F.k_h <= kSparseEntries * plan.n_regions;
+    const bool by_entry = B.two && plan.region_counters == (uint32_t)kRegionCounters &&
+                          (plan.region_shift == 10 || plan.region_shift == 11) &&
+                          B.n_super <= kRegionWG && len * F.k_h <= kSparseEntries * plan.n_regions;
+    const bool own = records || carry.mode == Carry::kOut;  // records in the regions' own room
+    const bool sparse = by_entry && !own && carry.mode == Carry::kNone && 8 * len * F.k_h <= room;
     if (records || carry.mode == Carry::kOut || sparse) {
         rec.cursor = W.n_entries + 3;
         if ((e = fill_u32(rec.cursor, 1, 0u, s)) != hipSuccess)
@@ -1492,10 +1553,11 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
         P->begin(kPhRegion, s);
     const uint32_t grid = region_grid(plan.n_regions, plan.region_counters);
     if (sparse) {
-        hipLaunchKernelGGL(plan.region_shift == 10 ? k_region_sparse<1> : k_region_sparse<2>,
+        hipLaunchKernelGGL((plan.region_shift == 10 ? k_region_sparse<1, false>
+                                                    : k_region_sparse<2, false>),
                            dim3(grid), dim3(kRegionWG), 0, s, F, plan, B, (const uint32_t *)merged,
                            (const uint8_t *)merged_hi, (const uint32_t *)starts, classify ? 1 : 0,
-                           tau, rec.cursor, rec.word + len * F.k_h);
+                           tau, rec.cursor, rec.word + len * F.k_h, rec, carry);
         if (P)
             P->end(s);
         if ((e = hipGetLastError()) != hipSuccess)
@@ -1511,14 +1573,22 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
             P->end(s);
         return e;
     }
-    const bool small = plan.region_counters == (uint32_t)kSmallRegionCounters;
-    hipLaunchKernelGGL(rec.sorted ? (small ? runs_kernel<kSmallRegionCounters, true>(plan, B)
-                                           : runs_kernel<kRegionCounters, true>(plan, B))
-                                  : (small ? runs_kernel<kSmallRegionCounters, false>(plan, B)
-                                           : runs_kernel<kRegionCounters, false>(plan, B)),
-                       dim3(grid), dim3(kRegionWG), 0,
-                       s, F, c0, plan, B, (const uint32_t *)(B.two ? merged : list),
-                       (const uint8_t *)merged_hi, runs, classify ? 1 : 0, tau, rec, carry);
+    if (by_entry && own) {
+        hipLaunchKernelGGL((plan.region_shift == 10 ? k_region_sparse<1, true>
+                                                    : k_region_sparse<2, true>),
+                           dim3(grid), dim3(kRegionWG), 0, s, F, plan, B, (const uint32_t *)merged,
+                           (const uint8_t *)merged_hi, (const uint32_t *)starts, classify ? 1 : 0,
+                           tau, rec.cursor, nullptr, rec, carry);
+    } else {
+        const bool small = plan.region_counters == (uint32_t)kSmallRegionCounters;
+        hipLaunchKernelGGL((rec.sorted ? (small ? runs_kernel<kSmallRegionCounters, true>(plan, B)
+                                                : runs_kernel<kRegionCounters, true>(plan, B))
+                                       : (small ? runs_kernel<kSmallRegionCounters, false>(plan, B)
+                                                : runs_kernel<kRegionCounters, false>(plan, B))),
+                           dim3(grid), dim3(kRegionWG), 0,
+                           s, F, c0, plan, B, (const uint32_t *)(B.two ? merged : list),
+                           (const uint8_t *)merged_hi, runs, classify ? 1 : 0, tau, rec, carry);
+    }
     if (P)
         P->end(s);
     e = hipGetLastError();

@@ -126,3 +126,25 @@ def test_uneven_buckets_against_the_oracle(n, hot):
 ])
 def test_sparse_regions_against_the_oracle(n, X, Y, alpha, k_h, k):
     test_block_form_against_the_oracle(n, X, Y, alpha, k_h, k)
+
+
+# the same regions with their records in room of their own: forced winner
+# records, and several chunks whose records wait for the last one's counters
+@pytest.mark.parametrize("n,hot,alpha,k_h,chunk", [
+    (400_000, 0, 8, 1, None), (400_000, 0, 5, 3, None), (400_000, 30_000, 4, 1, None),
+    (400_000, 0, 8, 1, 1 << 17), (400_000, 30_000, 4, 1, 1 << 17),
+])
+def test_sparse_regions_with_own_records(n, hot, alpha, k_h, chunk, monkeypatch):
+    print(f"case own records n={n} hot={hot} alpha={alpha} k_h={k_h} chunk={chunk}", flush=True)
+    monkeypatch.setenv("KMERCO_WINNER_RECORDS", "1")
+    if chunk:
+        monkeypatch.setenv("KMERCO_CHUNK_POSITIONS", str(chunk))
+    rs = reads_of(7, n, 31)
+    rs.reads[:hot] = ord("A")
+    reads = torch.from_numpy(rs.reads).cuda()
+    offs = torch.from_numpy(rs.offsets.view(np.int64)).cuda()
+    g = P.run_kmerco(reads, offs, 31, 2, 5779, 5813, alpha, k_h)
+    c = oracle.run_kmerco(rs.reads, rs.offsets, 31, 2, 5779, 5813, alpha, k_h)
+    for name, a, b in zip(["words", "distinct", "trust", "err"], g[:4], c[:4]):
+        assert np.array_equal(np.asarray(a, dtype=np.uint64), np.asarray(b, dtype=np.uint64)), name
+    assert g[4] == c[4]
