@@ -160,13 +160,13 @@ kc_status ensure_binned(kc_filter *f, const kc::BinPlan &B, uint64_t chunk_posit
     return KC_OK;
 }
 
-// partitioned binned-path buffers for one chunk of the given plan.  The
-// path needs two entry-sized buffers besides its count matrices, each used
-// twice (kernels of one stream, in this order):
-//   bucketed: slot ids and partition bytes (hashing -> partition scatter),
-//             then the bucket lists (list binning -> region binning);
-//   entries:  the partition lists (partition scatter -> list binning), then
-//             the region lists (region binning -> region pass).
+// partitioned binned-path buffers for one chunk of the given plan: two
+// entry-sized buffers besides the matrices' room, each used twice (kernels of
+// one stream, in this order; launch_blocks_chunk places what lies in them):
+//   bucketed: the blocks' list and table (hashing -> second level), then the
+//             first-seen records;
+//   entries:  the superblocks' list and starts (second level -> region pass),
+//             then the winner passes' first area.
 kc_status ensure_parts(kc_filter *f, const kc::BinPlan &B, uint64_t chunk_positions) {
     kc::Workspace &W = *f->W;
     const uint64_t n_slots = chunk_positions * f->layout.k_h;

@@ -162,7 +162,7 @@ __global__ void __launch_bounds__(256) kb_transpose(const SetDesc *__restrict__ 
 // Slot ids of an item -> its segments of the entry list, counting-sorted by
 // region in LDS per batch of kWriteStage entries.  The large batch keeps the
 // runs written per region long even for sets of 2048 regions (runs of the
-// smaller level-1 batches of the single-set path would be 2 entries there).
+// batches of 4096 entries would be 2 entries there).
 // One workgroup fits a CU, so it has 16 wavefronts: 256 sets of 0.2 M bases
 // 0.231 -> 0.194 ms against eight; 64 sets of 3 M bases 0.99 -> 0.97, bound
 // there by the short runs' partial lines.

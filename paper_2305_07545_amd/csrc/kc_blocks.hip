@@ -48,16 +48,17 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, kJ...>, Fn f
 // Hash every valid window of the block once and write the block's entries
 // sorted by bin: by region, or, in the two-level form (kTwo), by bucket of
 // 2^sub_log regions, the region within the bucket being the 11 high bits of a
-// 5-byte entry (the fifth bytes in an array of their own).  kEpt: entries per thread (kKh hash functions x
-// positions); kFast, kWide as k_bin_count.
+// 5-byte entry (the fifth bytes in an array of their own).  kEpt: entries per
+// thread (kKh hash functions x positions).  kFast: the fast layout
+// (fast_layout); kWide: two-word keys.
 //
 // The block's valid windows are first listed in LDS (in the space the sorted
 // entries take later), so that every lane hashes one at each step.  A
 // thread's entries stay in registers between hashing, where the histogram's
 // atomic also gives each entry's rank in its region, and staging.  Bound by
-// its vector instructions (82% busy; 144 per 64 windows, 117 of them the
-// hash): 0.55 ms for the bacterial workload's 116 M windows, where hashing
-// alone and writing slot ids took 0.42.
+// its vector instructions (79 to 82% busy; about 130 per 64 windows, 117 of
+// them the hash): 0.585 ms for 116 M windows over 3914 regions, where hashing
+// alone and writing slot ids took 0.43 and the sorting passes after it 0.88.
 template <int kWG, int kEpt, int kKh, bool kFast, bool kWide, bool kTwo>
 __global__ void __launch_bounds__(kWG, 4)
 k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t n_words, uint64_t c0, uint64_t c1, BlockPlan B,
@@ -499,8 +500,8 @@ k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
     }
 }
 
-// The region pass over the blocks' runs.  kCounters: counters per region (as
-// k_region).  kCells: the cells each thread updates, held in registers (the
+// The region pass over the blocks' runs.  kCounters: counters per region.
+// kCells: the cells each thread updates, held in registers (the
 // plan's region has kCells * kRegionWG cells), or 0 for regions of fewer cells than
 // threads.  kTwo: runs of superblocks, 5-byte entries.  kLanes (one-level form):
 // lanes that take a run together (by its expected length), or 0 for short

@@ -46,7 +46,7 @@ CASES = [
     (500_000, 2707, 2711, 8, 1, 31),          # 3584 regions
     (500_000, 2709, 2711, 8, 1, 31),          # 3587 regions
     (500_000, 3829, 3833, 8, 1, 40),          # 7167 regions
-    (500_000, 3833, 3837, 8, 1, 31),          # 7182 regions: counted binning
+    (500_000, 3833, 3837, 8, 1, 31),          # 7182 regions: two-level form
     (8_388_607, 809, 811, 8, 1, 31), (8_388_608, 809, 811, 8, 1, 31),  # small | large blocks
     (8_400_001, 2709, 2711, 8, 1, 31),        # blocks of 32768
 ]
