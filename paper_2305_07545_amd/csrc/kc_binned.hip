@@ -49,8 +49,9 @@ uint32_t region_grid(uint32_t n_regions, uint32_t counters) {
 // the next 5 bits) into blocks of 2^19 positions, whose bits are built in
 // LDS.  Runs are appended to each bucket at an atomic cursor (the
 // order of records inside a bucket does not matter: a bitmap is built from
-// them), in areas of the two entry buffers sized by the positions they
-// cover, so that they always fit.
+// them), in areas of the two entry buffers.  A position is first seen by each
+// of its hash functions at most, so an area has k_h records of room for every
+// position it covers.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kWinA = 24;             // level-A digit: t >> 24 (256 buckets)
 constexpr uint32_t kWinB = 19;             // level-B digit: (t >> 19) & 31 (2^19 positions)
@@ -70,10 +71,11 @@ static_assert(kWinBuckets <= 256 && kWinBlocksPerBucket <= 256, "digits are stag
 // counts scanned and each digit's run reserved at its bucket's cursor; the
 // kept records (keep(rec)) are then staged in LDS in digit order and written
 // out in that order, consecutive threads to consecutive addresses of a run
-// (the order of records inside a run does not matter).  Ends with a barrier.
+// (the order of records inside a run does not matter).  Buckets' areas are
+// `room` records apart.  Ends with a barrier.
 template <typename Rec, typename Keep>
 __device__ void win_append(const Rec (&v)[kWinPer], uint32_t ok, uint32_t n, uint32_t shift,
-                           uint32_t nd, uint32_t bucket0, uint32_t area_log, uint32_t *s_cnt,
+                           uint32_t nd, uint32_t bucket0, uint64_t room, uint32_t *s_cnt,
                            uint32_t *s_start, uint32_t *s_base, uint32_t *s_wave,
                            uint32_t *s_stage, uint8_t *s_tag, uint32_t *__restrict__ cursor,
                            uint32_t *__restrict__ out, Keep keep) {
@@ -119,7 +121,7 @@ __device__ void win_append(const Rec (&v)[kWinPer], uint32_t ok, uint32_t n, uin
     __syncthreads();
     for (uint32_t j = threadIdx.x; j < n; j += kWinThreads) {
         const uint32_t d = s_tag[j];
-        out[((uint64_t)(bucket0 + d) << area_log) + s_base[d] + (j - s_start[d])] = s_stage[j];
+        out[(bucket0 + d) * room + s_base[d] + (j - s_start[d])] = s_stage[j];
     }
     __syncthreads();
 }
@@ -137,7 +139,8 @@ __global__ void __launch_bounds__(kWinThreads) k_win_a(uint32_t n_regions,
                                                        const uint32_t *__restrict__ e_word,
                                                        const uint16_t *__restrict__ e_half,
                                                        uint32_t *__restrict__ cursor,
-                                                       uint32_t *__restrict__ out) {
+                                                       uint32_t *__restrict__ out,
+                                                       uint32_t k_h) {
     static_assert(kWinRegions == 64, "one wavefront scans the regions' counts");
     __shared__ uint32_t s_stage[kWinBatch];
     __shared__ uint8_t s_tag[kWinBatch];
@@ -186,7 +189,7 @@ __global__ void __launch_bounds__(kWinThreads) k_win_a(uint32_t n_regions,
                 ok |= 1u << u;
             }
         }
-        win_append(v, ok, m, kWinA, kWinBuckets, 0, kWinA, s_cnt, s_start, s_base, s_wave,
+        win_append(v, ok, m, kWinA, kWinBuckets, 0, (uint64_t)k_h << kWinA, s_cnt, s_start, s_base, s_wave,
                    s_stage, s_tag, cursor, out, keep);
     }
 }
@@ -196,7 +199,8 @@ __global__ void __launch_bounds__(kWinThreads) k_win_a(uint32_t n_regions,
 __global__ void __launch_bounds__(kWinThreads) k_win_b(const uint32_t *__restrict__ in,
                                                        const uint32_t *__restrict__ cursor_a,
                                                        uint32_t *__restrict__ cursor_b,
-                                                       uint32_t *__restrict__ out) {
+                                                       uint32_t *__restrict__ out,
+                                                       uint32_t k_h) {
     __shared__ uint32_t s_stage[kWinBatch];
     __shared__ uint8_t s_tag[kWinBatch];
     __shared__ uint32_t s_cnt[kWinBlocksPerBucket], s_start[kWinBlocksPerBucket],
@@ -204,10 +208,10 @@ __global__ void __launch_bounds__(kWinThreads) k_win_b(const uint32_t *__restric
     __shared__ uint32_t s_wave[kWinThreads / 64];
     const uint32_t a = blockIdx.x;
     const uint32_t n = cursor_a[a];
-    const uint32_t per = ((1u << kWinA) + kWinSlices - 1) / kWinSlices;
+    const uint32_t per = ((k_h << kWinA) + kWinSlices - 1) / kWinSlices;
     const uint32_t q0 = blockIdx.y * per;
     const uint32_t q1 = q0 + per < n ? q0 + per : n;
-    const uint32_t *src = in + ((uint64_t)a << kWinA);
+    const uint32_t *src = in + a * ((uint64_t)k_h << kWinA);
     auto keep = [](uint32_t v) -> uint32_t {
         return (v & ((1u << kWinB) - 1u)) | ((v >> kWinA) << kWinB);
     };
@@ -223,8 +227,9 @@ __global__ void __launch_bounds__(kWinThreads) k_win_b(const uint32_t *__restric
                 ok |= 1u << u;
         }
         // digit (t24 >> 19) & 31 of the record (t24 | mark << 24)
-        win_append(v, ok, m, kWinB, kWinBlocksPerBucket, a * kWinBlocksPerBucket, kWinB, s_cnt,
-                   s_start, s_base, s_wave, s_stage, s_tag, cursor_b, out, keep);
+        win_append(v, ok, m, kWinB, kWinBlocksPerBucket, a * kWinBlocksPerBucket,
+                   (uint64_t)k_h << kWinB, s_cnt, s_start, s_base, s_wave, s_stage, s_tag, cursor_b,
+                   out, keep);
     }
 }
 
@@ -380,10 +385,11 @@ bool records_mode(uint64_t len) {
     return len > (1ull << 28);
 }
 
-// The winner passes of one chunk [c0, c0 + len): its records, region r's
-// n_win[r] of them at offsets[r * off_stride] of the word and half arrays;
-// area_a, area_b: the entry buffers, the records' own not the first.
-hipError_t winner_passes(uint32_t n_regions, const uint32_t *offsets, uint64_t off_stride,
+// The winner passes of one chunk [c0, c0 + len): its records, at most k_h a
+// position, region r's n_win[r] of them at offsets[r * off_stride] of the word
+// and half arrays; area_a, area_b: the entry buffers (k_h entries of 8 bytes a
+// position, of which the areas take 4), the records' own not the first.
+hipError_t winner_passes(uint32_t k_h, uint32_t n_regions, const uint32_t *offsets, uint64_t off_stride,
                          const uint32_t *n_win, const uint32_t *rec_word,
                          const uint16_t *rec_half, uint64_t c0, uint64_t len, uint64_t n_bases,
                          uint32_t *area_a, uint32_t *area_b, const Workspace &W, hipStream_t s, Profiler *P) {
@@ -396,17 +402,17 @@ hipError_t winner_passes(uint32_t n_regions, const uint32_t *offsets, uint64_t o
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_win_a, dim3((n_regions + kWinRegions - 1) / kWinRegions),
                            dim3(kWinThreads), 0, s, n_regions, offsets, off_stride, n_win,
-                           rec_word, rec_half, cursors, area_a);
+                           rec_word, rec_half, cursors, area_a, k_h);
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_win_b, dim3(n_a, kWinSlices), dim3(kWinThreads), 0, s,
                            (const uint32_t *)area_a, (const uint32_t *)cursors,
-                           cursors + kWinBuckets, area_b);
+                           cursors + kWinBuckets, area_b, k_h);
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
-        e = launch_marks(area_b, 1ull << kWinB, kWinB, cursors + kWinBuckets, false, c0, len,
+        e = launch_marks(area_b, (uint64_t)k_h << kWinB, kWinB, cursors + kWinBuckets, false, c0, len,
                          n_bases, W, s);
     }
     if (P)
@@ -414,11 +420,11 @@ hipError_t winner_passes(uint32_t n_regions, const uint32_t *offsets, uint64_t o
     return e;
 }
 
-hipError_t launch_record_winners(uint32_t n_regions, const uint32_t *off, const uint32_t *n,
+hipError_t launch_record_winners(uint32_t k_h, uint32_t n_regions, const uint32_t *off, const uint32_t *n,
                                  const uint32_t *word, const uint16_t *half, uint64_t c0,
                                  uint64_t len, uint64_t n_bases, const Workspace &W, hipStream_t s,
                                  Profiler *P) {
-    return winner_passes(n_regions, off, 1, n, word, half, c0, len, n_bases, (uint32_t *)W.entries,
+    return winner_passes(k_h, n_regions, off, 1, n, word, half, c0, len, n_bases, (uint32_t *)W.entries,
                          (uint32_t *)W.bucketed, W, s, P);
 }
 
@@ -451,7 +457,8 @@ hipError_t launch_carried_winners(const BinPlan &plan, const Carry &carry, uint3
                                   uint64_t len, uint64_t n_bases, const Workspace &W, hipStream_t s,
                                   Profiler *P) {
     const uint64_t at = (uint64_t)j * carry.stride;
-    return winner_passes(plan.n_regions, carry.off + at, 1, carry.n + at,
+    // carried calls have one hash function
+    return winner_passes(1, plan.n_regions, carry.off + at, 1, carry.n + at,
                          carry.word + (uint64_t)j * carry.cap, carry.half + (uint64_t)j * carry.cap,
                          c0, len, n_bases, (uint32_t *)W.bucketed, (uint32_t *)W.entries, W, s, P);
 }

@@ -1594,7 +1594,7 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
         P->end(s);
     e = hipGetLastError();
     if (e == hipSuccess && records)
-        return launch_record_winners(plan.n_regions, rec.off, rec.n, rec.word, rec.half, c0, len,
+        return launch_record_winners(F.k_h, plan.n_regions, rec.off, rec.n, rec.word, rec.half, c0, len,
                                      R.n_bases, W, s, P);
     if (e == hipSuccess && rec.sorted) {
         if (P)

@@ -62,9 +62,9 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
                                bool classify, uint32_t tau, const Carry &carry, bool records,
                                hipStream_t s, Profiler *P);
 
-// The winner passes of chunk [c0, c0 + len) over records whose arrays lie in
-// W.bucketed (kc_binned.hip).
-hipError_t launch_record_winners(uint32_t n_regions, const uint32_t *off, const uint32_t *n,
+// The winner passes of chunk [c0, c0 + len) over records, at most k_h a
+// position, whose arrays lie in W.bucketed (kc_binned.hip).
+hipError_t launch_record_winners(uint32_t k_h, uint32_t n_regions, const uint32_t *off, const uint32_t *n,
                                  const uint32_t *word, const uint16_t *half, uint64_t c0,
                                  uint64_t len, uint64_t n_bases, const Workspace &W, hipStream_t s,
                                  Profiler *P);

@@ -148,3 +148,40 @@ def test_sparse_regions_with_own_records(n, hot, alpha, k_h, chunk, monkeypatch)
     for name, a, b in zip(["words", "distinct", "trust", "err"], g[:4], c[:4]):
         assert np.array_equal(np.asarray(a, dtype=np.uint64), np.asarray(b, dtype=np.uint64)), name
     assert g[4] == c[4]
+
+
+# Several hash functions leave up to k_h first-seen records a position: novel
+# reads over more than two of the winner passes' blocks of 2^19 positions, one-
+# and two-level lists, regions worked by counter and by entry
+@pytest.mark.parametrize("k_h,X,Y", [(2, 1009, 1013), (3, 1009, 1013), (8, 1009, 1013),
+                                     (2, 5779, 5813), (3, 5779, 5813)])
+def test_winner_records_of_several_hash_functions(k_h, X, Y, monkeypatch):
+    monkeypatch.setenv("KMERCO_WINNER_RECORDS", "1")
+    n, k = 3 * (1 << 19) + 12_345, 31
+    print(f"case records of several hash functions k_h={k_h} X={X} Y={Y}", flush=True)
+    rs = synth.random_reads(11 + k_h, n // 1000, 1000, 1000, k=k, p_n=0.0001)
+    reads = torch.from_numpy(rs.reads).cuda()
+    offs = torch.from_numpy(rs.offsets.view(np.int64)).cuda()
+    g = P.run_kmerco(reads, offs, k, 2, X, Y, 8, k_h)
+    c = oracle.run_kmerco(rs.reads, rs.offsets, k, 2, X, Y, 8, k_h)
+    for name, a, b in zip(["words", "distinct", "trust", "err"], g[:4], c[:4]):
+        assert np.array_equal(np.asarray(a, dtype=np.uint64), np.asarray(b, dtype=np.uint64)), name
+    assert g[4] == c[4]
+
+
+def test_winner_records_past_the_first_bucket(monkeypatch):
+    """More records than positions in a whole bucket of 2^24 positions, against the form that
+    sorts its records in the region pass."""
+    n, k = (1 << 24) + (1 << 21) + 777, 31
+    print(f"case records of two hash functions n={n}", flush=True)
+    rs = synth.random_reads(23, n // 1000, 1000, 1000, k=k)
+    reads = torch.from_numpy(rs.reads).cuda()
+    offs = torch.from_numpy(rs.offsets.view(np.int64)).cuda()
+    out = []
+    for forced in (False, True):
+        if forced:
+            monkeypatch.setenv("KMERCO_WINNER_RECORDS", "1")
+        out.append(P.run_kmerco(reads, offs, k, 2, 2707, 2711, 8, 2))
+    for a, b in zip(out[0][:4], out[1][:4]):
+        assert np.array_equal(np.asarray(a), np.asarray(b))
+    assert out[0][4] == out[1][4]
