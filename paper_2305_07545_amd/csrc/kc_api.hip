@@ -352,7 +352,9 @@ bool choose_plan(const kc_filter *f, uint64_t n_bases, kc::BinPlan &plan, uint64
         // entries of a chunk (positions x hash functions) index 32-bit offsets
         const uint64_t most = ((1ull << 32) - 1) / f->layout.k_h / kc::kTile * kc::kTile;
         const uint64_t pc = f->part_chunk < most ? f->part_chunk : most;
+        const uint64_t cap = kc::max_part_chunk();
         chunk = n_bases < pc ? n_bases : pc;
+        chunk = chunk < cap ? chunk : cap;
         return kc::bin_plan(f->F, chunk, plan, f->part_log, f->region_counters);
     }
     return true;

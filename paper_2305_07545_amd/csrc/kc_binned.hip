@@ -376,14 +376,17 @@ hipError_t launch_marks(const uint32_t *in, uint64_t room, uint32_t log, uint32_
 
 // Records mode, in which the winner passes distribute the regions' records:
 // for chunks of more than 2^28 positions, whose records the region pass cannot
-// sort by bucket itself (512 buckets of 2^19 positions);
-// KMERCO_WINNER_RECORDS=1 forces it for every chunk (tests).
-bool records_mode(uint64_t len) {
+// sort by bucket itself (512 buckets of 2^19 positions).
+// KMERCO_WINNER_RECORDS=1 forces it for every chunk, 0 turns it off: chunks
+// are 2^28 positions at most then (max_part_chunk).
+int records_from_env() {
     const char *e = std::getenv("KMERCO_WINNER_RECORDS");
-    if (e && *e && std::atoi(e) != 0)
-        return true;
-    return len > (1ull << 28);
+    return e && *e ? (std::atoi(e) != 0 ? 1 : 0) : -1;
 }
+
+bool records_mode(uint64_t len) { return records_from_env() == 1 || len > kBinChunk; }
+
+uint64_t max_part_chunk() { return records_from_env() == 0 ? kBinChunk : kPartChunk; }
 
 // The winner passes of one chunk [c0, c0 + len): its records, at most k_h a
 // position, region r's n_win[r] of them at offsets[r * off_stride] of the word

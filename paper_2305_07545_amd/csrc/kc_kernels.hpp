@@ -269,6 +269,8 @@ hipError_t launch_insert_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
 // partition size (regions) for countBFs of more than 2^part_log regions.
 bool bin_plan(const FilterArgs &F, uint64_t chunk_positions, BinPlan &B,
               uint32_t part_log = kPartLog, uint32_t region_counters = kRegionCounters);
+// Positions a partitioned chunk may have.
+uint64_t max_part_chunk();
 // Carried classification of a multi-chunk insert with one hash function:
 // the region passes of the chunks before the last keep their first-seen
 // records (Carry::kOut, chunk j of the carry arrays) instead of writing

@@ -122,3 +122,16 @@ def test_create_in_rejects_bad_arguments_on_the_host():
                             ctypes.byref(h)) == kmerco.KC_EINVAL
     assert lib.kc_create_in(ctypes.byref(L), w, 1, 0, ctypes.c_void_p(0x1010), 1 << 20, 0, None,
                             ctypes.byref(h)) == kmerco.KC_EINVAL
+
+
+def test_winner_records_turned_off_bound_the_chunk(monkeypatch):
+    """KMERCO_WINNER_RECORDS=0: partitioned chunks are small enough for the
+    region pass to sort its records itself, 2^28 positions."""
+    def scratch():
+        return P.scratch_bytes(31627, 31657, 2**30)
+    one_chunk = scratch()
+    monkeypatch.setenv("KMERCO_WINNER_RECORDS", "0")
+    off = scratch()
+    monkeypatch.delenv("KMERCO_WINNER_RECORDS")
+    monkeypatch.setenv("KMERCO_CHUNK_POSITIONS", str(2**28))
+    assert off == scratch() != one_chunk

@@ -185,3 +185,33 @@ def test_winner_records_past_the_first_bucket(monkeypatch):
     for a, b in zip(out[0][:4], out[1][:4]):
         assert np.array_equal(np.asarray(a), np.asarray(b))
     assert out[0][4] == out[1][4]
+
+
+@pytest.mark.parametrize("k_h", [1, 2])
+def test_a_chunk_beyond_the_sorted_records(k_h, monkeypatch):
+    """One chunk above 2^28 positions, which takes the winner passes unforced, against the same
+    insert with them turned off (two chunks, whose records the region pass sorts)."""
+    n, k = (1 << 28) + (1 << 20) + 4321, 31
+    print(f"case large chunk k_h={k_h} n={n}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17)
+    letters = torch.tensor(list(b"ACGT"), dtype=torch.uint8, device="cuda")
+    reads = torch.empty(n, dtype=torch.uint8, device="cuda")
+    for a in range(0, n, 1 << 26):
+        m = min(1 << 26, n - a)
+        reads[a:a + m] = letters[torch.randint(0, 4, (m,), generator=g, device="cuda")]
+    offs = torch.tensor([0, n // 3, n // 3 + 40, n], dtype=torch.int64, device="cuda")
+    out = []
+    for chunks in (1, 2):
+        if chunks == 2:
+            monkeypatch.setenv("KMERCO_WINNER_RECORDS", "0")
+        bf = P.CountBF(5779, 5813, 8, k_h)
+        assert bf.plan(n)["n_chunks"] == chunks
+        d, t, nt, e, ne = bf.insert_classify(reads, offs, k, 2)
+        bf.sync()
+        nd, nt, ne = int(bf.n_distinct.item()), int(nt.item()), int(ne.item())
+        out.append([bf.words.clone(), d[:nd].clone(), t[:nt].clone(), e[:ne].clone()])
+        bf.close()
+        del d, t, e
+    for name, a, b in zip(["words", "distinct", "trust", "err"], *out):
+        assert torch.equal(a, b), name
