@@ -215,3 +215,27 @@ def test_a_chunk_beyond_the_sorted_records(k_h, monkeypatch):
         del d, t, e
     for name, a, b in zip(["words", "distinct", "trust", "err"], *out):
         assert torch.equal(a, b), name
+
+
+def test_more_superblocks_than_threads():
+    """A region pass of more than 1024 superblocks takes their runs in turns: five regions in
+    partitions of four, whose superblocks are single blocks of 2^15 positions."""
+    n, k = 40_000_001, 31
+    print(f"case many superblocks n={n}", flush=True)
+    rs = reads_of(29, n // 8, k)
+    reads = torch.from_numpy(np.tile(rs.reads, 9)[:n].copy()).cuda()
+    offs = torch.tensor([0, n // 3, n // 3 + 40, n], dtype=torch.int64).cuda()
+    out = []
+    for env in ({"KMERCO_PART_LOG": "2"}, {"KMERCO_PATH": "direct"}):
+        with pytest.MonkeyPatch.context() as m:
+            for name, v in env.items():
+                m.setenv(name, v)
+            bf = P.CountBF(101, 101, 8, 1)
+            plan = bf.plan(n)
+            bf.close()
+            assert plan["path"] == ("direct" if out else "partitioned")
+            assert out or plan["n_regions"] == 5
+            out.append(P.run_kmerco(reads, offs, k, 2, 101, 101, 8, 1))
+    for name, a, b in zip(["words", "distinct", "trust", "err"], out[0][:4], out[1][:4]):
+        assert np.array_equal(np.asarray(a), np.asarray(b)), name
+    assert out[0][4] == out[1][4]
