@@ -99,7 +99,7 @@ def sha(t) -> str:
 
 def algorithmic_bytes(phase: str, n_bases: int, n_windows: int, n_distinct: int, k_h: int,
                       n_words: int, n_chunks: int = 1, partitioned: bool = False,
-                      binned: bool = True, key_bytes: int = 8, entry_bytes=None,
+                      key_bytes: int = 8, entry_bytes=None,
                       classified=None, carried=0) -> float:
     """Bytes one step's launches of `phase` must move by their definition
     (logical accesses, not cache lines), summed over the step's launches:
@@ -125,8 +125,8 @@ def algorithmic_bytes(phase: str, n_bases: int, n_windows: int, n_distinct: int,
         if carried:                  # carried records: 6 B written, then 2 B read + 2 B marked
             b += n_distinct * carried / n_bases * 10
         return b
-    if phase == "tile_count":        # flag byte per position; direct path: a bit, and the
-        return n_bases * (1.0 if binned else 0.625)  # packed input to count windows
+    if phase == "tile_count":        # batched form: flag byte per position
+        return n_bases
     if phase == "claim_increment":   # cell RMW + first-seen entry RMW per slot, packed input
         return n_windows * k_h * (16 + 8) + n_bases * 0.5
     if phase == "claim":             # cell read + entry RMW per slot

@@ -341,7 +341,7 @@ typedef enum {
     KC_PHASE_BIN_COUNT = 11,      /* binned path: hashing, entries sorted within blocks */
     KC_PHASE_BIN_BUCKET = 12,     /* batched form: entries grouped by region */
     KC_PHASE_REGION = 13,         /* binned path: LDS counting + first-seen per region */
-    KC_PHASE_TILE_COUNT = 14,     /* per-tile distinct / trustworthy / window counts */
+    KC_PHASE_TILE_COUNT = 14,     /* batched form: per-tile distinct / trustworthy counts */
     KC_PHASE_BIN_REGION = 15,     /* binned path: runs of the blocks arranged by region */
     KC_PHASE_BIN_PART = 16,       /* partitioned path: hashing, entries sorted by bucket */
     KC_PHASE_PART_COUNT = 17,     /* partitioned path: buckets counted and sorted by region */

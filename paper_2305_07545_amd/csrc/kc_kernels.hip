@@ -156,16 +156,24 @@ __global__ void __launch_bounds__(kWG) k_insert_phase(FilterArgs F, ReadsArgs R,
     }
 }
 
-// (the chunk's distinct bits are written whole, a wavefront's 64 positions at
-// a time)
+// The chunk's distinct bits, written whole, a wavefront's 64 positions at a
+// time; the tile's count of them, and of its valid windows, which are known
+// here: a pass of its own took 39 us over 3 M positions to test them again,
+// beside 41 here.  (The scan adds the tiles up: one atomic a tile took 80 of
+// 1680 us over 30 M positions.)
 __global__ void __launch_bounds__(kWG) k_resolve(FilterArgs F, ReadsArgs R, uint64_t c0,
-                                                 uint64_t c1, uint32_t *__restrict__ dbits) {
+                                                 uint64_t c1, uint32_t *__restrict__ dbits,
+                                                 uint32_t *__restrict__ tile_d,
+                                                 uint32_t *__restrict__ tile_v) {
+    __shared__ uint32_t s_count[kWG / 64];  // valid << 16 | distinct
     const uint64_t tile0 = c0 + (uint64_t)blockIdx.x * kTile;
+    uint32_t count = 0;  // of the wavefront
 #pragma unroll 1
     for (int j = 0; j < kTile / kWG; j++) {
         uint64_t p = tile0 + (uint64_t)j * kWG + threadIdx.x;
         bool win = false;
-        if (p < c1 && window_valid(R, p)) {
+        const bool valid = p < c1 && window_valid(R, p);
+        if (valid) {
             uint64_t fwd = window_key(R.codes, p, R.k);
             Canon c = canonical(fwd, R.k);
             uint32_t t = (uint32_t)(p - c0);
@@ -182,8 +190,19 @@ __global__ void __launch_bounds__(kWG) k_resolve(FilterArgs F, ReadsArgs R, uint
             }
         }
         const uint64_t m = __ballot(win);
+        count += (uint32_t)__popcll(__ballot(valid)) << 16 | (uint32_t)__popcll(m);
         if ((threadIdx.x & 63u) == 0)
             *reinterpret_cast<uint64_t *>(dbits + (p >> 5)) = m;
+    }
+    if ((threadIdx.x & 63u) == 0)
+        s_count[threadIdx.x >> 6] = count;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        count = 0;
+        for (int w = 0; w < kWG / 64; w++)
+            count += s_count[w];
+        tile_d[tile0 / kTile] = count & 0xFFFFu;
+        tile_v[tile0 / kTile] = count >> 16;
     }
 }
 
@@ -192,35 +211,6 @@ __global__ void __launch_bounds__(kWG) k_resolve(FilterArgs F, ReadsArgs R, uint
 // trustworthy / erroneous split): one distinct bit per position, and one
 // trustworthy bit (meaningful where the distinct bit is set)
 // ---------------------------------------------------------------------------
-// Direct path: per tile, distinct bits and (added up for the call) valid
-// windows.  One wavefront per tile.
-__global__ void __launch_bounds__(kWG) k_bits_count(ReadsArgs R, const uint32_t *__restrict__ dbits,
-                                                    uint64_t n_tiles, uint32_t *__restrict__ tile_d,
-                                                    unsigned long long *__restrict__ n_valid) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t n_waves = (uint64_t)gridDim.x * (kWG / 64);
-    uint64_t nv = 0;  // the same on every lane
-    for (uint64_t tile = (uint64_t)blockIdx.x * (kWG / 64) + wave; tile < n_tiles;
-         tile += n_waves) {
-        uint32_t nd = lane < kTile / 32 ? (uint32_t)__popc(dbits[tile * (kTile / 32) + lane]) : 0u;
-#pragma unroll 1
-        for (int j = 0; j < kTile / 64; j++) {
-            const uint64_t pb = tile * kTile + 64u * (uint64_t)j;
-            WaveWords w;
-            wave_load(R, pb, w);
-            uint64_t fwd;
-            nv += (uint32_t)__popcll(__ballot(wave_window(w, pb, lane, R.k, R.n_bases, fwd)));
-        }
-        for (uint32_t d = 32; d >= 1; d >>= 1)
-            nd += __shfl_down(nd, d, 64);
-        if (lane == 0)
-            tile_d[tile] = nd;
-    }
-    if (lane == 0 && nv)
-        atomicAdd(n_valid, (unsigned long long)nv);
-}
-
 // Batched form: per tile, distinct flags (bit 0 of a flag byte) and
 // trustworthy flags (bit 1).  One wavefront per tile, 16 flag bytes per lane.
 __global__ void __launch_bounds__(kWG) k_tile_count(const uint8_t *__restrict__ flags,
@@ -686,8 +676,8 @@ hipError_t launch_insert_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
     }
     if (e != hipSuccess)
         return e;
-    return launch(P, kPhResolve, k_resolve, grid, block, s, F, R, c0, c1,
-                  distinct_bits(W));
+    return launch(P, kPhResolve, k_resolve, grid, block, s, F, R, c0, c1, distinct_bits(W),
+                  W.tile_a, W.tile_c);
 }
 
 hipError_t launch_tile_count(const Workspace &W, uint64_t n_tiles, hipStream_t s) {
@@ -700,29 +690,24 @@ hipError_t launch_tile_count(const Workspace &W, uint64_t n_tiles, hipStream_t s
 hipError_t launch_distinct(const ReadsArgs &R, const Workspace &W, uint64_t *distinct,
                            uint64_t cap_d, uint64_t *n_distinct, uint64_t *n_windows,
                            uint64_t *trust, uint64_t *n_trust, uint64_t *err, uint64_t *n_err,
-                           uint64_t cap_te, uint32_t *status, bool counted, hipStream_t s,
+                           uint64_t cap_te, uint32_t *status, bool binned, hipStream_t s,
                            Profiler *P) {
     const uint64_t n_tiles = tiles(R.n_bases);
     const bool split = trust != nullptr;
     const dim3 grid((unsigned)(n_tiles < (uint64_t)kTileGrid ? n_tiles : kTileGrid));
     const uint32_t *dbits = distinct_bits(W), *tbits = trust_bits(W, R.n_bases);
-    hipError_t e = hipSuccess;
-    if (!counted)
-        e = launch(P, kPhTileCount, k_bits_count, grid, dim3(kWG), s, R, dbits, n_tiles, W.tile_a,
-                   (unsigned long long *)(W.totals + 5));
     if (P)
         P->begin(kPhScan, s);
-    if (e == hipSuccess) {
-        TileScan T{};
-        T.n_distinct = n_distinct;
-        T.n_windows = n_windows;
-        T.n_trust = split ? n_trust : nullptr;
-        T.n_err = n_err;
-        T.cap_d = cap_d;
-        T.cap_te = cap_te;
-        T.status = status;
-        e = launch_tile_scan(W, n_tiles, split, T, s);
-    }
+    TileScan T{};
+    T.n_distinct = n_distinct;
+    T.n_windows = n_windows;
+    T.n_trust = split ? n_trust : nullptr;
+    T.n_err = n_err;
+    T.cap_d = cap_d;
+    T.cap_te = cap_te;
+    T.status = status;
+    T.tile_v = binned ? nullptr : W.tile_c;
+    hipError_t e = launch_tile_scan(W, n_tiles, split, T, s);
     if (P)
         P->end(s);
     if (e == hipSuccess && R.k > 32)

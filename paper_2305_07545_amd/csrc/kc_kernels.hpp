@@ -234,11 +234,13 @@ inline CallState call_state(const Workspace &W, uint64_t n_bases) {
 hipError_t launch_clear_call(uint64_t n_bases, const Workspace &W, hipStream_t s);
 
 // Exclusive sums of the tiles' distinct counts (tile_a, onto *n_distinct) and
-// trustworthy counts (tile_b) into off_a and off_b, and the call's counters.
+// trustworthy counts (tile_b) into off_a and off_b, and the call's counters;
+// tile_v: the tiles' valid windows, where they are not in W.totals[5].
 struct TileScan {
     uint64_t *n_distinct, *n_windows, *n_trust, *n_err;
     uint64_t cap_d, cap_te;
     uint32_t *status;
+    const uint32_t *tile_v;
 };
 hipError_t launch_tile_scan(const Workspace &W, uint64_t n_tiles, bool split, const TileScan &T,
                             hipStream_t s);
@@ -305,12 +307,13 @@ hipError_t launch_binned_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
 hipError_t launch_carried_winners(const BinPlan &plan, const Carry &carry, uint32_t j, uint64_t c0,
                                   uint64_t len, uint64_t n_bases, const Workspace &W, hipStream_t s,
                                   Profiler *P);
-// counted: the insert passes already wrote the tiles' counts and added this
-// call's valid windows to W.totals[5] (else a pass over the bits does)
+// The insert passes have written the tiles' counts of distinct windows; this
+// call's valid windows they have added to W.totals[5] (binned) or counted by
+// tile (W.tile_c).
 hipError_t launch_distinct(const ReadsArgs &R, const Workspace &W, uint64_t *distinct,
                            uint64_t cap_d, uint64_t *n_distinct, uint64_t *n_windows,
                            uint64_t *trust, uint64_t *n_trust, uint64_t *err, uint64_t *n_err,
-                           uint64_t cap_te, uint32_t *status, bool counted, hipStream_t s,
+                           uint64_t cap_te, uint32_t *status, bool binned, hipStream_t s,
                            Profiler *P);
 hipError_t launch_classify(const FilterArgs &F, const uint64_t *keys, const uint64_t *n_keys,
                            const uint64_t *key_base, uint64_t grid_cap, uint64_t cap,

@@ -208,6 +208,16 @@ k_tile_scan(const uint32_t *__restrict__ tile_d, const uint32_t *__restrict__ ti
         v[u] = t < n_tiles ? (uint64_t)tile_d[t] | (split ? (uint64_t)tile_t[t] << 32 : 0ull) : 0ull;
         sum += v[u];
     }
+    if (T.tile_v && T.n_windows) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int u = 0; u < kPer; u++)
+            w += t0 + u < n_tiles ? T.tile_v[t0 + u] : 0u;
+        for (uint32_t d = 32; d >= 1; d >>= 1)
+            w += __shfl_xor(w, d, 64);
+        if (lane == 0 && w)
+            atomicAdd((unsigned long long *)T.n_windows, (unsigned long long)w);
+    }
     uint64_t total;
     const uint64_t before = wg_exclusive_sum<uint64_t>(sum, s_wave, total);
     const uint64_t own_d = total & 0xFFFFFFFFull, own_t = total >> 32;
@@ -243,7 +253,7 @@ k_tile_scan(const uint32_t *__restrict__ tile_d, const uint32_t *__restrict__ ti
         const uint64_t nd = s_base[0] + own_d, nt = s_base[1] + own_t;
         totals[3] = call_base;
         *T.n_distinct = call_base + nd;
-        if (T.n_windows)
+        if (T.n_windows && !T.tile_v)
             *T.n_windows += totals[5];
         bool over = call_base + nd > T.cap_d;
         if (T.n_trust) {
