@@ -296,6 +296,20 @@ struct LaneRuns {
     }
 };
 
+// The share `part` (of 2^split) of run [s, e): at least kPart entries, so that a
+// short run stays whole.  With eight superblocks or fewer, most of the region
+// pass's 16 wavefronts would have no run, and one a region's whole list: a
+// k-mer repeated over 94% of 3 M bases, 17.2 -> 2.4 ms (with the lanes of one
+// counter counted together, here and in the second level).
+constexpr uint32_t kPart = 128;
+__device__ __forceinline__ void share_run(uint32_t s, uint32_t e, uint32_t part, uint32_t split,
+                                          LaneRuns &R) {
+    const uint32_t len = e - s, piece = (len + (1u << split) - 1u) >> split;
+    const uint32_t each = piece > kPart ? piece : kPart;
+    const uint32_t lo = part * each, hi = lo + each;
+    R.set(s + (lo < len ? lo : len), s + (hi < len ? hi : len));
+}
+
 // Second level: the entries of bucket b in superblock sb (`super` blocks) ->
 // sorted by region, entries of 5 bytes again (the counter and the position
 // within the superblock).  Their place in the list needs no scan: the
@@ -389,6 +403,20 @@ k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
     auto sub_of = [](uint32_t w, uint32_t h) -> uint32_t {
         return (w >> kSubShift) | (h << (32 - kSubShift));
     };
+    // a place of region `sub` for each lane here: the lanes of the first one's
+    // region, often all of them in a bucket that holds this many, take theirs
+    // together
+    auto take = [&](uint32_t sub) -> uint32_t {
+        const uint32_t s0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)sub);
+        const uint64_t same = __ballot(sub == s0);
+        const uint32_t i = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+        uint32_t at = 0;
+        if (sub != s0 || i == 0)
+            at = atomicAdd(&s_cursor[sub], sub == s0 ? (uint32_t)__popcll(same) : 1u);
+        const uint32_t at0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        return sub == s0 ? at0 + i : at;
+    };
     __syncthreads();
     uint32_t rank[kGroups * 2];  // of two entries a word: read for buckets of at most kMergeTile
 #pragma unroll
@@ -398,7 +426,7 @@ k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
         load(w0);
         each(w0, [&](int, uint32_t w, uint32_t h, uint32_t, bool in) {
             if (in)
-                atomicAdd(&s_cursor[sub_of(w, h)], 1u);
+                take(sub_of(w, h));
         });
     }
     load(0);
@@ -462,7 +490,7 @@ k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
             load(w0);
             each(w0, [&](int, uint32_t w, uint32_t h, uint32_t k, bool in) {
                 if (in) {
-                    const uint32_t at = atomicAdd(&s_cursor[sub_of(w, h)], 1u);
+                    const uint32_t at = take(sub_of(w, h));
                     o[at] = merged(w, k, oh[at]);
                 }
             });
@@ -875,8 +903,10 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
         constexpr uint32_t kSet = kWaves * 64;
         const uint32_t *__restrict__ starts = (const uint32_t *)table;
         uint32_t bs, be;  // the lane's run: its entries in the list
+        // run x of a set of kSet: superblock x >> split, that share of it
+        const uint32_t part = wave & ((1u << B.split) - 1u);
         auto bounds = [&](uint32_t r, uint32_t b0) {
-            const uint32_t b = b0 + lane * kWaves + wave;
+            const uint32_t b = (b0 + lane * kWaves + wave) >> B.split;
             const bool in = b < B.n_super && r < P.n_regions;
             const uint32_t *t = starts + (in ? (uint64_t)b * (P.n_regions + 1u) + r : 0ull);
             bs = t[0];
@@ -905,7 +935,7 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
             for (int c = 0; c < kGroups; c++) {
                 const uint32_t m = which[c];
                 if (m >> 28) {
-                    const uint32_t b = b0 + (m & 63u) * kWaves + wave;
+                    const uint32_t b = (b0 + (m & 63u) * kWaves + wave) >> B.split;
                     const uint32_t tb = (b * B.super) << B.pos_log;
                     if ((m >> 28) & 1u)
                         count(x[c].x, h[c] & 0xFFu, tb);
@@ -919,7 +949,7 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
             }
         };
         bounds(r, 0);
-        R.set(bs, be);
+        share_run(bs, be, part, B.split, R);
         load(0);
         bounds(r + grid, 0);
         for (; r < P.n_regions; r += grid) {
@@ -931,7 +961,7 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
             }
             for (uint32_t b0 = kSet; b0 < B.n_super; b0 += kSet) {
                 bounds(r, b0);
-                R.set(bs, be);
+                share_run(bs, be, part, B.split, R);
                 mine += R.e - R.s;
                 for (uint32_t w0 = 0; w0 < R.n; w0 += 64u * kGroups) {
                     load(w0);
@@ -940,7 +970,7 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
                 if (b0 + kSet >= B.n_super)
                     bounds(r + grid, 0);
             }
-            R.set(bs, be);
+            share_run(bs, be, part, B.split, R);
             load(0);
             bounds(r + 2u * grid, 0);
             finish(
@@ -1086,8 +1116,9 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         return in ? *reinterpret_cast<const uint32_t *>(F.words + w) : 0u;
     };
     uint32_t bs, be;  // the lane's run: its entries in the list
+    const uint32_t part = wave & ((1u << B.split) - 1u);
     auto bounds = [&](uint32_t r) {
-        const uint32_t b = lane * kWaves + wave;
+        const uint32_t b = (lane * kWaves + wave) >> B.split;
         const bool in = b < B.n_super && r < P.n_regions;
         const uint32_t *t = starts + (in ? (uint64_t)b * (P.n_regions + 1u) + r : 0ull);
         bs = t[0];
@@ -1118,7 +1149,7 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         for (int c = 0; c < kGroups; c++)
             if (w0 + 64u * c < R.n) {
                 const uint32_t m = H.which[c];
-                const uint32_t tb = (((m & 63u) * kWaves + wave) * B.super) << B.pos_log;
+                const uint32_t tb = ((((m & 63u) * kWaves + wave) >> B.split) * B.super) << B.pos_log;
                 const uint32_t e[4] = {H.x[c].x, H.x[c].y, H.x[c].z, H.x[c].w};
 #pragma unroll
                 for (int q = 0; q < 4; q++)
@@ -1130,6 +1161,19 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
     };
     auto count = [&](int, uint32_t local, uint32_t t) {
         atomicAdd(&hits[local], 1u);
+        if (t < first[local])
+            atomicMin(&first[local], t);
+    };
+    // of a region with more entries than are held, many of them likely of one
+    // counter: the lanes of the first one's counter count together
+    auto count_many = [&](int, uint32_t local, uint32_t t) {
+        const uint32_t l0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)local);
+        const uint64_t same = __ballot(local == l0);
+        const bool led = local == l0 &&
+                         __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u)) != 0;
+        if (!led)
+            atomicAdd(&hits[local], local == l0 ? (uint32_t)__popcll(same) : 1u);
         if (t < first[local])
             atomicMin(&first[local], t);
     };
@@ -1159,7 +1203,7 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
     LaneRuns R;
     load_cells(r, cell);
     bounds(r);
-    R.set(bs, be);
+    share_run(bs, be, part, B.split, R);
     load(R, 0, H);
     bounds(r + grid);
     uint32_t line = touch(r + grid);
@@ -1180,7 +1224,7 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         LaneRuns Rn;
         Held Hn;
         uint64_t celln[kCells];
-        Rn.set(bs, be);
+        share_run(bs, be, part, B.split, Rn);
         load(Rn, 0, Hn);
         load_cells(r + grid, celln);
         bounds(r + 2u * grid);
@@ -1191,7 +1235,7 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         for (uint32_t w0 = kStep; w0 < R.n; w0 += kStep) {
             Held X;
             load(R, w0, X);
-            each(R, w0, X, count);
+            each(R, w0, X, count_many);
         }
         if constexpr (kOwn) {
             const uint32_t n = wave_inclusive(R.e - R.s);
@@ -1237,8 +1281,15 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
                 const uint32_t mark = update(local, t);
                 if (mark && kOwn)
                     put(s_base + atomicAdd(&s_n, 1u), t, carry_out ? local : mark);
-                else if (mark)
-                    flat[atomicAdd(cursor, 1u)] = t | (mark << 30);
+                else if (mark) {  // one atomic for the lanes that are here
+                    const uint64_t m = __ballot(true);
+                    const uint32_t i = __builtin_amdgcn_mbcnt_hi(
+                        (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                    uint32_t at = 0;
+                    if (i == 0)
+                        at = atomicAdd(cursor, (uint32_t)__popcll(m));
+                    flat[(uint32_t)__builtin_amdgcn_readfirstlane((int)at) + i] = t | (mark << 30);
+                }
             });
         }
         const uint32_t mine = (uint32_t)__popc(won), incl = wave_inclusive(mine);
@@ -1431,6 +1482,8 @@ bool block_plan(const BinPlan &plan, uint32_t k_h, uint64_t len, BlockPlan &B) {
     m = m < 1u ? 1u : (m > most ? most : m);
     B.super = m < B.n_blocks ? m : B.n_blocks;
     B.n_super = (B.n_blocks + B.super - 1u) / B.super;
+    while ((B.n_super << (B.split + 1u)) <= (uint32_t)kRegionWG / 64u)
+        B.split++;
     return true;
 }
 

@@ -51,6 +51,7 @@ struct BlockPlan {
     uint32_t sub_log;
     uint32_t super;
     uint32_t n_super;   // superblocks
+    uint32_t split;     // log2(wavefronts of the region pass that share a superblock's run)
 };
 
 // The blocks of `len` positions (false: none, or more buckets than kMaxBins).

@@ -239,3 +239,33 @@ def test_more_superblocks_than_threads():
     for name, a, b in zip(["words", "distinct", "trust", "err"], out[0][:4], out[1][:4]):
         assert np.array_equal(np.asarray(a), np.asarray(b)), name
     assert out[0][4] == out[1][4]
+
+
+def check_hot(n, hot, X, Y, k_h, what):
+    print(f"case {what} n={n} hot={hot} k_h={k_h}", flush=True)
+    rs = reads_of(31, n, 31)
+    rs.reads[n // 3:n // 3 + hot] = ord("A")
+    reads = torch.from_numpy(rs.reads).cuda()
+    offs = torch.from_numpy(rs.offsets.view(np.int64)).cuda()
+    g = P.run_kmerco(reads, offs, 31, 2, X, Y, 8, k_h)
+    c = oracle.run_kmerco(rs.reads, rs.offsets, 31, 2, X, Y, 8, k_h)
+    for name, a, b in zip(["words", "distinct", "trust", "err"], g[:4], c[:4]):
+        assert np.array_equal(np.asarray(a, dtype=np.uint64), np.asarray(b, dtype=np.uint64)), name
+    assert g[4] == c[4]
+
+
+# Up to eight superblocks share the region pass's 16 wavefronts: five regions,
+# superblocks of 13 blocks of 4096 positions, so many of them and a tail
+@pytest.mark.parametrize("supers", [1, 2, 3, 4, 5, 8, 9, 16, 17])
+@pytest.mark.parametrize("hot", [0, 30_000])
+def test_wavefronts_share_a_superblock(supers, hot, monkeypatch):
+    monkeypatch.setenv("KMERCO_PART_LOG", "2")
+    check_hot(13 * 4096 * supers - 1234, hot, 101, 101, 1, f"{supers} superblocks")
+
+
+# The same for regions worked by entry (superblocks of 2.75 M positions), with
+# regions and buckets of more entries than are held, mostly of one counter
+@pytest.mark.parametrize("n,hot,k_h", [(300_000, 250_000, 1), (300_000, 250_000, 3),
+                                       (3_000_000, 1_000_000, 1), (6_000_000, 300_000, 1)])
+def test_wavefronts_share_a_superblock_by_entry(n, hot, k_h):
+    check_hot(n, hot, 5779, 5813, k_h, "by entry")
