@@ -483,7 +483,7 @@ k_merge(BlockPlan B, uint32_t n_regions, const uint32_t *__restrict__ list,
         high = (uint8_t)(t >> (32 - kLocalBits));
         return (w & ((1u << kLocalBits) - 1u)) | (t << kLocalBits);
     };
-    if (!held) {
+    if (__builtin_expect(!held, 0)) {  // (else the registers of both paths spill)
         uint32_t *__restrict__ o = out + base;
         uint8_t *__restrict__ oh = out_hi + base;
         for (uint32_t w0 = 0; w0 < R.n; w0 += kStep) {
