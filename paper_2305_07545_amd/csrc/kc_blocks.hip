@@ -1067,26 +1067,47 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
 // regions: 1.67 -> 0.97 ms), bound by memory latency behind 32 KB of cells and
 // 20 KB of entries and records a region.  Two barriers a region here, and what the next region needs
 // (cells, entries; bounds of the one after) is requested before its entries
-// are counted.  The records' room is exact, so that they lie dense in `flat`:
-// asked for when a region's records are counted, and taken after the next
-// region's update, the records held in registers until then.
+// are counted.
 //
+// kRecords: where the records go.
+// kFlat: dense in `flat`, their room asked for when a region's records are
+// counted, and taken after the next region's update, the records held in
+// registers until then.
+// kFew (regions of kFewEntries entries on average): dense in `flat`, where
+// the records of many regions leave together from LDS.  The room comes from
+// one address, at 4.5 ns an atomic: one a region cost 74 of 204 us over 16 K
+// regions of 15 new k-mers, now 173; over 44 K regions of 450, kFlat takes 730
+// us and this 750.
 // kOwn (chunks above 2^28 positions, carried chunks): the records go to room of
 // the region's own for each of its entries, as k_region_runs' do.
-template <int kCells, bool kOwn>
+enum RecordForm { kOwn, kFlat, kFew };
+constexpr uint64_t kFewEntries = 128;
+
+template <int kCells, RecordForm kRecords>
 __global__ void __launch_bounds__(kRegionWG)
 k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict__ list,
                 const uint8_t *__restrict__ list_hi, const uint32_t *__restrict__ starts,
                 int classify, uint32_t tau, uint32_t *__restrict__ cursor,
                 uint32_t *__restrict__ flat, RecordSpace own, Carry C) {
     constexpr uint32_t kWaves = kRegionWG / 64;
+    constexpr bool kOwn = kRecords == RecordForm::kOwn;
     // larger chunks' runs are shorter: more groups of fewer entries
     constexpr int kGroups = kOwn ? 3 : 2, kHeld = 4 * kGroups;
     constexpr uint32_t kStep = 64u * kGroups;
     __shared__ uint32_t hits[kRegionCounters];
     __shared__ uint32_t first[kRegionCounters];
     __shared__ unsigned long long s_cell[kCells * kRegionWG];
-    __shared__ uint32_t s_n, s_base;
+    // records that wait in LDS: all of a region of up to kBatch (kFew), and those
+    // of entries that are not held
+    constexpr uint32_t kRecRoom = kOwn ? 1 : 2048, kBatch = 128;
+    __shared__ uint32_t s_rec[kRecRoom];
+    // by the region's parity: records of held entries, of others (!kOwn), and
+    // the room for this region's (!kOwn: the region before's), read at once
+    struct Tally {
+        uint32_t n, more, base, pad;
+    };
+    __shared__ __align__(16) Tally s_tally[2];
+    __shared__ uint32_t s_flush;
     __shared__ uint32_t s_total[2], s_over[2];  // kOwn, by the region's parity
     const uint32_t lane = threadIdx.x & 63u, wave = wave_id(), grid = gridDim.x;
     const uint32_t shift = P.region_shift, S = 1u << shift;
@@ -1097,7 +1118,8 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         first[i] = kIdle;
     }
     if (threadIdx.x == 0)
-        s_n = s_total[0] = s_total[1] = s_over[0] = s_over[1] = 0;
+        s_tally[0].n = s_tally[1].n = s_tally[0].more = s_tally[1].more = s_total[0] =
+            s_total[1] = s_over[0] = s_over[1] = 0;
     const bool carry_out = kOwn && C.mode == Carry::kOut;
     const bool carry_in = kOwn && C.mode == Carry::kIn && C.n_prev > 0;
     auto load_cells = [&](uint32_t r, uint64_t(&cell)[kCells]) {
@@ -1208,11 +1230,26 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
     bounds(r + grid);
     uint32_t line = touch(r + grid);
     uint32_t rec[kHeld], has = 0, at = 0, got = 0;  // records waiting for their room
+    uint32_t fill = 0;                              // records in s_rec (uniform)
     auto store_records = [&](uint32_t base) {
+        // (16 wavefronts share four instruction issuers: what a wavefront
+        // without a record would step over lane by lane, it skips)
+        if (kRecords == kFew && __ballot(has != 0) == 0)
+            return;
 #pragma unroll
         for (int j = 0; j < kHeld; j++)
             if ((has >> j) & 1u)
                 flat[base + at + (uint32_t)__popc(has & ((1u << j) - 1u))] = rec[j];
+    };
+    auto flush = [&]() {  // s_rec -> flat, by all threads
+        if (threadIdx.x == 0)
+            s_flush = atomicAdd(cursor, fill);
+        __syncthreads();
+        const uint32_t base = s_flush;
+        for (uint32_t i = threadIdx.x; i < fill; i += kRegionWG)
+            flat[base + i] = s_rec[i];
+        __syncthreads();
+        fill = 0;
     };
     // kOwn: the region's record `slot`, of position t and mark or counter
     auto put = [&](uint32_t slot, uint32_t t, uint32_t half) {
@@ -1246,6 +1283,8 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
             }
         }
         __syncthreads();  // counted
+        if (threadIdx.x == 0)  // the region before's, read by every thread
+            s_tally[turn ^ 1u].n = s_tally[turn ^ 1u].more = 0;
         if constexpr (kOwn) {  // room for a record of every entry
             got = 0;
             if (threadIdx.x == 0 && s_total[turn])
@@ -1271,32 +1310,48 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         if constexpr (kOwn)
             if (s_over[turn]) {
                 if (threadIdx.x == 0)
-                    s_base = got;
+                    s_tally[turn].base = got;
                 __syncthreads();
             }
         for (uint32_t w0 = kStep; w0 < R.n; w0 += kStep) {
-            // more than the registers hold: each record's room by itself
+            // more than the registers hold
             load(R, w0, H);
             each(R, w0, H, [&](int, uint32_t local, uint32_t t) {
                 const uint32_t mark = update(local, t);
                 if (mark && kOwn)
-                    put(s_base + atomicAdd(&s_n, 1u), t, carry_out ? local : mark);
+                    put(s_tally[turn].base + atomicAdd(&s_tally[turn].n, 1u), t,
+                        carry_out ? local : mark);
                 else if (mark) {  // one atomic for the lanes that are here
                     const uint64_t m = __ballot(true);
                     const uint32_t i = __builtin_amdgcn_mbcnt_hi(
                         (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                    const uint32_t n = (uint32_t)__popcll(m), x = t | (mark << 30);
                     uint32_t at = 0;
                     if (i == 0)
-                        at = atomicAdd(cursor, (uint32_t)__popcll(m));
-                    flat[(uint32_t)__builtin_amdgcn_readfirstlane((int)at) + i] = t | (mark << 30);
+                        at = atomicAdd(&s_tally[turn].more, n);
+                    at = fill + (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+                    const uint32_t left = at < kRecRoom ? kRecRoom - at : 0u;
+                    const uint32_t fit = n < left ? n : left;
+                    if (i < fit)
+                        s_rec[at + i] = x;
+                    if (fit < n) {
+                        if (i == 0)
+                            at = atomicAdd(cursor, n - fit);
+                        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+                        if (i >= fit)
+                            flat[at + i - fit] = x;
+                    }
                 }
             });
         }
-        const uint32_t mine = (uint32_t)__popc(won), incl = wave_inclusive(mine);
+        const bool some = __ballot(won != 0) != 0;  // uniform
         uint32_t place = 0;
-        if (lane == 63 && incl)
-            place = atomicAdd(&s_n, incl);
-        place = (uint32_t)__builtin_amdgcn_readlane((int)place, 63) + incl - mine;
+        if (some) {
+            const uint32_t mine = (uint32_t)__popc(won), incl = wave_inclusive(mine);
+            if (lane == 63)
+                place = atomicAdd(&s_tally[turn].n, incl);
+            place = (uint32_t)__builtin_amdgcn_readlane((int)place, 63) + incl - mine;
+        }
         // every load in flight is taken in before the first store
 #pragma unroll
         for (int c = 0; c < kGroups; c++)
@@ -1309,19 +1364,19 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         asm volatile("" : "+v"(bs), "+v"(be), "+v"(line));
         line = touch(r + 2u * grid);
         if (threadIdx.x == 0)
-            s_base = got;
+            s_tally[turn].base = got;
         __syncthreads();  // updated, counters clean
-        const uint32_t base = s_base;
+        const uint4 tally = *reinterpret_cast<const uint4 *>(&s_tally[turn]);
+        const uint32_t base = tally.z;
         if (threadIdx.x == 0) {
             if constexpr (kOwn) {
                 const uint64_t x = carry_out ? (uint64_t)C.chunk * C.stride + r : r;
                 (carry_out ? C.off : own.off)[x] = base;
-                (carry_out ? C.n : own.n)[x] = s_n;
+                (carry_out ? C.n : own.n)[x] = tally.x;
                 s_total[turn] = s_over[turn] = 0;
-            } else {
-                got = s_n ? atomicAdd(cursor, s_n) : 0u;
+            } else if (tally.x > (kRecords == kFew ? kBatch : 0u)) {
+                got = atomicAdd(cursor, tally.x);
             }
-            s_n = 0;
         }
         const uint64_t wbase = (uint64_t)r << shift;
 #pragma unroll
@@ -1334,21 +1389,39 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         }
         if constexpr (kOwn) {
             uint32_t slot = base + place;
+            if (some)
 #pragma unroll
-            for (int j = 0; j < kHeld; j++)
-                if ((won >> j) & 1u)
-                    put(slot++, fresh[j], (halves[j / 2] >> (16 * (j % 2))) & 0xFFFFu);
+                for (int j = 0; j < kHeld; j++)
+                    if ((won >> j) & 1u)
+                        put(slot++, fresh[j], (halves[j / 2] >> (16 * (j % 2))) & 0xFFFFu);
             if (carry_in) {
                 mark_carried(F, shift, C, r, s_cell, tau);
                 __syncthreads();  // the cells are rewritten by the next region
             }
         } else {
             store_records(base);
+            const uint32_t more = (uint32_t)__builtin_amdgcn_readfirstlane((int)tally.y);
+            fill = fill + more < kRecRoom ? fill + more : kRecRoom;
+            const uint32_t n =
+                kRecords == kFew ? (uint32_t)__builtin_amdgcn_readfirstlane((int)tally.x) : 0u;
+            if (__builtin_expect(fill + (kRecords == kFew ? kBatch : kRecRoom / 2) > kRecRoom, 0))
+                flush();
+            if (kRecords == kFew && n <= kBatch) {
+                has = 0;
+                place += fill;
+                if (some)
 #pragma unroll
-            for (int j = 0; j < kHeld; j++)
-                rec[j] = fresh[j];
-            has = won;
-            at = place;
+                    for (int j = 0; j < kHeld; j++)
+                        if ((won >> j) & 1u)
+                            s_rec[place++] = fresh[j];
+                fill += n;
+            } else {
+#pragma unroll
+                for (int j = 0; j < kHeld; j++)
+                    rec[j] = fresh[j];
+                has = won;
+                at = place;
+            }
         }
         R = Rn;
         H = Hn;
@@ -1356,9 +1429,11 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
     if constexpr (!kOwn) {
         __syncthreads();
         if (threadIdx.x == 0)
-            s_base = got;
+            s_tally[0].base = got;
         __syncthreads();
-        store_records(s_base);
+        store_records(s_tally[0].base);
+        if (fill)
+            flush();
     }
 }
 
@@ -1607,8 +1682,11 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
         P->begin(kPhRegion, s);
     const uint32_t grid = region_grid(plan.n_regions, plan.region_counters);
     if (sparse) {
-        hipLaunchKernelGGL((plan.region_shift == 10 ? k_region_sparse<1, false>
-                                                    : k_region_sparse<2, false>),
+        const bool few = len * F.k_h <= kFewEntries * plan.n_regions;
+        hipLaunchKernelGGL((few ? (plan.region_shift == 10 ? k_region_sparse<1, kFew>
+                                                           : k_region_sparse<2, kFew>)
+                                : (plan.region_shift == 10 ? k_region_sparse<1, kFlat>
+                                                           : k_region_sparse<2, kFlat>)),
                            dim3(grid), dim3(kRegionWG), 0, s, F, plan, B, (const uint32_t *)merged,
                            (const uint8_t *)merged_hi, (const uint32_t *)starts, classify ? 1 : 0,
                            tau, rec.cursor, rec.word + len * F.k_h, rec, carry);
@@ -1628,8 +1706,8 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
         return e;
     }
     if (by_entry && own) {
-        hipLaunchKernelGGL((plan.region_shift == 10 ? k_region_sparse<1, true>
-                                                    : k_region_sparse<2, true>),
+        hipLaunchKernelGGL((plan.region_shift == 10 ? k_region_sparse<1, kOwn>
+                                                    : k_region_sparse<2, kOwn>),
                            dim3(grid), dim3(kRegionWG), 0, s, F, plan, B, (const uint32_t *)merged,
                            (const uint8_t *)merged_hi, (const uint32_t *)starts, classify ? 1 : 0,
                            tau, rec.cursor, nullptr, rec, carry);

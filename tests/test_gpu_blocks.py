@@ -269,3 +269,34 @@ def test_wavefronts_share_a_superblock(supers, hot, monkeypatch):
                                        (3_000_000, 1_000_000, 1), (6_000_000, 300_000, 1)])
 def test_wavefronts_share_a_superblock_by_entry(n, hot, k_h):
     check_hot(n, hot, 5779, 5813, k_h, "by entry")
+
+
+def check_novel(n, X, Y, k_h, what):
+    print(f"case {what} n={n} k_h={k_h}", flush=True)
+    rs = synth.random_reads(37 + k_h, 1, n, n, k=31)
+    reads = torch.from_numpy(rs.reads).cuda()
+    offs = torch.from_numpy(rs.offsets.view(np.int64)).cuda()
+    g = P.run_kmerco(reads, offs, 31, 2, X, Y, 8, k_h)
+    c = oracle.run_kmerco(rs.reads, rs.offsets, 31, 2, X, Y, 8, k_h)
+    for name, a, b in zip(["words", "distinct", "trust", "err"], g[:4], c[:4]):
+        assert np.array_equal(np.asarray(a, dtype=np.uint64), np.asarray(b, dtype=np.uint64)), name
+    assert g[4] == c[4]
+
+
+# Regions of about 120 new k-mers, whose records wait in LDS: some have more
+# than wait there, and a workgroup's regions fill the room several times; then
+# the first averages past it
+@pytest.mark.parametrize("n", [2_000_000, 2_099_742, 2_200_000])
+def test_records_of_few_entries(n):
+    check_novel(n, 5779, 5813, 1, "records of few entries")
+
+
+# New k-mers beyond the entries that are held: a few a region, and (nearly all
+# entries in the first of two regions) more than their room
+@pytest.mark.parametrize("n,X,Y,k_h,part_log", [(40_900, 101, 101, 1, "2"), (20_450, 101, 101, 2, "2"),
+                                                (16_400, 1, 2053, 1, "0"), (8_200, 1, 2053, 2, "0")])
+def test_records_beyond_the_held_entries(n, X, Y, k_h, part_log, monkeypatch):
+    monkeypatch.setenv("KMERCO_PART_LOG", part_log)
+    check_novel(n, X, Y, k_h, "records beyond the held entries")
+    monkeypatch.setenv("KMERCO_WINNER_RECORDS", "1")
+    check_novel(n, X, Y, k_h, "own records beyond the held entries")
