@@ -1059,8 +1059,12 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
 // The region pass of sparse regions (a few thousand entries over 16384
 // counters), two-level form: by entry instead of by counter.  Entries are
 // counted as above; then the one that holds its counter's first position
-// updates the cell, which the workgroup has in LDS, cleans the counter, and
-// leaves a record (position | mark << 30) if it found the counter zero.
+// updates the cell, cleans the counter, and leaves a record (position | mark
+// << 30) if it found the counter zero.
+//
+// kCells: cells a thread holds; the workgroup has them in LDS (1: regions of up
+// to 1024 cells, 2: 2048).  0: regions of 4096 or 8192 cells, which do not fit
+// beside the counters; each first entry reads its cell and adds to it in memory.
 //
 // The sweep over all counters cost 5.8 us a region and workgroup however few
 // entries it had; this takes 3.1 with 50 and 4.0 with 1.9 K entries (62 K
@@ -1096,7 +1100,8 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
     constexpr uint32_t kStep = 64u * kGroups;
     __shared__ uint32_t hits[kRegionCounters];
     __shared__ uint32_t first[kRegionCounters];
-    __shared__ unsigned long long s_cell[kCells * kRegionWG];
+    constexpr int kHold = kCells ? kCells : 1;
+    __shared__ unsigned long long s_cell[kCells ? kCells * kRegionWG : 1];
     // records that wait in LDS: all of a region of up to kBatch (kFew), and those
     // of entries that are not held
     constexpr uint32_t kRecRoom = kOwn ? 1 : 2048, kBatch = 128;
@@ -1121,20 +1126,21 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         s_tally[0].n = s_tally[1].n = s_tally[0].more = s_tally[1].more = s_total[0] =
             s_total[1] = s_over[0] = s_over[1] = 0;
     const bool carry_out = kOwn && C.mode == Carry::kOut;
-    const bool carry_in = kOwn && C.mode == Carry::kIn && C.n_prev > 0;
-    auto load_cells = [&](uint32_t r, uint64_t(&cell)[kCells]) {
+    const bool carry_in = kOwn && kCells && C.mode == Carry::kIn && C.n_prev > 0;
+    auto load_cells = [&](uint32_t r, uint64_t(&cell)[kHold]) {
         const uint64_t wbase = (uint64_t)r << shift;
 #pragma unroll
         for (int k = 0; k < kCells; k++) {
             const uint32_t w = threadIdx.x + (uint32_t)k * kRegionWG;
-            cell[k] = r < P.n_regions && wbase + w < n_words ? F.words[wbase + w] : 0ull;
+            const bool in = (kCells > 1 || w < S) && r < P.n_regions && wbase + w < n_words;
+            cell[k] = in ? F.words[wbase + w] : 0ull;
         }
     };
     // Region r's cells into L2, a word of each line: they come from memory
     // that nothing else has read for long, further off than a region's time.
     auto touch = [&](uint32_t r) -> uint32_t {
         const uint64_t w = ((uint64_t)r << shift) + 16u * threadIdx.x;
-        const bool in = threadIdx.x < kCells * 64u && r < P.n_regions && w < n_words;
+        const bool in = kCells && 16u * threadIdx.x < S && r < P.n_regions && w < n_words;
         return in ? *reinterpret_cast<const uint32_t *>(F.words + w) : 0u;
     };
     uint32_t bs, be;  // the lane's run: its entries in the list
@@ -1199,8 +1205,8 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         if (t < first[local])
             atomicMin(&first[local], t);
     };
-    // the counter's update by its first entry; its record's mark, or 0
-    auto update = [&](uint32_t local, uint32_t t) -> uint32_t {
+    // The counter's hits, for its first entry (which cleans it), else 0.
+    auto claim = [&](uint32_t local, uint32_t t) -> uint32_t {
         if (first[local] != t)
             return 0u;
         // two hash functions may give one position the same counter
@@ -1212,15 +1218,31 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         }
         const uint32_t h = hits[local];
         hits[local] = 0;
-        const uint32_t w = local & (S - 1u), sh = F.alpha * (local >> shift);
-        const uint32_t pf = (uint32_t)(s_cell[w] >> sh) & fm;  // this entry's own field
+        return h;
+    };
+    // The cell's update by h hits; the record's mark, or 0.  pre: the cell, as
+    // far as this counter goes; the field grows without carrying out.
+    auto apply = [&](unsigned long long *cell, uint64_t pre, uint32_t local,
+                     uint32_t h) -> uint32_t {
+        const uint32_t sh = F.alpha * (local >> shift);
+        const uint32_t pf = (uint32_t)(pre >> sh) & fm;
         const uint32_t room = fm - pf, inc = h < room ? h : room;
-        if (inc)  // the field grows without carrying out
-            atomicAdd(&s_cell[w], (unsigned long long)inc << sh);
+        if (inc)
+            atomicAdd(cell, (unsigned long long)inc << sh);
         return pf ? 0u : (classify && inc > tau ? 3u : 1u);
     };
+    // both, for an entry of region r; its record's mark, or 0
+    auto update = [&](uint32_t r, uint32_t local, uint32_t t) -> uint32_t {
+        const uint32_t h = claim(local, t);
+        if (!h)
+            return 0u;
+        const uint32_t w = local & (S - 1u);
+        unsigned long long *cell =
+            kCells ? &s_cell[w] : (unsigned long long *)F.words + ((uint64_t)r << shift) + w;
+        return apply(cell, *cell, local, h);
+    };
     uint32_t r = (grid & 7u) == 0 ? (blockIdx.x & 7u) * (grid >> 3) + (blockIdx.x >> 3) : blockIdx.x;
-    uint64_t cell[kCells];
+    uint64_t cell[kHold];
     Held H;
     LaneRuns R;
     load_cells(r, cell);
@@ -1260,7 +1282,7 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
     for (uint32_t turn = 0; r < P.n_regions; r += grid, turn ^= 1u) {
         LaneRuns Rn;
         Held Hn;
-        uint64_t celln[kCells];
+        uint64_t celln[kHold];
         share_run(bs, be, part, B.split, Rn);
         load(Rn, 0, Hn);
         load_cells(r + grid, celln);
@@ -1297,8 +1319,28 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
 #pragma unroll
         for (int j = 0; j < kHeld / 2; j++)
             halves[j] = 0;
+        // cells in memory: those of all held entries are requested together
+        uint32_t marks[kHeld];
+        if constexpr (kCells == 0) {
+            uint64_t was[kHeld];
+            unsigned long long *cells = (unsigned long long *)F.words + ((uint64_t)r << shift);
+#pragma unroll
+            for (int j = 0; j < kHeld; j++) {
+                marks[j] = 0;
+                was[j] = 0;
+            }
+            each(R, 0, H, [&](int j, uint32_t local, uint32_t t) {
+                marks[j] = claim(local, t);
+                if (marks[j])
+                    was[j] = cells[local & (S - 1u)];
+            });
+            each(R, 0, H, [&](int j, uint32_t local, uint32_t) {
+                if (marks[j])
+                    marks[j] = apply(&cells[local & (S - 1u)], was[j], local, marks[j]);
+            });
+        }
         each(R, 0, H, [&](int j, uint32_t local, uint32_t t) {
-            const uint32_t mark = update(local, t);
+            const uint32_t mark = kCells ? update(r, local, t) : marks[j];
             if (kOwn) {
                 fresh[j] = t;
                 halves[j / 2] |= (carry_out ? local : mark) << (16 * (j % 2));
@@ -1317,7 +1359,7 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
             // more than the registers hold
             load(R, w0, H);
             each(R, w0, H, [&](int, uint32_t local, uint32_t t) {
-                const uint32_t mark = update(local, t);
+                const uint32_t mark = update(r, local, t);
                 if (mark && kOwn)
                     put(s_tally[turn].base + atomicAdd(&s_tally[turn].n, 1u), t,
                         carry_out ? local : mark);
@@ -1439,6 +1481,9 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
 
 namespace {
 
+using SparseKernel = void (*)(FilterArgs, BinPlan, BlockPlan, const uint32_t *, const uint8_t *,
+                              const uint32_t *, int, uint32_t, uint32_t *, uint32_t *, RecordSpace,
+                              Carry);
 using SortKernel = void (*)(FilterArgs, ReadsArgs, uint64_t, uint64_t, uint64_t, BlockPlan, uint32_t,
                             uint32_t *, uint8_t *, uint16_t *, unsigned long long *);
 using RunsKernel = void (*)(FilterArgs, uint64_t, BinPlan, BlockPlan, const uint32_t *,
@@ -1502,6 +1547,13 @@ RunsKernel runs_kernel(const BinPlan &P, const BlockPlan &B) {
     default:  // two counters a cell
         return runs_kernel_of<kCounters, 8, kSorted>(B);
     }
+}
+
+template <RecordForm kRecords>
+SparseKernel sparse_kernel(const BinPlan &P) {
+    return P.region_shift > 11    ? k_region_sparse<0, kRecords>
+           : P.region_shift == 11 ? k_region_sparse<2, kRecords>
+                                  : k_region_sparse<1, kRecords>;
 }
 
 }  // namespace
@@ -1648,10 +1700,10 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
         rec.log++;
     rec.n_buckets = (uint32_t)((len + (1ull << rec.log) - 1) >> rec.log);
     // Sparse regions are worked by entry: below kSparseEntries a region on
-    // average, for the forms whose cells fit beside the counters in LDS
-    const bool by_entry = B.two && plan.region_counters == (uint32_t)kRegionCounters &&
-                          (plan.region_shift == 10 || plan.region_shift == 11) &&
-                          B.n_super <= kRegionWG && len * F.k_h <= kSparseEntries * plan.n_regions;
+    // average (cells in memory: kSparseCells)
+    const bool by_entry =
+        B.two && plan.region_counters == (uint32_t)kRegionCounters && B.n_super <= kRegionWG &&
+        len * F.k_h <= (plan.region_shift > 11 ? kSparseCells : kSparseEntries) * plan.n_regions;
     const bool own = records || carry.mode == Carry::kOut;  // records in the regions' own room
     const bool sparse = by_entry && !own && carry.mode == Carry::kNone && 8 * len * F.k_h <= room;
     if (records || carry.mode == Carry::kOut || sparse) {
@@ -1683,10 +1735,7 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
     const uint32_t grid = region_grid(plan.n_regions, plan.region_counters);
     if (sparse) {
         const bool few = len * F.k_h <= kFewEntries * plan.n_regions;
-        hipLaunchKernelGGL((few ? (plan.region_shift == 10 ? k_region_sparse<1, kFew>
-                                                           : k_region_sparse<2, kFew>)
-                                : (plan.region_shift == 10 ? k_region_sparse<1, kFlat>
-                                                           : k_region_sparse<2, kFlat>)),
+        hipLaunchKernelGGL((few ? sparse_kernel<kFew>(plan) : sparse_kernel<kFlat>(plan)),
                            dim3(grid), dim3(kRegionWG), 0, s, F, plan, B, (const uint32_t *)merged,
                            (const uint8_t *)merged_hi, (const uint32_t *)starts, classify ? 1 : 0,
                            tau, rec.cursor, rec.word + len * F.k_h, rec, carry);
@@ -1706,8 +1755,7 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
         return e;
     }
     if (by_entry && own) {
-        hipLaunchKernelGGL((plan.region_shift == 10 ? k_region_sparse<1, kOwn>
-                                                    : k_region_sparse<2, kOwn>),
+        hipLaunchKernelGGL(sparse_kernel<kOwn>(plan),
                            dim3(grid), dim3(kRegionWG), 0, s, F, plan, B, (const uint32_t *)merged,
                            (const uint8_t *)merged_hi, (const uint32_t *)starts, classify ? 1 : 0,
                            tau, rec.cursor, nullptr, rec, carry);

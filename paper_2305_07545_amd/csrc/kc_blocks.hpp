@@ -28,8 +28,14 @@ constexpr uint32_t kMergeWG = 1024;   // threads of the second level
 // pass holds in registers up to there: 150 M bases over 62 K regions (1.9 K
 // entries each) 1.77 -> 1.08 ms with the records, 100 M over 16 K (5 K) 0.59 ->
 // 0.52; 200 M over 16 K (10 K) 0.73 -> 0.68, but more entries than are held are
-// read twice.
+// read twice.  Regions of 256 and 512 cells, as long as these: 30 M bases over
+// 20 K regions (1 K) 1.14 -> 0.58 and 0.89 -> 0.52 ms the call, 125 M (5 K)
+// 2.02 -> 1.51 and 1.88 -> 1.37.
 constexpr uint64_t kSparseEntries = 8192;
+// The same of regions of 4096 and 8192 cells, whose first entries read a cache
+// line each: 12 K regions of 1.2 K entries 0.68 -> 0.49 and 1.11 -> 0.50 ms the
+// call, of 2.4 K 0.87 -> 0.73 and 1.32 -> 0.76, of 4.8 K 1.22 and 1.69 -> 1.33.
+constexpr uint64_t kSparseCells = 4096;
 constexpr uint32_t kMergeTile = 12288;  // entries it stages in LDS (two workgroups per CU)
 
 // Blocks of one chunk: block b holds the entries of positions [b << pos_log,

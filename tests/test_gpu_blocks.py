@@ -300,3 +300,48 @@ def test_records_beyond_the_held_entries(n, X, Y, k_h, part_log, monkeypatch):
     check_novel(n, X, Y, k_h, "records beyond the held entries")
     monkeypatch.setenv("KMERCO_WINNER_RECORDS", "1")
     check_novel(n, X, Y, k_h, "own records beyond the held entries")
+
+
+# Regions worked by entry whose cells are not 1024 or 2048: 256 and 512 cells,
+# and 4096 and 8192 that stay in memory, flat and own records, a counter hit
+# twice by a position, saturating ones, more entries than are held
+@pytest.mark.parametrize("alpha,k_h,n,X,Y,part_log", [
+    (1, 1, 400_000, 1511, 1523, None),    # 8990 regions of 256 cells
+    (1, 3, 200_000, 1511, 1523, None),
+    (2, 2, 400_000, 2003, 2011, None),    # 7868 regions of 512 cells
+    (3, 8, 60_000, 2003, 2011, None),
+    (16, 1, 400_000, 5779, 5813, None),   # 8202 regions of 4096 cells
+    (16, 2, 400_000, 5779, 5813, None),
+    (32, 1, 400_000, 1009, 1013, "2"),    # 125 regions of 8192 cells
+    (20, 3, 130_000, 1009, 1013, "2"),
+    (32, 1, 32_760, 89, 719, "2"),        # 8 regions of 4095 entries on average
+])
+@pytest.mark.parametrize("own", [False, True])
+def test_sparse_regions_of_other_cells(alpha, k_h, n, X, Y, part_log, own, monkeypatch):
+    if part_log:
+        monkeypatch.setenv("KMERCO_PART_LOG", part_log)
+    if own:
+        monkeypatch.setenv("KMERCO_WINNER_RECORDS", "1")
+    test_block_form_against_the_oracle(n, X, Y, alpha, k_h, 31)
+
+
+@pytest.mark.parametrize("alpha,X,Y", [(1, 1511, 1523), (16, 5779, 5813)])
+def test_sparse_regions_of_other_cells_overfull(alpha, X, Y):
+    """Most entries in one region, over counters that are not zero before."""
+    n = 400_000
+    print(f"case other cells, overfull alpha={alpha}", flush=True)
+    rs = reads_of(41, n, 31)
+    rs.reads[1000:300_000] = ord("A")
+    twice = synth.concat_reads([rs, rs])
+    one = [torch.from_numpy(a).cuda() for a in (rs.reads, rs.offsets.view(np.int64))]
+    bf = P.CountBF(X, Y, alpha, 1)
+    lists = []
+    for _ in range(2):
+        d, t, nt, e, ne = bf.insert_classify(*one, 31, 1)
+        bf.sync()
+        lists.append((d[:int(bf.n_distinct.item())].clone(), t[:int(nt.item())].clone()))
+    c = oracle.run_kmerco(twice.reads, twice.offsets, 31, 1, X, Y, alpha, 1)
+    assert np.array_equal(bf.words.cpu().numpy().view(np.uint64), np.asarray(c[0], dtype=np.uint64))
+    assert np.array_equal(lists[0][0].cpu().numpy().view(np.uint64), np.asarray(c[1], dtype=np.uint64))
+    assert lists[1][1].numel() == 0
+    bf.close()
