@@ -1565,7 +1565,10 @@ bool block_plan(const BinPlan &plan, uint32_t k_h, uint64_t len, BlockPlan &B) {
     B.kh = 1;
     while (B.kh < k_h)
         B.kh *= 2;
-    B.two = plan.n_parts || plan.n_regions > kBlockRegions;
+    const uint64_t entries = len * k_h;
+    const bool full = plan.region_counters == (uint32_t)kRegionCounters;
+    B.two = plan.n_parts || plan.n_regions > kBlockRegions ||
+            (full && plan.n_regions >= kSparseRegions && entries <= kSparseShort * plan.n_regions);
     // large blocks make long runs; chunks that would leave the chip idle take
     // small ones
     B.wg = B.two || plan.n_regions > kHalfRegions ? 1024u : 512u;
@@ -1611,6 +1614,10 @@ bool block_plan(const BinPlan &plan, uint32_t k_h, uint64_t len, BlockPlan &B) {
     B.n_super = (B.n_blocks + B.super - 1u) / B.super;
     while ((B.n_super << (B.split + 1u)) <= (uint32_t)kRegionWG / 64u)
         B.split++;
+    // sparse regions are worked by entry, up to kSparseEntries a region on
+    // average (cells in memory: kSparseCells)
+    B.by_entry = full && B.n_super <= kRegionWG &&
+                 entries <= (plan.region_shift > 11 ? kSparseCells : kSparseEntries) * plan.n_regions;
     return true;
 }
 
@@ -1699,13 +1706,8 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
     while ((len + (1ull << rec.log) - 1) >> rec.log > kMarkBuckets || rec.log < 12)
         rec.log++;
     rec.n_buckets = (uint32_t)((len + (1ull << rec.log) - 1) >> rec.log);
-    // Sparse regions are worked by entry: below kSparseEntries a region on
-    // average (cells in memory: kSparseCells)
-    const bool by_entry =
-        B.two && plan.region_counters == (uint32_t)kRegionCounters && B.n_super <= kRegionWG &&
-        len * F.k_h <= (plan.region_shift > 11 ? kSparseCells : kSparseEntries) * plan.n_regions;
     const bool own = records || carry.mode == Carry::kOut;  // records in the regions' own room
-    const bool sparse = by_entry && !own && carry.mode == Carry::kNone && 8 * len * F.k_h <= room;
+    const bool sparse = B.by_entry && !own && carry.mode == Carry::kNone && 8 * len * F.k_h <= room;
     if (records || carry.mode == Carry::kOut || sparse) {
         rec.cursor = W.n_entries + 3;
         if ((e = fill_u32(rec.cursor, 1, 0u, s)) != hipSuccess)
@@ -1754,7 +1756,7 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
             P->end(s);
         return e;
     }
-    if (by_entry && own) {
+    if (B.by_entry && own) {
         hipLaunchKernelGGL(sparse_kernel<kOwn>(plan),
                            dim3(grid), dim3(kRegionWG), 0, s, F, plan, B, (const uint32_t *)merged,
                            (const uint8_t *)merged_hi, (const uint32_t *)starts, classify ? 1 : 0,

@@ -36,6 +36,15 @@ constexpr uint64_t kSparseEntries = 8192;
 // line each: 12 K regions of 1.2 K entries 0.68 -> 0.49 and 1.11 -> 0.50 ms the
 // call, of 2.4 K 0.87 -> 0.73 and 1.32 -> 0.76, of 4.8 K 1.22 and 1.69 -> 1.33.
 constexpr uint64_t kSparseCells = 4096;
+// A countBF that the one-level form takes goes to the two-level one for that
+// from this many regions on, with up to this many entries a region: the call
+// (one-level against two-level) with 10 new k-mers a region over 1000 regions
+// 66 and 69 us, 1500 80 and 78, 3000 115 and 95, 7000 197 and 137; with 50 over
+// 7000 204 and 138; over 2000 regions with 600 entries 114 and 100, 2400 149 and
+// 142, 4800 183 and 215; 4096 cells a region, 6000 regions, 300 198 and 179,
+// 2400 336 and 352.
+constexpr uint32_t kSparseRegions = 1536;
+constexpr uint64_t kSparseShort = 2048;
 constexpr uint32_t kMergeTile = 12288;  // entries it stages in LDS (two workgroups per CU)
 
 // Blocks of one chunk: block b holds the entries of positions [b << pos_log,
@@ -57,6 +66,7 @@ struct BlockPlan {
     uint32_t sub_log;
     uint32_t super;
     uint32_t n_super;   // superblocks
+    uint32_t by_entry;  // sparse regions: worked by entry
     uint32_t split;     // log2(wavefronts of the region pass that share a superblock's run)
 };
 

@@ -345,3 +345,21 @@ def test_sparse_regions_of_other_cells_overfull(alpha, X, Y):
     assert np.array_equal(lists[0][0].cpu().numpy().view(np.uint64), np.asarray(c[1], dtype=np.uint64))
     assert lists[1][1].numel() == 0
     bf.close()
+
+
+# Sparse regions of a countBF small enough for the one-level form: the line
+# between the forms in regions (1535 | 1536) and in entries, from a few bases
+# on, chunks of which the last is sparser than the others
+@pytest.mark.parametrize("n,X,Y,alpha,k_h,chunk", [
+    (500, 1811, 1737, 8, 1, None),        # 1536 regions
+    (40_000, 1811, 1735, 8, 1, None),     # 1535
+    (40_000, 1811, 1737, 8, 3, None),
+    (3_145_728, 1811, 1737, 8, 1, None), (3_145_729, 1811, 1737, 8, 1, None),  # 2048 a region
+    (300_000, 2707, 2711, 16, 1, None),   # 1792 regions of 4096 cells
+    (300_000, 1009, 1013, 2, 2, None),    # 1997 regions of 512 cells
+    (4_000_000, 1811, 1737, 8, 1, 3_300_000 // 1024 * 1024),
+])
+def test_sparse_regions_of_smaller_countbfs(n, X, Y, alpha, k_h, chunk, monkeypatch):
+    if chunk:
+        monkeypatch.setenv("KMERCO_CHUNK_POSITIONS", str(chunk))
+    test_block_form_against_the_oracle(n, X, Y, alpha, k_h, 31)
