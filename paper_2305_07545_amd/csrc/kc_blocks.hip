@@ -1205,17 +1205,18 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
         if (t < first[local])
             atomicMin(&first[local], t);
     };
-    // The counter's hits, for its first entry (which cleans it), else 0.
-    auto claim = [&](uint32_t local, uint32_t t) -> uint32_t {
+    // Whether the entry at position t is its counter's first (which then cleans
+    // it: the minimum here, the hits in `taken`).
+    auto is_first = [&](uint32_t local, uint32_t t) -> bool {
         if (first[local] != t)
-            return 0u;
+            return false;
         // two hash functions may give one position the same counter
-        if (F.k_h > 1u) {
-            if (atomicExch(&first[local], kIdle) != t)
-                return 0u;
-        } else {
-            first[local] = kIdle;
-        }
+        if (F.k_h > 1u)
+            return atomicExch(&first[local], kIdle) == t;
+        first[local] = kIdle;
+        return true;
+    };
+    auto taken = [&](uint32_t local) -> uint32_t {
         const uint32_t h = hits[local];
         hits[local] = 0;
         return h;
@@ -1231,12 +1232,11 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
             atomicAdd(cell, (unsigned long long)inc << sh);
         return pf ? 0u : (classify && inc > tau ? 3u : 1u);
     };
-    // both, for an entry of region r; its record's mark, or 0
+    // all of it, for an entry of region r; its record's mark, or 0
     auto update = [&](uint32_t r, uint32_t local, uint32_t t) -> uint32_t {
-        const uint32_t h = claim(local, t);
-        if (!h)
+        if (!is_first(local, t))
             return 0u;
-        const uint32_t w = local & (S - 1u);
+        const uint32_t h = taken(local), w = local & (S - 1u);
         unsigned long long *cell =
             kCells ? &s_cell[w] : (unsigned long long *)F.words + ((uint64_t)r << shift) + w;
         return apply(cell, *cell, local, h);
@@ -1330,9 +1330,10 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
                 was[j] = 0;
             }
             each(R, 0, H, [&](int j, uint32_t local, uint32_t t) {
-                marks[j] = claim(local, t);
-                if (marks[j])
+                if (is_first(local, t)) {
+                    marks[j] = taken(local);
                     was[j] = cells[local & (S - 1u)];
+                }
             });
             each(R, 0, H, [&](int j, uint32_t local, uint32_t) {
                 if (marks[j])
