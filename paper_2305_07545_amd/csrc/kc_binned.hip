@@ -208,7 +208,8 @@ __global__ void __launch_bounds__(kWinThreads) k_win_b(const uint32_t *__restric
     __shared__ uint32_t s_wave[kWinThreads / 64];
     const uint32_t a = blockIdx.x;
     const uint32_t n = cursor_a[a];
-    const uint32_t per = ((k_h << kWinA) + kWinSlices - 1) / kWinSlices;
+    // the bucket's records in equal slices of whole batches
+    const uint32_t per = ((n + kWinSlices - 1) / kWinSlices + kWinBatch - 1) / kWinBatch * kWinBatch;
     const uint32_t q0 = blockIdx.y * per;
     const uint32_t q1 = q0 + per < n ? q0 + per : n;
     const uint32_t *src = in + a * ((uint64_t)k_h << kWinA);
