@@ -1080,12 +1080,13 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
 // kFew (regions of kFewEntries entries on average): dense in `flat`, where
 // the records of many regions leave together from LDS.  The room comes from
 // one address, at 4.5 ns an atomic: one a region cost 74 of 204 us over 16 K
-// regions of 15 new k-mers, now 173; over 44 K regions of 450, kFlat takes 730
-// us and this 750.
+// regions of 15 new k-mers, now 173; the call over 10 K regions of 180 206 us
+// in kFlat, 189 in this form, over 100 K of 220 1.650 and 1.641 ms, of 250 1.688
+// and 1.693.
 // kOwn (chunks above 2^28 positions, carried chunks): the records go to room of
 // the region's own for each of its entries, as k_region_runs' do.
 enum RecordForm { kOwn, kFlat, kFew };
-constexpr uint64_t kFewEntries = 128;
+constexpr uint64_t kFewEntries = 256;
 
 template <int kCells, RecordForm kRecords>
 __global__ void __launch_bounds__(kRegionWG)
@@ -1104,7 +1105,7 @@ k_region_sparse(FilterArgs F, BinPlan P, BlockPlan B, const uint32_t *__restrict
     __shared__ unsigned long long s_cell[kCells ? kCells * kRegionWG : 1];
     // records that wait in LDS: all of a region of up to kBatch (kFew), and those
     // of entries that are not held
-    constexpr uint32_t kRecRoom = kOwn ? 1 : 2048, kBatch = 128;
+    constexpr uint32_t kRecRoom = kOwn ? 1 : 2048, kBatch = 320;
     __shared__ uint32_t s_rec[kRecRoom];
     // by the region's parity: records of held entries, of others (!kOwn), and
     // the room for this region's (!kOwn: the region before's), read at once
