@@ -1568,9 +1568,11 @@ bool block_plan(const BinPlan &plan, uint32_t k_h, uint64_t len, BlockPlan &B) {
     while (B.kh < k_h)
         B.kh *= 2;
     const uint64_t entries = len * k_h;
-    const bool full = plan.region_counters == (uint32_t)kRegionCounters;
+    // (regions of half the counters: twice the regions, half the entries each)
+    const uint32_t half = plan.region_counters == (uint32_t)kSmallRegionCounters ? 1u : 0u;
     B.two = plan.n_parts || plan.n_regions > kBlockRegions ||
-            (full && plan.n_regions >= kSparseRegions && entries <= kSparseShort * plan.n_regions);
+            (plan.n_regions >= kSparseRegions << half &&
+             entries <= (kSparseShort >> half) * plan.n_regions);
     // large blocks make long runs; chunks that would leave the chip idle take
     // small ones
     B.wg = B.two || plan.n_regions > kHalfRegions ? 1024u : 512u;
@@ -1618,7 +1620,7 @@ bool block_plan(const BinPlan &plan, uint32_t k_h, uint64_t len, BlockPlan &B) {
         B.split++;
     // sparse regions are worked by entry, up to kSparseEntries a region on
     // average (cells in memory: kSparseCells)
-    B.by_entry = full && B.n_super <= kRegionWG &&
+    B.by_entry = B.n_super <= kRegionWG &&
                  entries <= (plan.region_shift > 11 ? kSparseCells : kSparseEntries) * plan.n_regions;
     return true;
 }
@@ -1736,7 +1738,10 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
                              : (const void *)(B.turned ? turned : table);
     if (P)
         P->begin(kPhRegion, s);
-    const uint32_t grid = region_grid(plan.n_regions, plan.region_counters);
+    // (the by-entry pass has LDS for the larger regions' counters)
+    const bool whole = sparse || (B.by_entry && own);
+    const uint32_t grid =
+        region_grid(plan.n_regions, whole ? (uint32_t)kRegionCounters : plan.region_counters);
     if (sparse) {
         const bool few = len * F.k_h <= kFewEntries * plan.n_regions;
         hipLaunchKernelGGL((few ? sparse_kernel<kFew>(plan) : sparse_kernel<kFlat>(plan)),
@@ -1758,7 +1763,7 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
             P->end(s);
         return e;
     }
-    if (B.by_entry && own) {
+    if (whole) {
         hipLaunchKernelGGL(sparse_kernel<kOwn>(plan),
                            dim3(grid), dim3(kRegionWG), 0, s, F, plan, B, (const uint32_t *)merged,
                            (const uint8_t *)merged_hi, (const uint32_t *)starts, classify ? 1 : 0,

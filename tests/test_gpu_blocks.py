@@ -363,3 +363,22 @@ def test_sparse_regions_of_smaller_countbfs(n, X, Y, alpha, k_h, chunk, monkeypa
     if chunk:
         monkeypatch.setenv("KMERCO_CHUNK_POSITIONS", str(chunk))
     test_block_form_against_the_oracle(n, X, Y, alpha, k_h, 31)
+
+
+# Regions of 8192 counters worked by entry: from the one-level and the
+# partitioned plan, own records, carried chunks, cells in memory
+@pytest.mark.parametrize("n,X,Y,alpha,k_h,env", [
+    (400_000, 1811, 1741, 8, 1, {}),      # 3080 regions
+    (400_000, 1811, 1733, 8, 1, {}),      # 3065: one-level
+    (400_000, 4201, 4211, 8, 2, {}),      # 17277: partitioned
+    (400_000, 4201, 4211, 8, 1, {"KMERCO_WINNER_RECORDS": "1"}),
+    (400_000, 4201, 4211, 8, 1, {"KMERCO_CHUNK_POSITIONS": "131072"}),
+    (300_000, 4201, 4211, 16, 1, {}),     # 8639 of 2048 cells
+    (300_000, 5779, 5813, 32, 3, {}),     # 8202 of 4096 cells
+    (300_000, 1009, 1013, 1, 1, {}),      # 7985 of 128 cells
+])
+def test_small_sparse_regions(n, X, Y, alpha, k_h, env, monkeypatch):
+    monkeypatch.setenv("KMERCO_REGION_COUNTERS", "8192")
+    for name, v in env.items():
+        monkeypatch.setenv(name, v)
+    test_block_form_against_the_oracle(n, X, Y, alpha, k_h, 31)
