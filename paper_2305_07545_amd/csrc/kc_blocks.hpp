@@ -65,6 +65,7 @@ struct BlockPlan {
     uint32_t wg;        // threads of the hashing kernel
     uint32_t turned;    // short runs: 16-bit offsets per region of the turned table, else 0
     uint32_t lanes;     // lanes of the region pass per run
+    uint32_t share;     // short runs: blocks a wavefront takes at a time (64 at most)
     uint32_t two;       // two-level form
     uint32_t sub_log;
     uint32_t super;
