@@ -180,7 +180,7 @@ void kc_destroy(kc_filter *f);
  * Sizes, k_h = 1: countBFs of up to 16384 regions (256 MB at alpha = 8) take
  * the binned path, about 22 bytes per base (packed codes and bitmaps, the
  * positions' bits, entry lists and their tables); larger countBFs take the partitioned
- * path, about 19 bytes per base of a chunk of up to 2^32 - 2^16 bases (two
+ * path, about 18 bytes per base of a chunk of up to 2^32 - 2^16 bases (two
  * entry buffers of 8 bytes, each holding two kinds of data in turn); the direct
  * path (forced, or beyond 256 partitions) takes 4 bytes per counter plus
  * about 2 bytes per base.  Scratch grows, and is never shrunk, by calls

@@ -57,7 +57,7 @@ void wait_idle(kc_filter *f) {
 
 // per-position buffers for inserts of up to n bases (waits for `wait_on`
 // before releasing smaller ones); valid_bitmap: with the valid-window bitmap
-// of the binned paths
+// of the batched form
 kc_status ensure_positions(kc::Workspace &W, hipStream_t wait_on, uint64_t n, bool valid_bitmap) {
     if (W.codes && n <= W.cap && (W.valid || !valid_bitmap))
         return KC_OK;
@@ -110,114 +110,61 @@ kc_status ensure_tiles(kc::Workspace &W, hipStream_t wait_on, uint64_t n) {
 }
 
 kc_status ensure_positions(kc_filter *f, uint64_t n) {
-    return ensure_positions(*f->W, f->last, n, true);
+    return ensure_positions(*f->W, f->last, n, false);
 }
 kc_status ensure_tiles(kc_filter *f, uint64_t n) { return ensure_tiles(*f->W, f->last, n); }
 
-// binned-path buffers for one chunk of the given plan
-kc_status ensure_binned(kc_filter *f, const kc::BinPlan &B, uint64_t chunk_positions) {
+// binned-path buffers for one chunk of the given plan: the tables' rooms, and
+// two entry-sized buffers each used twice (kernels of one stream, in this
+// order; launch_blocks_chunk places what lies in them):
+//   bucketed: two-level form, the blocks' list and table (hashing -> second
+//             level); then the first-seen records;
+//   entries:  the list that the region pass reads (two-level form: and its
+//             starts); then the winner passes' first area.
+kc_status ensure_plan(kc_filter *f, const kc::BinPlan &B, uint64_t chunk_positions) {
     kc::Workspace &W = *f->W;
-    // smaller chunks of the same countBF make at most kBinSpread workgroups:
-    // room for them too, so that a reservation covers every smaller insert
-    const uint64_t g = B.G > kc::kBinSpread ? B.G : kc::kBinSpread;
-    const uint64_t n_mat = (uint64_t)B.n_regions * g;
-    const uint64_t n_coarse = (uint64_t)B.n_buckets * g;
-    const uint64_t n_slots = chunk_positions * f->layout.k_h;
-    const uint64_t n_ent = n_slots;
-    if (W.matrix && n_mat <= W.matrix_cap && n_coarse <= W.coarse_cap && n_slots <= W.slots_cap &&
-        n_ent <= W.entries_cap)
+    const uint64_t n_ent = chunk_positions * f->layout.k_h;
+    const uint64_t n_mat =
+        B.n_parts ? ((uint64_t)B.n_parts * B.rooms) << B.part_log : (uint64_t)B.n_regions * B.rooms;
+    const uint64_t n_slots = B.n_parts ? 0 : n_ent, n_index = B.n_parts ? 0 : 2ull * B.n_regions;
+    const bool mat = !W.matrix || n_mat > W.matrix_cap;
+    const bool idx = n_index && (!W.index || n_index > W.index_cap);
+    const bool slots = n_slots && (!W.slots || n_slots > W.slots_cap);
+    const bool ent = !W.entries || n_ent > W.entries_cap;
+    if (!mat && !idx && !slots && !ent)
         return KC_OK;
     if (W.fixed)
         return KC_ERANGE;
     wait_idle(f);
-    if (!W.matrix || n_mat > W.matrix_cap || n_coarse > W.coarse_cap) {
+    if (mat) {
         dev_free(W.matrix);
         dev_free(W.matrix_t);
-        dev_free(W.coarse);
-        dev_free(W.partial32);
-        W.matrix_cap = W.coarse_cap = 0;
-        if (!dev_alloc(&W.matrix, n_mat) || !dev_alloc(&W.matrix_t, n_mat) ||
-            !dev_alloc(&W.coarse, n_coarse) || !dev_alloc(&W.partial32, kc::scan_partials(n_mat)))
+        W.matrix_cap = 0;
+        if (!dev_alloc(&W.matrix, n_mat) || !dev_alloc(&W.matrix_t, n_mat))
             return KC_ENOMEM;
         W.matrix_cap = n_mat;
-        W.coarse_cap = n_coarse;
     }
-    if (!W.slots || n_slots > W.slots_cap) {
+    if (idx) {
+        dev_free(W.index);
+        W.index_cap = 0;
+        if (!dev_alloc(&W.index, n_index))
+            return KC_ENOMEM;
+        W.index_cap = n_index;
+    }
+    if (slots) {
         dev_free(W.slots);
         W.slots_cap = 0;
         if (!dev_alloc(&W.slots, n_slots))
             return KC_ENOMEM;
         W.slots_cap = n_slots;
     }
-    if (!W.entries || n_ent > W.entries_cap) {
+    if (ent) {
         dev_free(W.entries);
         dev_free(W.bucketed);
         W.entries_cap = 0;
         if (!dev_alloc(&W.entries, n_ent) || !dev_alloc(&W.bucketed, n_ent))
             return KC_ENOMEM;
         W.entries_cap = n_ent;
-    }
-    return KC_OK;
-}
-
-// partitioned binned-path buffers for one chunk of the given plan: two
-// entry-sized buffers besides the matrices' room, each used twice (kernels of
-// one stream, in this order; launch_blocks_chunk places what lies in them):
-//   bucketed: the blocks' list and table (hashing -> second level), then the
-//             first-seen records;
-//   entries:  the superblocks' list and starts (second level -> region pass),
-//             then the winner passes' first area.
-kc_status ensure_parts(kc_filter *f, const kc::BinPlan &B, uint64_t chunk_positions) {
-    kc::Workspace &W = *f->W;
-    const uint64_t n_slots = chunk_positions * f->layout.k_h;
-    const uint64_t n_pmat = (uint64_t)B.n_parts * B.G;
-    const uint64_t n_fine = (uint64_t)B.n_regions * B.list_g;
-    const uint64_t nbp = (1ull << B.part_log) >> B.bucket_shift;
-    const uint64_t n_coarse = (uint64_t)B.n_parts * nbp * B.list_g;
-    // the scans share partial32; the list workgroups' rows (matrix_t) are
-    // 2^part_log counts long in every partition
-    const uint64_t n_rows = (uint64_t)B.n_parts * B.list_g << B.part_log;
-    uint64_t n_mat = n_fine > n_pmat ? n_fine : n_pmat;
-    if (n_rows > n_mat)
-        n_mat = n_rows;
-    if (W.entries && W.pbounds && W.pdesc && n_slots <= W.entries_cap && n_pmat <= W.pmat_cap &&
-        n_mat <= W.matrix_cap && n_coarse <= W.coarse_cap)
-        return KC_OK;
-    if (W.fixed)
-        return KC_ERANGE;
-    wait_idle(f);
-    if (!W.pbounds && !dev_alloc(&W.pbounds, kc::kMaxParts + 1))
-        return KC_ENOMEM;
-    if (!W.pdesc && !dev_alloc(&W.pdesc, 3ull * kc::kMaxParts))
-        return KC_ENOMEM;
-    if (!W.matrix || n_mat > W.matrix_cap || n_coarse > W.coarse_cap) {
-        const uint64_t m = n_mat > W.matrix_cap ? n_mat : W.matrix_cap;
-        const uint64_t c = n_coarse > W.coarse_cap ? n_coarse : W.coarse_cap;
-        dev_free(W.matrix);
-        dev_free(W.matrix_t);
-        dev_free(W.coarse);
-        dev_free(W.partial32);
-        W.matrix_cap = W.coarse_cap = 0;
-        if (!dev_alloc(&W.matrix, m) || !dev_alloc(&W.matrix_t, m) || !dev_alloc(&W.coarse, c) ||
-            !dev_alloc(&W.partial32, kc::scan_partials(m > c ? m : c)))
-            return KC_ENOMEM;
-        W.matrix_cap = m;
-        W.coarse_cap = c;
-    }
-    if (!W.pmat || n_pmat > W.pmat_cap) {
-        dev_free(W.pmat);
-        W.pmat_cap = 0;
-        if (!dev_alloc(&W.pmat, n_pmat))
-            return KC_ENOMEM;
-        W.pmat_cap = n_pmat;
-    }
-    if (!W.entries || n_slots > W.entries_cap) {
-        dev_free(W.entries);
-        dev_free(W.bucketed);
-        W.entries_cap = 0;
-        if (!dev_alloc(&W.entries, n_slots) || !dev_alloc(&W.bucketed, n_slots))
-            return KC_ENOMEM;
-        W.entries_cap = n_slots;
     }
     return KC_OK;
 }
@@ -265,15 +212,11 @@ void free_workspace(kc::Workspace &W) {
     dev_free(W.partial64);
     dev_free(W.matrix);
     dev_free(W.matrix_t);
-    dev_free(W.coarse);
-    dev_free(W.partial32);
+    dev_free(W.index);
     dev_free(W.slots);
     dev_free(W.bucketed);
     dev_free(W.entries);
-    dev_free(W.pmat);
-    dev_free(W.pbounds);
-    dev_free(W.pdesc);
-    W.slots_cap = W.entries_cap = W.matrix_cap = W.coarse_cap = W.pmat_cap = 0;
+    W.slots_cap = W.entries_cap = W.matrix_cap = W.index_cap = 0;
     dev_free(W.carry);
     dev_free(W.carry_off);
     dev_free(W.carry_n);
@@ -358,10 +301,6 @@ bool choose_plan(const kc_filter *f, uint64_t n_bases, kc::BinPlan &plan, uint64
         return kc::bin_plan(f->F, chunk, plan, f->part_log, f->region_counters);
     }
     return true;
-}
-
-kc_status ensure_plan(kc_filter *f, const kc::BinPlan &plan, uint64_t chunk) {
-    return plan.n_parts ? ensure_parts(f, plan, chunk) : ensure_binned(f, plan, chunk);
 }
 
 // Whether an insert of n_bases in chunks of `chunk` takes the carried
@@ -495,7 +434,7 @@ kc_status insert_core(kc_filter *f, const kc::Workspace &W, uint64_t n_bases, ui
                       uint64_t cap_te, hipStream_t s, kc::Profiler *P) {
     const bool split = trust != nullptr;
     hipError_t e = hipSuccess;
-    kc::ReadsArgs R{W.codes, W.inv, W.rs, n_bases, k, W.valid};
+    kc::ReadsArgs R{W.codes, W.inv, W.rs, n_bases, k, nullptr};
     const uint64_t chunk = binned ? bchunk : f->chunk;
     // The split is taken from marks on the distinct flags: the region pass
     // of the last chunk marks the k-mers first seen in it (one hash function:
@@ -653,7 +592,6 @@ kc_status insert_range(kc_filter *f, const kc::Workspace &pos, uint64_t base, ui
     V.codes = pos.codes + base / 16;
     V.inv = pos.inv + base / 32;
     V.rs = pos.rs + base / 32;
-    V.valid = pos.valid + base / 32;
     V.flags8 = pos.flags8 + base;
     if (kc::launch_clear_call(n_bases, V, s) != hipSuccess)
         return KC_EDEVICE;

@@ -25,7 +25,7 @@
 namespace kc {
 
 // Workgroups of the persistent region pass: as many as the CUs hold at once
-// (one per CU with the 144 KiB arrays, two with the 72 KiB ones), at most one
+// (one per CU with 128 KiB of counters, two with 64 KiB), at most one
 // per region.
 uint32_t region_grid(uint32_t n_regions, uint32_t counters) {
     static int n_cu = 0;
@@ -487,59 +487,27 @@ bool bin_plan(const FilterArgs &F, uint64_t chunk_positions, BinPlan &B, uint32_
     B = BinPlan{};
     B.region_shift = shift;
     B.region_counters = region_counters;
-    B.slice = kSlice;
-    if (n_regions > (1ull << part_log)) {
-        // partitioned: bin workgroups count partitions, passes over each
-        // partition's list bin its regions as the single-level path does
-        const uint64_t np = (n_regions + (1ull << part_log) - 1) >> part_log;
-        if (np > kMaxParts)
-            return false;
-        B.n_regions = (uint32_t)n_regions;
+    const uint64_t np = (n_regions + (1ull << part_log) - 1) >> part_log;
+    if (np > kMaxParts)
+        return false;
+    B.n_regions = (uint32_t)n_regions;
+    if (np > 1) {  // partitioned
         B.n_parts = (uint32_t)np;
         B.part_log = part_log;
-        // 64 buckets per partition (fewer for tiny test partitions), so that
-        // global bucket b holds regions [b << bshift, (b + 1) << bshift)
-        B.bucket_shift = part_log >= 6 ? part_log - 6 : 0;
-        B.n_buckets = (uint32_t)((n_regions + (1ull << B.bucket_shift) - 1) >> B.bucket_shift);
-        // list workgroups per partition: about kListWGs in all, and region /
-        // bucket count matrices of bounded size
-        uint64_t lg = (kListWGs + np - 1) / np;
-        if (lg > kMaxListG)
-            lg = kMaxListG;
-        if (lg * n_regions > kMaxMatrix)
-            lg = kMaxMatrix / n_regions;
-        const uint64_t nbp = (1ull << part_log) >> B.bucket_shift;
-        if (lg * np * nbp > kMaxCoarse)
-            lg = kMaxCoarse / (np * nbp);
-        if (lg == 0)
-            return false;
-        B.list_g = (uint32_t)lg;
-        uint64_t tile = kBinTileMin;
-        while ((chunk_positions + tile - 1) / tile * np > kMaxMatrix)
-            tile *= 2;
-        B.tile = tile;
-        B.G = (uint32_t)((chunk_positions + tile - 1) / tile);
-        B.n_slices = (B.G + B.slice - 1) / B.slice;
+        uint64_t g = (kPartRooms + np - 1) / np;
+        g = g > kMaxPartRooms ? kMaxPartRooms : g;
+        B.rooms = (uint32_t)(g * n_regions > kMaxMatrix ? kMaxMatrix / n_regions : g);
         return true;
     }
-    B.n_regions = (uint32_t)n_regions;
-    uint32_t bshift = 0;
-    while (((n_regions + (1ull << bshift) - 1) >> bshift) > kMaxBuckets)
-        bshift++;
-    B.bucket_shift = bshift;
-    B.n_buckets = (uint32_t)((n_regions + (1ull << bshift) - 1) >> bshift);
-    // positions per bin workgroup: kBinTileMin, enough to amortise the
-    // histograms (small chunks: fewer, down to kBinTileFloor, so that about
-    // kBinSpread workgroups still spread over the chip), and a region matrix
-    // of at most kMaxMatrix counts
-    uint64_t tile = (chunk_positions + kBinSpread - 1) / kBinSpread;
+    // small chunks of the countBF have kRoomSpread rooms at most: a reservation
+    // covers every smaller insert
+    uint64_t tile = (chunk_positions + kRoomSpread - 1) / kRoomSpread;
     tile = (tile + kBinWG - 1) / kBinWG * kBinWG;
-    tile = tile < kBinTileFloor ? kBinTileFloor : (tile > kBinTileMin ? kBinTileMin : tile);
+    tile = tile < kRoomFloor ? kRoomFloor : (tile > kRoomMin ? kRoomMin : tile);
     while ((chunk_positions + tile - 1) / tile * n_regions > kMaxMatrix)
         tile *= 2;
-    B.tile = tile;
-    B.G = (uint32_t)((chunk_positions + tile - 1) / tile);
-    B.n_slices = (B.G + B.slice - 1) / B.slice;
+    const uint64_t g = (chunk_positions + tile - 1) / tile;
+    B.rooms = (uint32_t)(g > kRoomSpread ? g : kRoomSpread);
     return true;
 }
 

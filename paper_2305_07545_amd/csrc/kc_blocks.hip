@@ -1636,13 +1636,12 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
                                bool classify, uint32_t tau, const Carry &carry, bool records,
                                hipStream_t s, Profiler *P) {
     const uint64_t len = c1 - c0;
-    // Rooms of the workspace (sized by the plan's count matrices and 8-byte
-    // entries, more than these lists need).  One-level form: the list in
-    // entries, the table in the count matrix's room or the slot ids', the
-    // turned table in the second matrix's or behind the list.  Two-level form:
-    // the blocks' list and table in bucketed, the superblocks' list and starts
-    // in entries (small calls: the table and starts in the matrices' rooms).
-    // Records take bucketed, which either form has read by then.
+    // Rooms of the workspace.  One-level form: the list in entries, the table in
+    // the first matrix or in slots, the turned table in the second matrix or
+    // behind the list.  Two-level form: the blocks' list and table in bucketed,
+    // the superblocks' list and starts in entries (small calls: the table and
+    // starts in the matrices).  Records take bucketed, which either form has
+    // read by then.
     const uint64_t last = c1 - c0 - ((uint64_t)(B.n_blocks - 1) << B.pos_log);
     const uint64_t n_list = ((uint64_t)(B.n_blocks - 1) * B.cap + last * F.k_h + 15) / 16 * 16;
     const uint64_t room = 8 * W.entries_cap;  // bytes of entries, and of bucketed
@@ -1715,7 +1714,6 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
     RecordSpace rec{};
     while ((len + (1ull << rec.log) - 1) >> rec.log > kMarkBuckets || rec.log < 12)
         rec.log++;
-    rec.n_buckets = (uint32_t)((len + (1ull << rec.log) - 1) >> rec.log);
     const bool own = records || carry.mode == Carry::kOut;  // records in the regions' own room
     const bool sparse = B.by_entry && !own && carry.mode == Carry::kNone && 8 * len * F.k_h <= room;
     if (records || carry.mode == Carry::kOut || sparse) {
@@ -1726,8 +1724,8 @@ hipError_t launch_blocks_chunk(const FilterArgs &F, const ReadsArgs &R, uint64_t
             rec.room = (uint64_t)F.k_h << rec.log;
             rec.word = (uint32_t *)W.bucketed;  // the sorted records; the dense ones after them
         } else if (records) {
-            uint32_t *index = B.two ? W.matrix_t : W.coarse;
-            if (2ull * plan.n_regions > (B.two ? W.matrix_cap : W.coarse_cap))
+            uint32_t *index = B.two ? W.matrix_t : W.index;
+            if (2ull * plan.n_regions > (B.two ? W.matrix_cap : W.index_cap))
                 return hipErrorInvalidValue;
             rec.word = (uint32_t *)W.bucketed;
             rec.half = (uint16_t *)(rec.word + W.entries_cap);

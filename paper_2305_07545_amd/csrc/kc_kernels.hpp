@@ -19,20 +19,16 @@ constexpr uint64_t kChunk = 1ull << 31;
 
 // Binned path
 constexpr int kBinWG = 512;                  // threads per bin workgroup
-constexpr uint64_t kBinTileMin = 65536;      // positions per bin workgroup (at least)
-constexpr uint64_t kBinTileFloor = 4096;     // ... for chunks of fewer than kBinSpread tiles
-constexpr uint64_t kBinSpread = 2048;        // bin workgroups a small chunk is spread over
+// Rooms of a chunk's tables (BinPlan::rooms): one for each of so many positions
+constexpr uint64_t kRoomMin = 65536;         // positions per room (at least)
+constexpr uint64_t kRoomFloor = 4096;        // ... for chunks of fewer than kRoomSpread rooms
+constexpr uint64_t kRoomSpread = 2048;       // rooms of a small chunk
 constexpr int kRegionWG = 1024;              // threads per region workgroup
 constexpr int kRegionCounters = 16384;       // counters per region: hits + first = 128 KiB LDS
 constexpr int kSmallRegionCounters = 8192;   // the smaller region choice: 64 KiB
-constexpr uint32_t kMaxRegions = 16384;      // LDS histogram of the bin kernels: 64 KiB
-constexpr uint64_t kMaxMatrix = 1ull << 25;  // (region, bin workgroup) counts per chunk
+constexpr uint32_t kMaxRegions = 16384;      // regions of an unpartitioned plan
+constexpr uint64_t kMaxMatrix = 1ull << 25;  // (region, room) words per chunk
 constexpr uint64_t kBinChunk = 1ull << 28;   // positions per binned chunk (entries < 2^31)
-constexpr uint32_t kMaxBuckets = 64;         // level-1 buckets (groups of regions)
-constexpr uint32_t kMaxRegionsPerBucket = kMaxRegions / kMaxBuckets;
-constexpr int kStage = 4096;                 // entries staged per batch in LDS: 32 KiB
-constexpr uint32_t kStageLog = 12;           // kStage == 1 << kStageLog
-constexpr uint32_t kSlice = 32;              // bin workgroups per level-2 workgroup
 constexpr int kTileGrid = 2048;              // workgroups of the persistent tile kernels
 // Partitioned binned path, for countBFs of more than kMaxRegions regions:
 // partition p holds regions [p * kMaxRegions, (p + 1) * kMaxRegions)
@@ -40,29 +36,19 @@ constexpr uint32_t kPartLog = 14;            // kMaxRegions == 1 << kPartLog
 constexpr uint32_t kMaxParts = 256;          // partitions (4M regions: 64 GB at alpha = 8)
 // positions per partitioned chunk: entry offsets and chunk-relative positions
 // are 32-bit (chunk * k_h < 2^32, t < 2^32 - 1, the idle first-seen value),
-// and a multiple of the largest bin tile; the countBF is read and written
-// once per chunk, so an 8 Gbase insert takes two passes over it
+// and a multiple of kRoomMin; the countBF is read and written once per chunk, so an 8 Gbase insert takes two passes over it
 constexpr uint64_t kPartChunk = (1ull << 32) - (1ull << 16);
-constexpr uint32_t kListWGs = 4096;          // list workgroups over all partitions, about
-constexpr uint32_t kMaxListG = 512;          // list workgroups per partition (at most)
-constexpr uint64_t kMaxCoarse = 1ull << 19;  // (partition bucket, list workgroup) counts
+constexpr uint32_t kPartRooms = 4096;        // rooms over all partitions, about
+constexpr uint32_t kMaxPartRooms = 512;      // rooms per partition (at most)
 constexpr int kSuper = 4;                    // tiles per iteration of the tile kernels
 constexpr uint32_t kWinCursors = 256 + 256 * 32;  // winner passes: level-A and block cursors
 
 struct BinPlan {
     uint32_t region_shift;  // log2(cells per region)
     uint32_t n_regions;
-    uint32_t bucket_shift;  // log2(regions per bucket)
-    uint32_t n_buckets;
-    uint32_t G;             // bin workgroups of the chunk
-    uint32_t slice;         // bin workgroups per level-2 workgroup
-    uint32_t n_slices;
-    uint64_t tile;          // positions per bin workgroup (multiple of kBinWG)
-    uint64_t entries_cap;   // capacity of each entry list
+    uint32_t rooms;         // words per region that a chunk's tables get in each matrix
     uint32_t n_parts;       // partitioned path: partitions (0: regions binned directly)
     uint32_t part_log;      // partitioned path: log2(regions per partition) <= kPartLog
-    uint32_t region0;       // global index of region 0 of the launch (0 but in tests)
-    uint32_t list_g;        // partitioned path: list workgroups per partition
     uint32_t region_counters;  // counters per region (kRegionCounters or kSmallRegionCounters)
 };
 
@@ -82,24 +68,22 @@ struct Workspace {
     uint64_t *tmask = nullptr;    // tile_cap * kTile / 64 classification bits
     uint64_t *partial64 = nullptr;
     uint64_t tile_cap = 0;
-    // binned path (per chunk)
-    uint32_t *matrix = nullptr;   // matrix_cap region counts, scanned in place to offsets
-    uint32_t *matrix_t = nullptr; // matrix_cap counts as the bin workgroups write them
-                                  // (workgroup-major), transposed into matrix
-    uint32_t *coarse = nullptr;   // coarse_cap bucket counts, scanned in place to offsets
-    uint32_t *partial32 = nullptr;
-    uint64_t matrix_cap = 0, coarse_cap = 0;
-    uint32_t *slots = nullptr;    // slots_cap slot ids (position-major per hash function)
+    // binned paths (per chunk); which table lies where: launch_blocks_chunk
+    uint32_t *matrix = nullptr;   // matrix_cap words for the blocks' table or the superblocks'
+                                  // starts
+    uint32_t *matrix_t = nullptr; // matrix_cap words for the turned table, or the records'
+                                  // index and the blocks' table
+    uint64_t matrix_cap = 0;
+    uint32_t *index = nullptr;    // one-level form: offset and count of every region's records
+    uint64_t index_cap = 0;
+    uint32_t *slots = nullptr;    // slots_cap words (4 bytes per position and hash function):
+                                  // a table that `matrix` is too small for
     uint64_t slots_cap = 0;
-    uint64_t *bucketed = nullptr; // entries_cap entries grouped by bucket
-    uint64_t *entries = nullptr;  // entries_cap entries grouped by region
+    uint64_t *bucketed = nullptr; // entries_cap x 8 bytes: the blocks' list of the two-level
+                                  // form, then the first-seen records
+    uint64_t *entries = nullptr;  // entries_cap x 8 bytes: the list the region pass reads, then
+                                  // the winner passes' first area
     uint64_t entries_cap = 0;
-    // partitioned binned path (per chunk): slot ids and partition bytes in
-    // `bucketed`, the partition lists in `entries` (see launch_parts_chunk)
-    uint32_t *pmat = nullptr;     // pmat_cap (partition, bin workgroup) counts -> offsets
-    uint64_t pmat_cap = 0;
-    uint32_t *pbounds = nullptr;  // kMaxParts + 1 partition starts in plist
-    uint64_t *pdesc = nullptr;    // kMaxParts x (list start, entries, list tile)
     // scalars
     uint64_t *totals = nullptr;   // 8 scan totals / saved counters
     uint32_t *n_entries = nullptr;  // 4 entry totals
@@ -121,32 +105,6 @@ struct Workspace {
 
 inline uint64_t tiles(uint64_t n) { return (n + kTile - 1) / kTile; }
 
-// Exclusive sum over a workgroup of kWG threads; `total` receives the sum.
-// Every thread of the workgroup must call it (it synchronises).
-__device__ __forceinline__ uint32_t wg_exclusive_u32(uint32_t v, uint32_t *s_wave,
-                                                     uint32_t &total) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = threadIdx.x >> 6;
-    uint32_t incl = v;
-    for (uint32_t d = 1; d < 64; d <<= 1) {
-        uint32_t o = __shfl_up(incl, d, 64);
-        if (lane >= d)
-            incl += o;
-    }
-    if (lane == 63)
-        s_wave[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0;
-    total = 0;
-    for (uint32_t w = 0; w < kWG / 64; w++) {
-        const uint32_t t = s_wave[w];
-        if (w < wave)
-            before += t;
-        total += t;
-    }
-    __syncthreads();
-    return before + incl - v;
-}
 // Exclusive sum over one wavefront (lane = threadIdx.x & 63); `total`
 // receives the wavefront's sum on every lane.
 __device__ __forceinline__ uint32_t wave_exclusive(uint32_t v, uint32_t lane, uint32_t &total) {

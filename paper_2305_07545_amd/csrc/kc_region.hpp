@@ -10,14 +10,6 @@
 
 namespace kc {
 
-// Element at a 32-bit byte offset from a wavefront-uniform base: the address
-// is the base's scalar registers plus one 32-bit vector register, not a
-// 64-bit address per thread.
-template <typename T>
-__device__ __forceinline__ T &at_byte(T *base, uint32_t byte_off) {
-    return *(T *)((char *)base + byte_off);
-}
-
 // The carried records of region r (chunks 0 .. n_prev - 1): trustworthy (3)
 // when the counter's final value, staged in s_cell, is above tau.
 __device__ __forceinline__ void mark_carried(const FilterArgs &F, uint32_t shift, const Carry &C,
@@ -44,7 +36,7 @@ __device__ __forceinline__ void mark_carried(const FilterArgs &F, uint32_t shift
 // of word (t) and half (mark), in room reserved at cursor[0].
 struct RecordSpace {
     uint32_t *sorted;
-    uint32_t log, n_buckets;
+    uint32_t log;
     uint64_t room;
     uint32_t *word;
     uint16_t *half;
