@@ -382,3 +382,14 @@ def test_small_sparse_regions(n, X, Y, alpha, k_h, env, monkeypatch):
     for name, v in env.items():
         monkeypatch.setenv(name, v)
     test_block_form_against_the_oracle(n, X, Y, alpha, k_h, 31)
+
+
+# Carried chunks of which the last is worked by entry (its own records in the
+# regions' room, unforced), after denser ones and sparse ones
+@pytest.mark.parametrize("n,chunk,X,Y,alpha", [
+    (400_000, 1 << 17, 5779, 5813, 8), (400_000, 1 << 17, 3833, 3837, 4),
+    (300_500, 300_032, 1511, 1523, 1), (4_000_000, 3_999_744, 1811, 1737, 8),
+])
+def test_carried_chunks_by_entry(n, chunk, X, Y, alpha, monkeypatch):
+    monkeypatch.setenv("KMERCO_CHUNK_POSITIONS", str(chunk))
+    test_block_form_against_the_oracle(n, X, Y, alpha, 1, 31)
