@@ -303,7 +303,7 @@ hipError_t launch_sort_records(const uint32_t *in, const uint32_t *n, uint32_t *
 // bucket's cursor[g] records (position | mark << log, `room` apart): bitmaps
 // in LDS, every word of the bucket's tiles written.  clean: the cursor is left
 // zero for the next chunk.  c0 is a multiple of the tile.
-// Bound by its clears and LDS atomics at one or two workgroups per CU: 0.07 ms
+// Bound by its clears and LDS atomics at one or two workgroups per CU: 0.09 ms
 // over 150 M positions; the byte flags cost 0.20 ms to store at random and
 // 0.17 ms to read again in the compaction (0.07 from bits).
 // kLog: the bitmaps' room; the smaller ones leave room for several workgroups

@@ -1,6 +1,6 @@
 // Binned insertion over block-sorted entry lists.
 //
-// The hashing workgroup of a block (at most 16384 entries) sorts them by
+// The hashing workgroup of a block (at most 32768 entries) sorts them by
 // region in LDS and writes them as one contiguous run, with a table of the
 // 16-bit offset of every region's run inside the block.  Nothing has to be
 // counted before: a block's place in the list is fixed, so there are no count
@@ -14,8 +14,9 @@
 // into 37 regions 67 instead of 112 us.
 //
 // An entry is 32 bits: the counter within the region (14 bits) and the
-// position within the block (14 bits); the block gives the rest of the
-// position.
+// position within the block (15 bits); the block gives the rest of the
+// position.  The two-level form, for many regions, adds the region within its
+// bucket, in 40 bits in all.
 #include <hip/hip_runtime.h>
 
 #include <utility>
@@ -56,9 +57,10 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, kJ...>, Fn f
 // entries take later), so that every lane hashes one at each step.  A
 // thread's entries stay in registers between hashing, where the histogram's
 // atomic also gives each entry's rank in its region, and staging.  Bound by
-// its vector instructions (79 to 82% busy; about 130 per 64 windows, 117 of
-// them the hash): 0.585 ms for 116 M windows over 3914 regions, where hashing
-// alone and writing slot ids took 0.43 and the sorting passes after it 0.88.
+// its vector instructions (77 to 82% busy; 153 per 64 windows, 155 in the
+// two-level form, 117 of them the hash): 0.585 ms for 116 M windows over 3914
+// regions, where hashing alone and writing slot ids took 0.43 and the sorting
+// passes after it 0.88.
 template <int kWG, int kEpt, int kKh, bool kFast, bool kWide, bool kTwo>
 __global__ void __launch_bounds__(kWG, 4)
 k_hash_sort(FilterArgs F, ReadsArgs R, uint64_t n_words, uint64_t c0, uint64_t c1, BlockPlan B,

@@ -36,7 +36,8 @@ constexpr uint32_t kPartLog = 14;            // kMaxRegions == 1 << kPartLog
 constexpr uint32_t kMaxParts = 256;          // partitions (4M regions: 64 GB at alpha = 8)
 // positions per partitioned chunk: entry offsets and chunk-relative positions
 // are 32-bit (chunk * k_h < 2^32, t < 2^32 - 1, the idle first-seen value),
-// and a multiple of kRoomMin; the countBF is read and written once per chunk, so an 8 Gbase insert takes two passes over it
+// and a multiple of kRoomMin; the countBF is read and written once per chunk,
+// so an 8 Gbase insert takes two passes over it
 constexpr uint64_t kPartChunk = (1ull << 32) - (1ull << 16);
 constexpr uint32_t kPartRooms = 4096;        // rooms over all partitions, about
 constexpr uint32_t kMaxPartRooms = 512;      // rooms per partition (at most)

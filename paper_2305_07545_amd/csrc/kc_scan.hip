@@ -1,6 +1,7 @@
-// Multi-workgroup exclusive prefix sums (block sums, then a rescan of each
-// block with the sum of the blocks before it) used for the ordered outputs
-// and the bin offsets.
+// Multi-workgroup exclusive prefix sums: block sums, then a rescan of each
+// block with the sum of the blocks before it (key-list classification, the
+// batched form's outputs and bin offsets), and a one-pass scan of the tiles'
+// counts (the single-set pipeline's ordered outputs).
 #include <hip/hip_runtime.h>
 
 #include "kc_kernels.hpp"
