@@ -1072,10 +1072,10 @@ k_region_runs(FilterArgs F, uint64_t c0, BinPlan P, BlockPlan B,
 //
 // The sweep over all counters cost 5.8 us a region and workgroup however few
 // entries it had; this takes 3.1 with 50 and 4.0 with 1.9 K entries (62 K
-// regions: 1.67 -> 0.97 ms), bound by memory latency behind 32 KB of cells and
-// 20 KB of entries and records a region.  Two barriers a region here, and what the next region needs
-// (cells, entries; bounds of the one after) is requested before its entries
-// are counted.
+// regions: 1.67 -> 0.98 ms), bound by memory latency behind 32 KB of cells and
+// 20 KB of entries and records a region.  Two barriers a region here, and what
+// the next region needs (cells, entries; bounds of the one after) is requested
+// before its entries are counted.
 //
 // kRecords: where the records go.
 // kFlat: dense in `flat`, their room asked for when a region's records are
